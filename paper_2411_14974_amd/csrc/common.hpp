@@ -63,10 +63,12 @@ struct RenderArgs {
 
 // One view of a (possibly batched) render, as the kernels read it from device
 // memory.  Tiles of all views share one global index space: view v owns
-// [tile_off, tile_off + tiles_x * tiles_y); its per-pixel state starts at pix_off.
+// [tile_off, tile_off + tiles_x * tiles_y); its per-pixel state starts at pix_off;
+// its cells, blocks of 2^cell_shift x 2^cell_shift tiles, start at cell_off.
 struct ViewDesc {
     CamArgs cam;
-    int32_t tiles_x, tiles_y, tile_off, pad;
+    int32_t tiles_x, tiles_y, tile_off, cell_off;
+    uint32_t cell_shift, pad;
     int64_t pix_off;
     float *out_rgb;        // [H][W][3]
     const float *dl_drgb;  // [H][W][3], backward only
@@ -75,12 +77,52 @@ struct ViewDesc {
 // Header of the device view table; the ViewDesc array follows it.  Kernels
 // read the view count and the tile total from here, so a captured graph can be
 // replayed with other cameras and resolutions.
+//
+// Convexes are binned by cell, a block of S x S tiles of a view (S = 1, 2 or 4):
+// one (cell, convex) pair carries the mask of the cell's tiles that the convex
+// can reach, so one sorted pair stands for up to S^2 (tile, convex) pairs (at
+// 1M convexes, 1080p: 2.3 M sorted pairs instead of 8.9 M), and a tile's
+// depth-ordered list is its cell's list filtered by the tile's mask bit.  A
+// view has the smallest cells of which VIEW_CELLS cover it, at most 4 x 4: a
+// small view's convexes are smaller than a few tiles, and large cells would
+// only lengthen the lists that its tiles filter (200k convexes at 256 x 256:
+// 0.29 ms with the 256 tiles as cells, 0.46 ms with 16 cells).
+// A pair's sort key holds the cell in its low key_bits bits, the mask above:
+// 16 + 16 bits, or 28 + 4 (cells of at most 2 x 2) when a call has more cells.
 struct FrameHeader {
     uint32_t nviews, total_tiles;
     int64_t total_pix;
-    uint32_t pad[12];
+    uint32_t total_cells, key_bits;
+    uint32_t pad[10];
 };
+constexpr uint32_t VIEW_CELLS = 512; // one 9-bit pass sorts a view's pairs
+constexpr uint32_t MAX_CELLS_16 = 1u << 16;
+constexpr uint32_t MAX_CELL_PAIRS = (1u << 30) - 1u; // (cell, convex) pairs of one call stay below this
 static_assert(sizeof(FrameHeader) == 64, "frame header is 64 bytes");
+
+// The view that owns the global tile gt.
+__device__ __forceinline__ int find_view(const ViewDesc *__restrict__ views, int nviews, int gt)
+{
+    int lo = 0, hi = nviews - 1;
+    while (lo < hi) {
+        const int mid = (lo + hi + 1) >> 1;
+        if (views[mid].tile_off <= gt) lo = mid;
+        else hi = mid - 1;
+    }
+    return lo;
+}
+// The global cell of a view's tile (tx, ty).
+__host__ __device__ __forceinline__ uint32_t tile_cell(const ViewDesc &vd, uint32_t tx, uint32_t ty)
+{
+    const uint32_t s = vd.cell_shift;
+    return (uint32_t)vd.cell_off + (ty >> s) * (((uint32_t)vd.tiles_x + (1u << s) - 1u) >> s) + (tx >> s);
+}
+// The key bit of a view's tile (tx, ty) in its cell's pairs.
+__host__ __device__ __forceinline__ uint32_t tile_bit(const ViewDesc &vd, uint32_t key_bits, uint32_t tx, uint32_t ty)
+{
+    const uint32_t s = vd.cell_shift, side = (1u << s) - 1u;
+    return 1u << (key_bits + ((ty & side) << s) + (tx & side));
+}
 
 constexpr int MAX_VIEWS = 256;
 constexpr int NUM_QUEUES = 8; // one work queue per XCD
@@ -95,8 +137,9 @@ constexpr int EVAL_SLOTS = 16384;
 enum : int { EV_TESTED = 0, EV_FULL = 1, EV_SUM_T = 2, EV_WAVES = 3, EVAL_FIELDS = 4 };
 
 // Device counters of one frame (u32 words).
-// Per-instance binning record (16 bytes): the tile rectangle, tx0 | ty0 << 16
-// and tx1 | ty1 << 16 (empty when tx0 > tx1), and 64 bits of kept tiles:
+// Per-instance binning record (16 bytes): the view's cell shift and the tile
+// rectangle, tx0 | shift << 12 | ty0 << 16 and tx1 | ty1 << 16 (empty when tx0 >
+// tx1; a view has at most 2048 tiles a side), and 64 bits of kept tiles:
 //  - a rectangle of at most 64 tiles: the mask of kept tiles (bit
 //    (ty - ty0) * width + (tx - tx0));
 //  - a larger one: its rows are grouped into at most BIG_BANDS bands of
@@ -104,11 +147,16 @@ enum : int { EV_TESTED = 0, EV_FULL = 1, EV_SUM_T = 2, EV_WAVES = 3, EVAL_FIELDS
 //    blocks of ceil(tw / 2^BIG_BITS) tiles; field r (2 BIG_BITS bits) holds
 //    band r's kept blocks as the interval bx0 | bx1 << BIG_BITS (empty when
 //    bx0 > bx1), and the band keeps every tile of those blocks.
-__host__ __device__ inline uint4 make_bin(int tx0, int ty0, int tx1, int ty1, uint64_t mask)
+__host__ __device__ inline uint4 make_bin(int tx0, int ty0, int tx1, int ty1, uint64_t mask, uint32_t shift)
 {
-    return make_uint4((uint32_t)tx0 | ((uint32_t)ty0 << 16), (uint32_t)tx1 | ((uint32_t)ty1 << 16), (uint32_t)mask,
+    return make_uint4((uint32_t)tx0 | (shift << 12) | ((uint32_t)ty0 << 16), (uint32_t)tx1 | ((uint32_t)ty1 << 16), (uint32_t)mask,
                       (uint32_t)(mask >> 32));
 }
+__host__ __device__ inline uint32_t bin_shift(uint4 b) { return (b.x >> 12) & 15u; }
+__host__ __device__ inline uint32_t bin_tx0(uint4 b) { return b.x & 0xFFFu; }
+__host__ __device__ inline uint32_t bin_ty0(uint4 b) { return b.x >> 16; }
+__host__ __device__ inline uint32_t bin_tx1(uint4 b) { return b.y & 0xFFFFu; }
+__host__ __device__ inline uint32_t bin_ty1(uint4 b) { return b.y >> 16; }
 #ifndef CS_BIG_BANDS
 #define CS_BIG_BANDS 4
 #endif
@@ -146,7 +194,7 @@ __host__ __device__ inline void big_band(uint64_t mask, int tw, int th, int r, i
 }
 __device__ inline uint32_t bin_count(uint4 b)
 {
-    const int tx0 = (int)(b.x & 0xFFFFu), ty0 = (int)(b.x >> 16), tx1 = (int)(b.y & 0xFFFFu), ty1 = (int)(b.y >> 16);
+    const int tx0 = (int)bin_tx0(b), ty0 = (int)bin_ty0(b), tx1 = (int)bin_tx1(b), ty1 = (int)bin_ty1(b);
     if (tx0 > tx1 || ty0 > ty1) return 0u;
     const int tw = tx1 - tx0 + 1, th = ty1 - ty0 + 1;
     const uint64_t mask = (uint64_t)b.z | ((uint64_t)b.w << 32);
@@ -159,6 +207,15 @@ __device__ inline uint32_t bin_count(uint4 b)
         c += (uint32_t)(nrow * ncol);
     }
     return c;
+}
+
+// The cells that a binning record's tile rectangle meets: each is one pair (a
+// cell whose kept tiles are all culled included: its mask is empty).
+__device__ inline uint32_t bin_cells(uint4 b)
+{
+    const uint32_t tx0 = bin_tx0(b), ty0 = bin_ty0(b), tx1 = bin_tx1(b), ty1 = bin_ty1(b), s = bin_shift(b);
+    if (tx0 > tx1 || ty0 > ty1) return 0u;
+    return ((tx1 >> s) - (tx0 >> s) + 1u) * ((ty1 >> s) - (ty0 >> s) + 1u);
 }
 
 // Up to two word ranges that a kernel clears on the side (each block its
@@ -183,6 +240,8 @@ __device__ inline void zero_share(const ZeroSpans &z)
 // Layout of a frame's counter buffer (32-bit words):
 //   [0, CNT_WORDS)            counters read back by the host:
 //     CNT_SORT_ERR: a radix-sort look-back wait ran out of its bound (never expected)
+//     CNT_PAIRS: (cell, convex) pairs; CNT_PAIRS_EFF: those that fit the buffers
+//     CNT_TILE_PAIRS: (tile, convex) pairs that they stand for
 //     CNT_SCAN_TILE: tile claims of the pair-offset scan
 //   [CNT_QUEUE, CNT_QUEUE_B)  the forward compositing's work queues' claim
 //                             counters, one per QUEUE_STRIDE words: device-scope
@@ -191,7 +250,7 @@ __device__ inline void zero_share(const ZeroSpans &z)
 //   [CNT_QUEUE_B, CNT_STATUS) the backward compositing's (cleared with the rest
 //                             when the forward starts)
 //   [CNT_STATUS, ...)         the pair-offset scan's look-back status (u64 per tile)
-enum : int { CNT_PAIRS = 0, CNT_PAIRS_EFF = 1, CNT_OVERFLOW = 2, CNT_SORT_ERR = 3, CNT_SCAN_TILE = 20, CNT_WORDS = 32 };
+enum : int { CNT_PAIRS = 0, CNT_PAIRS_EFF = 1, CNT_OVERFLOW = 2, CNT_SORT_ERR = 3, CNT_TILE_PAIRS = 4, CNT_SCAN_TILE = 20, CNT_WORDS = 32 };
 constexpr int QUEUE_STRIDE = 1024; // 4 KiB
 constexpr int CNT_QUEUE = CNT_WORDS;
 constexpr int QUEUE_WORDS = NUM_QUEUES * QUEUE_STRIDE;

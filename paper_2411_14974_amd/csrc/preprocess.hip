@@ -456,7 +456,8 @@ __global__ __launch_bounds__(PF_BLOCK) void preprocess_fwd_kernel(
     const bool has_tiles = status == ST_VISIBLE && tx0 <= tx1 && ty0 <= ty1;
     if (active) {
         keys[inst] = status == ST_VISIBLE ? key : KEY_CULLED;
-        bins[inst] = has_tiles ? make_bin(tx0, ty0, tx1, ty1, tmask) : make_bin(1, 0, 0, 0, 0);
+        const uint32_t shift = reinterpret_cast<const ViewDesc *>(frame + 1)[blockIdx.y].cell_shift;
+        bins[inst] = has_tiles ? make_bin(tx0, ty0, tx1, ty1, tmask, shift) : make_bin(1, 0, 0, 0, 0, 0);
         // hull indices (3 bits each, bits 0-23), the clamped colour channels
         // (bits 24-26: the backward pass's colour gradient is zero there), T
         hullpk[inst] = (status == ST_VISIBLE || status == ST_FAINT)

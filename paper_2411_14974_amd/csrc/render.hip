@@ -2,8 +2,8 @@
 //
 // One workgroup per tile (8x8, 16x16 or 32x32 pixels), one pixel per thread,
 // in a persistent grid that pulls tiles of all views from per-XCD work queues.
-// The tile's depth-ordered convex list is streamed through LDS in batches of
-// records; every thread walks the batch front to back and evaluates, for its pixel,
+// The tile's depth-ordered convex list (its cell's list, filtered by the tile's
+// mask bit) is streamed through LDS in batches of records; every thread walks the batch front to back and evaluates, for its pixel,
 //   x2_j = log2(e) delta' L_j(q)           (FP64: hull lines, Supp. B scaling)
 //   phi  = LogSumExp of the x_j            (Sec. 3.1 Eq. smoothness, base 2)
 //   I    = Sigmoid(-sigma' phi)            (Sec. 3.1 Eq. sharpness)
@@ -292,22 +292,27 @@ template <int K, int RW = 8, int RH = 8> __device__ __forceinline__ bool square_
 }
 
 // Software pipeline of the LDS record batches.  While a batch is composited
-// from LDS, the records of the next batch are in flight into registers and
-// the list ids of the batch after that into a register, so a record load never
-// waits on its id load; one LDS record buffer and two LDS id buffers suffice.
+// from LDS, the records of the next batch are in flight into registers, and
+// the list is kept queued a batch further ahead (TileFeed), so a record load
+// seldom waits on its id load and one LDS record buffer suffices.
 template <int K, int NT, int BATCH> constexpr int pipe_regs() { return (BATCH * (rec_stride(K) / 16) + NT - 1) / NT; }
+
+// The thread index, opaque to the compiler: what a step between the record
+// loops derives from it (addresses, quotients, lane masks) is computed there
+// instead of being kept in registers across those loops.
+__device__ __forceinline__ int opaque_tid()
+{
+    int t = threadIdx.x;
+    asm volatile("" : "+v"(t));
+    return t;
+}
 
 // native 16-byte vector (HIP's uint4 is a struct with a union, which keeps a
 // register array of it in scratch)
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 
-__device__ __forceinline__ uint32_t pipe_load_id(const uint32_t *__restrict__ ids, int base, int cnt)
-{
-    return (int)threadIdx.x < cnt ? ids[base + threadIdx.x] : 0u;
-}
-
 template <int K, int NT, int NL>
-__device__ __forceinline__ void pipe_load_records(u32x4 (&pre)[NL], const uint32_t *s_ids,
+__device__ __forceinline__ void pipe_load_records(u32x4 (&pre)[NL], const uint2 *s_ring, uint32_t head, uint32_t ringmask,
                                                   const uint8_t *__restrict__ records, int cnt)
 {
     constexpr int CH = rec_stride(K) / 16;
@@ -316,18 +321,19 @@ __device__ __forceinline__ void pipe_load_records(u32x4 (&pre)[NL], const uint32
     for (int r = 0; r < NL; ++r) {
         const int c = min((int)threadIdx.x + r * NT, last);
         const int e = c / CH, part = c - e * CH;
-        pre[r] = reinterpret_cast<const u32x4 *>(records + (size_t)s_ids[e] * rec_stride(K))[part];
+        pre[r] = reinterpret_cast<const u32x4 *>(records + (size_t)s_ring[(head + e) & ringmask].x * rec_stride(K))[part];
     }
 }
 
 template <int K, int NT>
-__device__ __forceinline__ void load_records_direct(uint4 *lds, const uint32_t *s_ids, const uint8_t *__restrict__ records,
-                                                    int cnt)
+__device__ __forceinline__ void load_records_direct(uint4 *lds, const uint2 *s_ring, uint32_t head, uint32_t ringmask,
+                                                    const uint8_t *__restrict__ records, int cnt)
 {
     constexpr int CH = rec_stride(K) / 16;
-    for (int c = threadIdx.x; c < cnt * CH; c += NT) {
+    for (int c = opaque_tid(); c < cnt * CH; c += NT) {
         const int e = c / CH, part = c - e * CH;
-        reinterpret_cast<u32x4 *>(lds)[c] = reinterpret_cast<const u32x4 *>(records + (size_t)s_ids[e] * rec_stride(K))[part];
+        reinterpret_cast<u32x4 *>(lds)[c] =
+            reinterpret_cast<const u32x4 *>(records + (size_t)s_ring[(head + e) & ringmask].x * rec_stride(K))[part];
     }
 }
 
@@ -378,21 +384,107 @@ __device__ __forceinline__ uint32_t next_item(uint32_t *queues, uint32_t total, 
         *s_item = item;
     }
     __syncthreads();
-    const uint32_t item = *s_item;
+    // a scalar: what hangs on the item (view, cell, list, image size) then stays
+    // in scalar registers
+    const uint32_t item = (uint32_t)__builtin_amdgcn_readfirstlane((int)*s_item);
     __syncthreads();
     return item;
 }
 
-__device__ __forceinline__ int find_view(const ViewDesc *__restrict__ views, int nviews, int gt)
-{
-    int lo = 0, hi = nviews - 1;
-    while (lo < hi) {
-        const int mid = (lo + hi + 1) >> 1;
-        if (views[mid].tile_off <= gt) lo = mid;
-        else hi = mid - 1;
+// A tile's depth-ordered convex list, streamed out of its cell's list into a
+// ring in LDS that the batches of records are taken from.  A round reads the
+// keys of FEED_SUB * NT consecutive entries, front to back or (REVERSE) back
+// to front, and counts those with the tile's mask bit per wavefront; after a
+// barrier whole sub-rounds of NT entries are appended in order, as (id,
+// position in the cell's list), until enough are queued (the rest is read
+// again by the next round).  Only the entries that are appended have their
+// ids read.  About a quarter of a cell's entries are a given tile's at 1M
+// convexes and 1080p, but a twelfth where convexes are smaller than a tile
+// (200k convexes, 256 x 256), hence rounds of 4 NT: with rounds of NT that
+// view's compositing took twice as long.
+// While a batch is composited one sub-round is in flight
+// (request), which the kernels count before and appends after the barrier of the next
+// batch (publish, append): where the hits are dense enough, the list is then
+// read on without a wait.
+constexpr int FEED_SUB = 4;
+template <int NT, int RING, bool REVERSE> struct TileFeed {
+    static constexpr int NW = NT / 64;
+    const uint32_t *keys, *ids;  // the cell's list
+    int next, count;     // entries gone through / to go through
+    uint32_t hitmask;    // the tile's bit in a key
+    uint32_t head, tail; // ring positions: first queued entry, end
+    uint32_t k0, v0;     // the sub-round in flight: this thread's entry
+
+    __device__ __forceinline__ void request()
+    {
+        const int i = next + opaque_tid();
+        const uint32_t pos = (uint32_t)(REVERSE ? count - 1 - i : i);
+        k0 = i < count ? keys[pos] : 0u;
+        v0 = i < count ? ids[pos] : 0u;
     }
-    return lo;
-}
+    __device__ __forceinline__ void publish(uint32_t (*s_cnt)[NW])
+    {
+        const uint32_t c = (uint32_t)__popcll(__ballot((k0 & hitmask) != 0u));
+        const int t = opaque_tid();
+        if ((t & 63) == 0) s_cnt[0][t >> 6] = c;
+    }
+    __device__ __forceinline__ void append(uint32_t k, uint32_t v, bool have_v, int t, const uint32_t *cnt, uint2 *s_ring)
+    {
+        const int wave = t >> 6;
+        uint32_t at = tail, end = tail;
+#pragma unroll
+        for (int w = 0; w < NW; ++w) {
+            const uint32_t c = cnt[w];
+            if (w < wave) at += c;
+            end += c;
+        }
+        tail = (uint32_t)__builtin_amdgcn_readfirstlane((int)end);
+        const bool hit = (k & hitmask) != 0u;
+        const uint64_t m = __ballot(hit);
+        if (hit) {
+            const uint32_t rank = __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+            const int i = next + t, pos = REVERSE ? count - 1 - i : i;
+            s_ring[(at + rank) & (RING - 1)] = make_uint2(have_v ? v : ids[(uint32_t)pos], (uint32_t)pos);
+        }
+        next += NT;
+    }
+    __device__ __forceinline__ void start(const uint32_t *keys_, const uint32_t *ids_, int count_, uint32_t hitmask_)
+    {
+        keys = keys_; ids = ids_; count = count_; hitmask = hitmask_;
+        next = 0;
+        head = tail = 0;
+    }
+    __device__ __forceinline__ bool more() const { return next < count; }
+    __device__ __forceinline__ int queued() const { return (int)(tail - head); }
+    // Rounds until `want` entries are queued or the list is through (want <=
+    // RING - NT - the entries before head that are still in use).  Every thread
+    // calls it; returns with the ring readable.
+    __device__ __forceinline__ void fill(int want, uint32_t (*s_cnt)[NW], uint2 *s_ring)
+    {
+        while (queued() < want && more()) {
+            const int t = opaque_tid();
+            uint32_t k[FEED_SUB];
+#pragma unroll
+            for (int j = 0; j < FEED_SUB; ++j) {
+                const int i = next + j * NT + t;
+                k[j] = i < count ? keys[(uint32_t)(REVERSE ? count - 1 - i : i)] : 0u;
+            }
+#pragma unroll
+            for (int j = 0; j < FEED_SUB; ++j) {
+                const uint32_t c = (uint32_t)__popcll(__ballot((k[j] & hitmask) != 0u));
+                if ((t & 63) == 0) s_cnt[j][t >> 6] = c;
+            }
+            __syncthreads();
+#pragma unroll
+            for (int j = 0; j < FEED_SUB; ++j)
+                if (queued() < want && more()) append(k[j], 0u, false, t, s_cnt[j], s_ring);
+            __syncthreads();
+        }
+    }
+};
+// Entries of the ring: a sub-round, two batches queued and one in use (batches
+// of 64, of 32 at 64 threads).
+template <int NT> constexpr int feed_ring() { return NT >= 1024 ? 2048 : NT == 256 ? 512 : 256; }
 
 // The workgroup's work counters (per-lane tested / full / hull-size sums and
 // the wavefront's evaluation count, which every lane of a wavefront holds),
@@ -428,26 +520,30 @@ constexpr uint32_t FWD_CHUNK = 2;
 // outside the record loop, and the extra wavefront hides more of the LDS and
 // transcendental latency (0.183 -> 0.169 ms at 1M convexes, 1080p, against 4
 // wavefronts and 106 VGPRs without spills).
+constexpr int fwd_waves(int K, int TILE) { return K <= (TILE == 8 ? 4 : 6) ? 5 : 4; }
 template <int K, int TILE, int BATCH>
-__global__ __launch_bounds__(TILE *TILE) __attribute__((amdgpu_waves_per_eu(5))) void render_fwd_kernel(
+__global__ __launch_bounds__(TILE *TILE) __attribute__((amdgpu_waves_per_eu(fwd_waves(K, TILE)))) void render_fwd_kernel(
     const FrameHeader *__restrict__ frame, const uint32_t *__restrict__ order, uint32_t *__restrict__ queues,
-    const uint2 *__restrict__ ranges, const uint32_t *__restrict__ ids,
+    const uint2 *__restrict__ ranges, const uint32_t *__restrict__ keys, const uint32_t *__restrict__ ids,
     const uint8_t *__restrict__ records, RenderArgs ra, uint2 *__restrict__ pixstate,
     unsigned long long *__restrict__ evalcount, u32x4 *__restrict__ zero_acc, uint32_t zero_n4)
 {
     constexpr int NT = TILE * TILE;
     constexpr int CH = rec_stride(K) / 16;
-    static_assert(BATCH <= NT, "one id per thread");
+    constexpr int RING = feed_ring<NT>();
     static_assert(BATCH <= 64, "one ballot bit per batch entry");
+    constexpr int WANT = RING - NT - BATCH; // queued entries to go for: a batch may be in use, a sub-round may overshoot
+    static_assert(WANT >= 2 * BATCH, "the ring holds less than two batches");
     __shared__ uint4 lds[BATCH * CH];
-    __shared__ uint32_t s_ids[2][BATCH];
+    __shared__ uint2 s_ring[RING];
+    __shared__ uint32_t s_cnt[FEED_SUB][NT / 64];
     __shared__ uint32_t s_item;
     __shared__ unsigned long long s_ev[EVAL_FIELDS];
     const int lane = threadIdx.x & 63, wbit = threadIdx.x >> 6;
     if (threadIdx.x < EVAL_FIELDS) s_ev[threadIdx.x] = 0ull;
     constexpr int NL = pipe_regs<K, NT, BATCH>();
     u32x4 pre[NL];
-    uint32_t idr = 0;
+    TileFeed<NT, RING, false> feed;
     const ViewDesc *views = reinterpret_cast<const ViewDesc *>(frame + 1);
     const int nviews = (int)frame->nviews;
     const uint32_t total_tiles = frame->total_tiles;
@@ -479,32 +575,40 @@ __global__ __launch_bounds__(TILE *TILE) __attribute__((amdgpu_waves_per_eu(5)))
         const int su = tx * TILE + (wbit % (TILE / 8)) * 8, sv = ty * TILE + (wbit / (TILE / 8)) * 8; // wave's square
         const bool inside = u < W && y < H;
         const float pxf = (float)u + 0.5f, pyf = (float)y + 0.5f;
-        const uint2 rg = ranges[gt];
-        const int start = (int)rg.x, end = (int)rg.y;
+        // the tile's cell and its bit in the cell's keys
+        const uint2 rg = ranges[tile_cell(vd, (uint32_t)tx, (uint32_t)ty)];
+        const uint32_t hitmask = tile_bit(vd, frame->key_bits, (uint32_t)tx, (uint32_t)ty);
 
         float T = 1.0f, C0 = 0.0f, C1 = 0.0f, C2 = 0.0f, Tlast = 1.0f;
-        int nend = 0;
+        uint32_t nend = 0; // position after the last contributor in the cell's list
         bool done = !inside;
-        const int nb = (end - start + BATCH - 1) / BATCH;
-        if (nb > 0) { // prologue: ids of batches 0 and 1, records of batch 0
-            idr = pipe_load_id(ids, start, min(BATCH, end - start));
-            if ((int)threadIdx.x < BATCH) s_ids[0][threadIdx.x] = idr;
-            if (nb > 1) idr = pipe_load_id(ids, start + BATCH, min(BATCH, end - start - BATCH));
-            __syncthreads();
-            pipe_load_records<K, NT, NL>(pre, s_ids[0], records, min(BATCH, end - start));
+        int cnt = 0;
+        if (rg.y > rg.x) { // prologue: the first batch's ids, then its records
+            feed.start(keys + rg.x, ids + rg.x, (int)(rg.y - rg.x), hitmask);
+            feed.fill(2 * BATCH, s_cnt, s_ring); // most tiles need no more
+            feed.request();
+            cnt = min(BATCH, feed.queued());
+            if (cnt > 0) pipe_load_records<K, NT, NL>(pre, s_ring, feed.head, RING - 1, records, cnt);
         }
-        for (int bi = 0; bi < nb; ++bi) {
-            const int base = start + bi * BATCH;
-            const int cnt = min(BATCH, end - base);
-            __syncthreads();
+        while (cnt > 0) {
             pipe_store_records<K, NT, NL>(pre, lds, cnt);
-            if ((int)threadIdx.x < BATCH) s_ids[(bi + 1) & 1][threadIdx.x] = idr;
+            const bool refill = feed.queued() <= RING - NT && feed.more();
+            if (refill) feed.publish(s_cnt);
             __syncthreads();
-            if (bi + 2 < nb) idr = pipe_load_id(ids, base + 2 * BATCH, min(BATCH, end - base - 2 * BATCH));
-            if (bi + 1 < nb) pipe_load_records<K, NT, NL>(pre, s_ids[(bi + 1) & 1], records, min(BATCH, end - base - BATCH));
+            const uint32_t head = feed.head;
+            feed.head += (uint32_t)cnt;
+            // the next batch, of what the ring held before this refill (unless
+            // that is little: then the list is read on first)
+            const int ncnt = feed.queued() >= BATCH / 2 || !feed.more() ? min(BATCH, feed.queued()) : 0;
+            if (refill) {
+                feed.append(feed.k0, feed.v0, true, opaque_tid(), s_cnt[0], s_ring);
+                feed.request();
+            }
+            if (ncnt > 0) pipe_load_records<K, NT, NL>(pre, s_ring, feed.head, RING - 1, records, ncnt);
             // the wave's records of this batch (lane e tests entry e against
             // the wave's square), front to back in a wave-uniform walk
             uint64_t M = 0;
+            int last = -1; // the pixel's last contributor of this batch
             if (!__all(done)) {
                 const bool meets = lane < cnt && square_meets<K>(reinterpret_cast<const uint8_t *>(&lds[min(lane, BATCH - 1) * CH]), su, sv);
                 M = __ballot(meets);
@@ -528,12 +632,22 @@ __global__ __launch_bounds__(TILE *TILE) __attribute__((amdgpu_waves_per_eu(5)))
                     C2 = fmaf(w, h.rgb[2], C2);
                     Tlast = T;
                     T = T * pe.oma;
-                    nend = base - start + e + 1;
+                    last = e;
                     done = T < ra.t_min;
                 }
                 if (__all(done)) break;
             }
+            if (last >= 0) nend = s_ring[(head + (uint32_t)last) & (RING - 1)].y + 1u;
             if (__syncthreads_and(done)) break;
+            cnt = ncnt;
+            if (cnt == 0 && feed.queued() < BATCH && feed.more()) {
+                feed.fill(WANT, s_cnt, s_ring);
+                feed.request();
+            }
+            if (cnt == 0) {
+                cnt = min(BATCH, feed.queued());
+                if (cnt > 0) pipe_load_records<K, NT, NL>(pre, s_ring, feed.head, RING - 1, records, cnt);
+            }
         }
         if (inside) {
             const size_t pix = (size_t)y * W + u;
@@ -541,7 +655,7 @@ __global__ __launch_bounds__(TILE *TILE) __attribute__((amdgpu_waves_per_eu(5)))
             o[0] = fmaf(T, ra.bg[0], C0);
             o[1] = fmaf(T, ra.bg[1], C1);
             o[2] = fmaf(T, ra.bg[2], C2);
-            pixstate[vd.pix_off + pix] = make_uint2((uint32_t)nend, __float_as_uint(Tlast));
+            pixstate[vd.pix_off + pix] = make_uint2(nend, __float_as_uint(Tlast));
         }
     }
     if (evalcount) store_work_counts(evalcount, s_ev, nevals, nfull, 0u, 0u);
@@ -641,9 +755,9 @@ __device__ __forceinline__ void bwd_record(const uint8_t *rec, bool live, int u,
 }
 
 template <int K, int TILE, int BATCH>
-__global__ __launch_bounds__(TILE *TILE) void render_bwd_kernel(
+__global__ __launch_bounds__(TILE *TILE) __attribute__((amdgpu_waves_per_eu(K <= 6 ? 5 : 1))) void render_bwd_kernel(
     const FrameHeader *__restrict__ frame, const uint32_t *__restrict__ order, uint32_t *__restrict__ queues,
-    const uint2 *__restrict__ ranges, const uint32_t *__restrict__ ids,
+    const uint2 *__restrict__ ranges, const uint32_t *__restrict__ keys, const uint32_t *__restrict__ ids,
     const uint8_t *__restrict__ records, RenderArgs ra, const uint2 *__restrict__ pixstate,
     float *__restrict__ acc, unsigned long long *__restrict__ evalcount)
 {
@@ -651,10 +765,13 @@ __global__ __launch_bounds__(TILE *TILE) void render_bwd_kernel(
     constexpr int CH = rec_stride(K) / 16;
     constexpr int AS = acc_stride(K);
     constexpr int NP = bwd_padded<K>(); // LDS slot per batch entry (compact values of the largest hull)
-    static_assert(BATCH <= NT, "one id per thread");
+    constexpr int RING = feed_ring<NT>();
     static_assert(BATCH <= 64, "one ballot bit per batch entry");
+    constexpr int WANT = RING - NT - BATCH; // queued entries to go for: a batch may be in use, a sub-round may overshoot
+    static_assert(WANT >= 2 * BATCH, "the ring holds less than two batches");
     __shared__ uint4 lds[BATCH * CH];
-    __shared__ uint32_t s_ids[BATCH];
+    __shared__ uint2 s_ring[RING];
+    __shared__ uint32_t s_cnt[FEED_SUB][NT / 64];
     // per entry sums of the block's waves, flushed after each batch
     __shared__ float s_acc[BATCH * NP];
     __shared__ int s_maxn;
@@ -669,6 +786,7 @@ __global__ __launch_bounds__(TILE *TILE) void render_bwd_kernel(
     int q = blockIdx.x % NUM_QUEUES, tried = 0;
     uint32_t cnext = 0, cend = 0;
     uint32_t nfull = 0, nsumT = 0, nwave = 0;
+    TileFeed<NT, RING, true> feed;
     for (;;) {
         const uint32_t item = next_item<1>(queues, total_tiles, q, tried, cnext, cend, &s_item);
         if (item == 0xFFFFFFFFu) break;
@@ -684,7 +802,9 @@ __global__ __launch_bounds__(TILE *TILE) void render_bwd_kernel(
         const int su = tx * TILE + (wbit % (TILE / 8)) * 8, sv = ty * TILE + (wbit / (TILE / 8)) * 8; // wave's square
         const bool inside = u < W && y < H;
         const float pxf = (float)u + 0.5f, pyf = (float)y + 0.5f;
-        const int start = (int)ranges[gt].x;
+        // the tile's cell and its bit in the cell's keys
+        const uint2 rg = ranges[tile_cell(vd, (uint32_t)tx, (uint32_t)ty)];
+        const uint32_t hitmask = tile_bit(vd, frame->key_bits, (uint32_t)tx, (uint32_t)ty);
 
         BwdPixel P{0.f, 0.f, 0.f, 1.f, 1.f, ra.bg[0], ra.bg[1], ra.bg[2], true};
         int nend = 0;
@@ -703,32 +823,49 @@ __global__ __launch_bounds__(TILE *TILE) void render_bwd_kernel(
         __syncthreads();
         if (nend > 0) atomicMax(&s_maxn, nend);
         __syncthreads();
-        const int maxn = s_maxn;
+        const int maxn = min(__builtin_amdgcn_readfirstlane(s_maxn), (int)(rg.y - rg.x));
         int wmaxn = nend; // the wave's last contributor
 #pragma unroll
         for (int o = 32; o > 0; o >>= 1) wmaxn = max(wmaxn, __shfl_xor(wmaxn, o, 64));
+        wmaxn = __builtin_amdgcn_readfirstlane(wmaxn);
 
-        // batches walk the list back to front (the walk is VALU-bound: plain loads,
-        // no prefetch registers)
-        for (int hi = maxn; hi > 0; hi -= BATCH) {
-            const int lo = max(hi - BATCH, 0);
-            const int cnt = hi - lo;
+        // batches walk the list back to front from the tile's last contributor
+        // (the walk is VALU-bound: plain loads, no prefetch registers)
+        if (maxn > 0) {
+            feed.start(keys + rg.x, ids + rg.x, maxn, hitmask);
+            feed.request();
+        }
+        while (maxn > 0) {
+            __syncthreads(); // the previous batch's records are flushed
+            if (feed.queued() < BATCH && feed.more()) {
+                feed.fill(2 * BATCH, s_cnt, s_ring);
+                feed.request();
+            }
+            const int cnt = min(BATCH, feed.queued());
+            if (cnt == 0) break;
+            load_records_direct<K, NT>(lds, s_ring, feed.head, RING - 1, records, cnt);
+            const bool refill = feed.queued() <= RING - NT && feed.more();
+            if (refill) feed.publish(s_cnt);
             __syncthreads();
-            if ((int)threadIdx.x < cnt) s_ids[threadIdx.x] = ids[start + lo + threadIdx.x];
-            __syncthreads();
-            load_records_direct<K, NT>(lds, s_ids, records, cnt);
-            __syncthreads();
+            const uint32_t head = feed.head;
+            feed.head += (uint32_t)cnt;
+            if (refill) {
+                feed.append(feed.k0, feed.v0, true, opaque_tid(), s_cnt[0], s_ring);
+                feed.request();
+            }
             // the wave's records of this batch before its last contributor, back to front
-            const uint8_t *mine = reinterpret_cast<const uint8_t *>(&lds[min(lane, BATCH - 1) * CH]);
-            const bool meets = lane < min(cnt, wmaxn - lo) && square_meets<K>(mine, su, sv);
+            const int mine_e = min(lane, cnt - 1);
+            const uint8_t *mine = reinterpret_cast<const uint8_t *>(&lds[mine_e * CH]);
+            const int mypos = (int)s_ring[(head + (uint32_t)mine_e) & (RING - 1)].y; // lane e: list position of entry e
+            const bool meets = lane < cnt && mypos < wmaxn && square_meets<K>(mine, su, sv);
             const int myT = reinterpret_cast<const RecHeader *>(mine)->T; // lane e: hull size of entry e
             uint64_t M = __ballot(meets);
             while (M) {
-                const int e = 63 - __builtin_clzll(M);
-                M &= ~(1ull << e);
+                const int e = __builtin_ctzll(M);
+                M &= M - 1;
                 const uint8_t *rec = reinterpret_cast<const uint8_t *>(&lds[e * CH]);
                 const int Tr = __builtin_amdgcn_readlane(myT, e);
-                const bool live = lo + e < nend;
+                const bool live = __builtin_amdgcn_readlane(mypos, e) < nend;
                 bool full = false;
                 CS_DISPATCH_NL(K, Tr, bwd_record<K, NLL>(rec, live, u, y, pxf, pyf, ra.eps_alpha, P, &s_acc[e * NP], full));
                 nfull += full;
@@ -738,13 +875,13 @@ __global__ __launch_bounds__(TILE *TILE) void render_bwd_kernel(
             // one global atomic per (entry, value) for the whole workgroup; the
             // compact values of entry e go to the slots of its hull size
             __syncthreads();
-            for (int c = threadIdx.x; c < cnt * NP; c += NT) {
+            for (int c = opaque_tid(); c < cnt * NP; c += NT) {
                 const int e = c / NP, qv = c - e * NP;
                 float *src = &s_acc[c];
                 const float a = *src;
                 if (a != 0.0f) {
                     const int T = reinterpret_cast<const RecHeader *>(&lds[e * CH])->T;
-                    unsafeAtomicAdd(&acc[(size_t)s_ids[e] * AS + acc_slot<K>(qv, T)], a);
+                    unsafeAtomicAdd(&acc[(size_t)s_ring[(head + (uint32_t)e) & (RING - 1)].x * AS + acc_slot<K>(qv, T)], a);
                     *src = 0.0f;
                 }
             }
@@ -798,8 +935,8 @@ template <class F> int persistent_grid(F kernel, int threads)
 // max_items bounds the grid (a persistent grid larger than the work only idles).
 // Returns the grid size (the number of evalcount slots written).
 int launch_render_fwd(hipStream_t st, int K, int tile, const FrameHeader *frame, const uint32_t *order,
-                      uint32_t max_items, uint32_t *queues, const uint2 *ranges, const uint32_t *ids,
-                      const uint8_t *records, const RenderArgs &ra, uint2 *pixstate, unsigned long long *evalcount,
+                      uint32_t max_items, uint32_t *queues, const uint2 *ranges, const uint32_t *keys,
+                      const uint32_t *ids, const uint8_t *records, const RenderArgs &ra, uint2 *pixstate, unsigned long long *evalcount,
                       float *zero_acc, size_t zero_floats)
 {
     // the accumulator rows are whole 16-byte words (acc_stride is a multiple of 4)
@@ -810,7 +947,7 @@ int launch_render_fwd(hipStream_t st, int K, int tile, const FrameHeader *frame,
     CS_DISPATCH_K(K, CS_DISPATCH_TILE(tile, {
         auto kern = render_fwd_kernel<KK, TT, BF>;
         const int grid = std::min({persistent_grid(kern, TT * TT), (int)max_items, EVAL_SLOTS});
-        hipLaunchKernelGGL(kern, dim3(grid), dim3(TT * TT), 0, st, frame, order, queues, ranges, ids, records, ra,
+        hipLaunchKernelGGL(kern, dim3(grid), dim3(TT * TT), 0, st, frame, order, queues, ranges, keys, ids, records, ra,
                            pixstate, evalcount, z4, n4);
         used = grid;
     }));
@@ -819,8 +956,8 @@ int launch_render_fwd(hipStream_t st, int K, int tile, const FrameHeader *frame,
 
 // Returns the grid size (the number of evalcount slots written).
 int launch_render_bwd(hipStream_t st, int K, int tile, const FrameHeader *frame, const uint32_t *order,
-                      uint32_t max_items, uint32_t *queues, const uint2 *ranges, const uint32_t *ids,
-                      const uint8_t *records, const RenderArgs &ra, const uint2 *pixstate, float *acc,
+                      uint32_t max_items, uint32_t *queues, const uint2 *ranges, const uint32_t *keys,
+                      const uint32_t *ids, const uint8_t *records, const RenderArgs &ra, const uint2 *pixstate, float *acc,
                       unsigned long long *evalcount)
 {
     if (max_items == 0) return 0;
@@ -828,7 +965,7 @@ int launch_render_bwd(hipStream_t st, int K, int tile, const FrameHeader *frame,
     CS_DISPATCH_K(K, CS_DISPATCH_TILE(tile, {
         auto kern = render_bwd_kernel<KK, TT, BBW>;
         const int grid = std::min({persistent_grid(kern, TT * TT), (int)max_items, EVAL_SLOTS});
-        hipLaunchKernelGGL(kern, dim3(grid), dim3(TT * TT), 0, st, frame, order, queues, ranges, ids, records, ra,
+        hipLaunchKernelGGL(kern, dim3(grid), dim3(TT * TT), 0, st, frame, order, queues, ranges, keys, ids, records, ra,
                            pixstate, acc, evalcount);
         used = grid;
     }));

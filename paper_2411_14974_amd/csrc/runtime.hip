@@ -9,6 +9,7 @@
 #include <atomic>
 #include <cstring>
 #include <map>
+#include <new>
 #include <string>
 #include <tuple>
 #include <vector>
@@ -24,8 +25,8 @@ void launch_preprocess_fwd(hipStream_t, int, int, int, int, int, const void *, c
 void launch_preprocess_bwd(hipStream_t, int, int, int, int, int, const void *, const void *, const void *,
                            const void *, const FrameHeader *, const uint32_t *, const float *,
                            float *, float *, float *, float *, float *);
-void radix_sort(hipStream_t, uint32_t **, uint32_t **, uint32_t **, uint32_t **, uint32_t, const uint32_t *, uint32_t, int,
-                uint32_t *, int, uint32_t *, bool);
+bool radix_sort(hipStream_t, uint32_t **, uint32_t **, uint32_t **, uint32_t **, uint32_t, const uint32_t *, uint32_t, int,
+                uint32_t *, int, uint32_t *, bool, uint2 *, uint32_t);
 size_t radix_sort_words(uint32_t, bool, uint32_t, int, int);
 size_t sort_temp_words(uint32_t, int, int);
 size_t scan_status_words(uint32_t);
@@ -36,13 +37,13 @@ void launch_emit_pairs(hipStream_t, uint32_t, uint32_t, const uint32_t *, const 
                        const uint4 *, const FrameHeader *, uint32_t, uint32_t *, uint32_t *, uint32_t *, uint32_t);
 void launch_prepare_tail(hipStream_t, uint32_t *, uint32_t, uint32_t *, size_t);
 void launch_zero_ranges(hipStream_t, uint32_t *, size_t, uint32_t *, size_t, uint32_t *, size_t);
-void launch_tile_length_keys(hipStream_t, uint32_t, const uint2 *, uint32_t *, uint32_t *);
-void launch_tile_ranges(hipStream_t, const uint32_t *, uint32_t, const uint32_t *, uint32_t, uint2 *, uint32_t);
+void launch_tile_length_keys(hipStream_t, uint32_t, const FrameHeader *, const uint2 *, uint32_t *, uint32_t *);
+void launch_cell_ranges(hipStream_t, const uint32_t *, uint32_t, const uint32_t *, uint32_t, uint2 *, uint32_t, uint32_t);
 int launch_render_fwd(hipStream_t, int, int, const FrameHeader *, const uint32_t *, uint32_t, uint32_t *,
-                       const uint2 *, const uint32_t *, const uint8_t *, const RenderArgs &, uint2 *,
+                       const uint2 *, const uint32_t *, const uint32_t *, const uint8_t *, const RenderArgs &, uint2 *,
                        unsigned long long *, float *, size_t);
 int launch_render_bwd(hipStream_t, int, int, const FrameHeader *, const uint32_t *, uint32_t, uint32_t *,
-                      const uint2 *, const uint32_t *, const uint8_t *, const RenderArgs &, const uint2 *, float *,
+                      const uint2 *, const uint32_t *, const uint32_t *, const uint8_t *, const RenderArgs &, const uint2 *, float *,
                       unsigned long long *);
 hipError_t launch_l1_grad(hipStream_t, const float *, const float *, size_t, float *, float *);
 } // namespace cs
@@ -215,6 +216,22 @@ int Frame::init(int n_, int K_, int deg_, int V_, size_t tiles, size_t pix, hipS
     return CS_OK;
 }
 
+// Pairs to make room for, given the counts of (cell, convex) and (tile, convex)
+// pairs: the cell pairs with a margin.  A graph's frame (by_tile_pairs) is sized
+// by the tile pairs, of which a caller is promised the margin, and a frame past
+// it is reported: then any frame within the promise fits, whatever share of
+// its cells' tiles its convexes reach (surplus workgroups of the grids leave
+// at once).
+size_t Frame::pair_room(uint32_t cell_pairs, uint32_t tile_pairs, double margin)
+{
+    size_t room = (size_t)std::ceil(cell_pairs * margin);
+    if (by_tile_pairs) {
+        cap_tile_pairs = (size_t)std::ceil(tile_pairs * margin);
+        room = std::max(room, cap_tile_pairs);
+    }
+    return std::min<size_t>(room, MAX_CELL_PAIRS);
+}
+
 int Frame::ensure_pairs(size_t m)
 {
     if (m <= cap_pairs && pt) return CS_OK;
@@ -325,6 +342,10 @@ int Frame::bind(uint8_t *base, size_t bytes, int n_, int K_, int deg_, size_t ti
 int Frame::upload_views(const FrameHeader &hdr, const ViewDesc *views, int table)
 {
     const size_t bytes = sizeof(FrameHeader) + sizeof(ViewDesc) * hdr.nviews;
+    if (table == 0) {
+        cells = hdr.total_cells;
+        key_bits = hdr.key_bits;
+    }
     std::vector<char> &sent = table_sent[table];
     if (table_stream[table] == st && sent.size() == bytes && std::memcmp(sent.data(), &hdr, sizeof(hdr)) == 0 &&
         std::memcmp(sent.data() + sizeof(FrameHeader), views, bytes - sizeof(FrameHeader)) == 0)
@@ -480,6 +501,23 @@ int plan_views(int nviews, const cs_camera *cams, int tile, float *const *out, c
         poff += (int64_t)cams[v].width * cams[v].height;
     }
     if (toff >= (1ll << 30)) return fail(CS_EINVAL, "too many tiles in one call");
+    // every view's cells (see FrameHeader)
+    for (uint32_t most : {2u, 1u}) {
+        int64_t coff = 0;
+        for (ViewDesc &d : vp.views) {
+            auto cells = [&](uint32_t s) {
+                const int64_t side = 1 << s;
+                return ((d.tiles_x + side - 1) >> s) * ((d.tiles_y + side - 1) >> s);
+            };
+            d.cell_shift = 0;
+            while (d.cell_shift < most && cells(d.cell_shift) > (int64_t)VIEW_CELLS) ++d.cell_shift;
+            d.cell_off = (int32_t)coff;
+            coff += cells(d.cell_shift);
+        }
+        vp.hdr.total_cells = (uint32_t)coff;
+        vp.hdr.key_bits = most == 2 ? 16u : 28u;
+        if (coff <= (int64_t)MAX_CELLS_16) break;
+    }
     vp.hdr.nviews = (uint32_t)nviews;
     vp.hdr.total_tiles = (uint32_t)toff;
     vp.hdr.total_pix = poff;
@@ -499,31 +537,30 @@ static uint32_t next_count_tag()
     return t;
 }
 
-// Waits for the pair count tagged `tag` in the pinned word (polling: a
-// blocking wait wakes up late and the GPU idles).  The stream is queried now
-// and then, so that a stream that finished or failed without writing it ends
-// the wait with an error.
-static int wait_pair_count(const HostRing &ring, uint32_t tag, hipStream_t st, uint32_t *count)
+// Waits for the counts of (cell, convex) and (tile, convex) pairs tagged `tag`
+// in the pinned words (polling: a blocking wait wakes up late and the GPU
+// idles).  The stream is queried now and then, so that a stream that finished
+// or failed without writing them ends the wait with an error.
+static int wait_pair_count(const HostRing &ring, uint32_t tag, hipStream_t st, uint32_t *count, uint32_t *tiles)
 {
     const unsigned long long *w = reinterpret_cast<const unsigned long long *>(ring.h_word);
-    for (uint64_t spin = 1;; ++spin) {
-        const unsigned long long v = __atomic_load_n(w, __ATOMIC_ACQUIRE);
-        if ((uint32_t)(v >> 32) == tag) {
-            *count = (uint32_t)v;
-            return CS_OK;
-        }
-        if ((spin & 4095) == 0) {
-            const hipError_t q = hipStreamQuery(st);
-            if (q == hipErrorNotReady) continue;
-            const unsigned long long v2 = __atomic_load_n(w, __ATOMIC_ACQUIRE);
-            if (q == hipSuccess && (uint32_t)(v2 >> 32) == tag) {
-                *count = (uint32_t)v2;
-                return CS_OK;
-            }
-            return fail(CS_EHIP, "pair count read-back: %s", q == hipSuccess ? "the count was not written"
-                                                                          : hipGetErrorString(q));
-        }
+    auto arrived = [&] {
+        const unsigned long long v = __atomic_load_n(w, __ATOMIC_ACQUIRE), t = __atomic_load_n(w + 1, __ATOMIC_ACQUIRE);
+        if ((uint32_t)(v >> 32) != tag || (uint32_t)(t >> 32) != tag) return false;
+        *count = (uint32_t)v;
+        *tiles = (uint32_t)t;
+        return true;
+    };
+    for (uint64_t spin = 1; !arrived(); ++spin) {
+        if ((spin & 4095) != 0) continue;
+        const hipError_t q = hipStreamQuery(st);
+        if (q == hipErrorNotReady) continue;
+        if (q == hipSuccess && arrived()) break;
+        return fail(CS_EHIP, "pair count read-back: %s", q == hipSuccess ? "the count was not written"
+                                                                      : hipGetErrorString(q));
     }
+    if (*count >= MAX_CELL_PAIRS) return fail(CS_ENOMEM, "too many (cell, convex) pairs in one call");
+    return CS_OK;
 }
 
 // Forward pass on frame F.  device_count: the pair count stays on the device
@@ -538,6 +575,10 @@ int enqueue_forward(cs_ctx *ctx, Frame &F, const cs_scene *sc, const RenderArgs 
     F.tile = kn.tile;
     F.longest = kn.longest;
     F.digits = kn.digits;
+    // cells that the buffers and the cell sort provide for: this call's, or (graph
+    // capture, replayed with other resolutions) any that its tiles can form
+    const size_t ncells = device_count ? F.cap_cells() : F.cells;
+    const int sort_bits = std::max(1, ilog2_ceil(ncells));
     // The clearing of the frame's counters, the sort temporaries and the tile
     // ranges rides on the kernels before their users (preprocess, pair scan,
     // emission) instead of launches of their own, when those kernels run.
@@ -584,41 +625,43 @@ int enqueue_forward(cs_ctx *ctx, Frame &F, const cs_scene *sc, const RenderArgs 
         scan_prepared = false;
         uint32_t *pt = F.pt, *pi = F.pi, *pt_alt = F.pt_alt, *pi_alt = F.pi_alt;
         if (ninst > 0) {
-            const int tile_bits = std::max(1, ilog2_ceil(F.cap_tiles));
-            // the emission clears the tile sort's temporaries
-            const size_t tw = radix_sort_words(M_host, m_dev != nullptr, (uint32_t)F.cap_pairs, tile_bits, kn.digits);
+            // the emission clears the cell sort's temporaries
+            const size_t tw = radix_sort_words(M_host, m_dev != nullptr, (uint32_t)F.cap_pairs, sort_bits, kn.digits);
             tm.begin();
             launch_emit_pairs(st, ninst, (uint32_t)n, ids, F.offsets, F.counts_sorted, F.bins_sorted, F.d_frame,
                               (uint32_t)F.cap_pairs, pt, pi, F.hist, (uint32_t)tw);
             tm.end(CS_STAGE_EMIT);
             tm.begin();
-            radix_sort(st, &pt, &pi, &pt_alt, &pi_alt, M_host, m_dev, (uint32_t)F.cap_pairs, tile_bits, F.hist,
-                       kn.digits, F.counters + CNT_SORT_ERR, true);
+            const bool ranged = radix_sort(st, &pt, &pi, &pt_alt, &pi_alt, M_host, m_dev, (uint32_t)F.cap_pairs,
+                                           sort_bits, F.hist, kn.digits, F.counters + CNT_SORT_ERR, true, F.ranges,
+                                           (uint32_t)ncells);
             tm.end(CS_STAGE_TILE_SORT);
             tm.begin();
-            launch_tile_ranges(st, pt, M_host, m_dev, m_dev ? (uint32_t)F.cap_pairs : M_host, F.ranges,
-                               (uint32_t)F.cap_tiles);
+            if (!ranged)
+                launch_cell_ranges(st, pt, M_host, m_dev, m_dev ? (uint32_t)F.cap_pairs : M_host, F.ranges,
+                                   (uint32_t)ncells, (1u << F.key_bits) - 1u);
             tm.end(CS_STAGE_RANGES);
         }
+        F.sorted_keys = pt;
         F.sorted_ids = pi;
         F.order = nullptr;
         if (kn.longest) {
             uint32_t *ok = F.ord_k, *ov = F.ord_v, *ok2 = F.ord_k_alt, *ov2 = F.ord_v_alt;
             tm.begin();
-            launch_tile_length_keys(st, (uint32_t)F.cap_tiles, F.ranges, ok, ov);
+            launch_tile_length_keys(st, (uint32_t)F.cap_tiles, F.d_frame, F.ranges, ok, ov);
             radix_sort(st, &ok, &ov, &ok2, &ov2, (uint32_t)F.cap_tiles, nullptr, (uint32_t)F.cap_tiles, 16, F.hist,
-                       8, F.counters + CNT_SORT_ERR, false);
+                       8, F.counters + CNT_SORT_ERR, false, nullptr, 0);
             tm.end(CS_STAGE_ORDER);
             F.order = ov;
         }
         tm.begin();
         F.eval_slots = launch_render_fwd(st, F.K, kn.tile, F.d_frame, F.order, (uint32_t)F.cap_tiles, F.counters + CNT_QUEUE, F.ranges,
-                          F.sorted_ids, F.records, ra, F.pixstate, F.evalcount, zero_acc ? F.acc : nullptr,
+                          F.sorted_keys, F.sorted_ids, F.records, ra, F.pixstate, F.evalcount, zero_acc ? F.acc : nullptr,
                           zero_acc ? F.ninst * acc_stride(F.K) : 0);
         tm.end(CS_STAGE_RENDER_FWD);
     };
 
-    uint32_t M = 0;
+    uint32_t M = 0, tile_pairs = 0;
     const uint32_t tag = next_count_tag();
     if (ninst > 0) {
         if (!F.pt) { // first sizing: the sort temporaries come with the pair buffers
@@ -627,7 +670,7 @@ int enqueue_forward(cs_ctx *ctx, Frame &F, const cs_scene *sc, const RenderArgs 
         }
         tm.begin();
         radix_sort(st, &keys, &ids, &keys_alt, &ids_alt, ninst, nullptr, ninst, 32, F.hist, 8, F.counters + CNT_SORT_ERR,
-                   fused);
+                   fused, nullptr, 0);
         tm.end(CS_STAGE_DEPTH_SORT);
         tm.begin();
         // the count also goes straight to pinned host memory (no copy in the
@@ -641,9 +684,9 @@ int enqueue_forward(cs_ctx *ctx, Frame &F, const cs_scene *sc, const RenderArgs 
         tm.end(CS_STAGE_BIN_SCAN);
         if (!device_count) {
             if (!speculative) { // a new frame waits for its count here
-                int r = wait_pair_count(*F.ring, tag, st, &M);
+                int r = wait_pair_count(*F.ring, tag, st, &M, &tile_pairs);
                 if (r) return r;
-                r = F.ensure_pairs((size_t)std::ceil(M * margin));
+                r = F.ensure_pairs(F.pair_room(M, tile_pairs, margin));
                 if (r) return r;
                 F.npairs = M;
             }
@@ -655,11 +698,12 @@ int enqueue_forward(cs_ctx *ctx, Frame &F, const cs_scene *sc, const RenderArgs 
     }
     tail(M, (device_count || speculative) ? F.counters + CNT_PAIRS_EFF : nullptr);
     if (speculative) {
-        int r = wait_pair_count(*F.ring, tag, st, &M);
+        int r = wait_pair_count(*F.ring, tag, st, &M, &tile_pairs);
         if (r) return r;
         F.npairs = M;
+        if (F.fixed && tile_pairs > F.cap_pairs) return F.ensure_pairs(tile_pairs); // beyond the documented limit
         if (M > F.cap_pairs) { // did not fit: grow, reset the tile queues and counts, run the tail again
-            int r = F.ensure_pairs((size_t)std::ceil(M * margin));
+            int r = F.ensure_pairs(F.pair_room(M, tile_pairs, margin));
             if (r) return r;
             launch_zero_ranges(st, F.counters + CNT_QUEUE, QUEUE_WORDS, nullptr, 0,
                                nullptr, 0);
@@ -688,7 +732,7 @@ int enqueue_backward(Frame &F, const cs_scene *sc, const cs_grads *g, const Rend
     F.acc_zeroed = false; // a second backward of the same forward clears them again
     tm.begin();
     F.eval_slots_bwd = launch_render_bwd(st, F.K, F.tile, F.d_frame_b, F.order, (uint32_t)F.cap_tiles, F.counters + CNT_QUEUE_B,
-                                         F.ranges, F.sorted_ids, F.records, ra, F.pixstate, F.acc,
+                                         F.ranges, F.sorted_keys, F.sorted_ids, F.records, ra, F.pixstate, F.acc,
                                          F.evalcount + (size_t)EVAL_SLOTS * EVAL_FIELDS);
     tm.end(CS_STAGE_RENDER_BWD);
     tm.begin();
@@ -1033,7 +1077,7 @@ int cs_render_forward_batch(cs_ctx *ctx, const cs_scene *sc, int32_t n_views, co
     const uint64_t key = scene_key(sc, n_views, kn, ra);
     Frame *F = ctx->batch;
     const bool fits = F && ctx->batch_key == key && F->st == st && vp.hdr.total_tiles <= F->cap_tiles &&
-                      (size_t)vp.hdr.total_pix <= F->cap_pix;
+                      (size_t)vp.hdr.total_pix <= F->cap_pix && vp.hdr.key_bits == F->key_bits;
     if (!fits) {
         if (F) {
             (void)hipStreamSynchronize(F->st);
@@ -1044,6 +1088,7 @@ int cs_render_forward_batch(cs_ctx *ctx, const cs_scene *sc, int32_t n_views, co
         int r = F->init(sc->n, sc->k, sc->sh_degree, n_views, vp.hdr.total_tiles, (size_t)vp.hdr.total_pix, st, &ctx->ring);
         if (!r) r = F->upload_views(vp.hdr, vp.views.data());
         if (!r) r = F->init_async_readback();
+        F->by_tile_pairs = true;
         // first frame: eager, pair buffers sized from its count plus 30 %
         if (!r) r = enqueue_forward(ctx, *F, sc, ra, kn, false, 1.3, tm);
         if (r) { delete F; return r; }
@@ -1095,13 +1140,13 @@ int cs_batch_check(cs_ctx *ctx, const cs_fwd_state *s)
     }
     CS_HIP(hipEventSynchronize(F->counters_ev));
     if (F->h_counters[CNT_SORT_ERR]) return fail(CS_EHIP, "radix sort: a look-back wait exceeded its bound");
-    if (F->h_counters[CNT_OVERFLOW]) {
-        const size_t m = F->h_counters[CNT_PAIRS];
+    const uint32_t m = F->h_counters[CNT_TILE_PAIRS];
+    if (F->h_counters[CNT_OVERFLOW] || m > F->cap_tile_pairs) {
         CS_HIP(hipStreamSynchronize(F->st));
         F->drop_graphs();
-        int r = F->ensure_pairs((size_t)std::ceil(m * 1.3));
+        int r = F->ensure_pairs(F->pair_room(F->h_counters[CNT_PAIRS], m, 1.3));
         if (r) return r;
-        return fail(CS_EOVERFLOW, "frame needed %zu (convex, tile) pairs; buffers grown, render it again", m);
+        return fail(CS_EOVERFLOW, "frame needed %u (convex, tile) pairs; buffers grown, render it again", m);
     }
     return CS_OK;
 }
@@ -1265,7 +1310,7 @@ int read_work_counters(Frame *F, cs_work_counters *w)
     CS_HIP(hipStreamSynchronize(F->st));
     if (cnt[CNT_SORT_ERR]) return fail(CS_EHIP, "radix sort: a look-back wait exceeded its bound");
     std::memset(w, 0, sizeof(*w));
-    w->pairs = cnt[CNT_PAIRS];
+    w->pairs = cnt[CNT_TILE_PAIRS];
     for (int g = 0; g < F->eval_slots; ++g) {
         const unsigned long long *e = &ev[(size_t)EVAL_FIELDS * g];
         w->tested += (int64_t)e[EV_TESTED];
@@ -1351,27 +1396,60 @@ int cs_debug_preprocess(cs_ctx *ctx, const cs_scene *sc, const cs_camera *cam, c
     return CS_OK;
 }
 
+namespace {
+// The depth-ordered list of every tile, to host memory: its cell's list,
+// filtered by the tile's mask bit.
+int copy_tile_lists(Frame *F, int32_t *ranges, int64_t ranges_len, int32_t *ids, int64_t ids_len)
+{
+    uint32_t cnt[CNT_WORDS];
+    CS_HIP(hipMemcpyAsync(cnt, F->counters, sizeof(cnt), hipMemcpyDeviceToHost, F->st));
+    CS_HIP(hipStreamSynchronize(F->st));
+    const size_t npairs = cnt[CNT_PAIRS_EFF];
+    FrameHeader hdr;
+    CS_HIP(hipMemcpy(&hdr, F->d_frame, sizeof(hdr), hipMemcpyDeviceToHost));
+    std::vector<ViewDesc> views(hdr.nviews);
+    std::vector<uint2> cells(hdr.total_cells);
+    std::vector<uint32_t> keys(npairs), cids(npairs);
+    CS_HIP(hipMemcpyAsync(views.data(), F->d_frame + 1, sizeof(ViewDesc) * views.size(), hipMemcpyDeviceToHost, F->st));
+    CS_HIP(hipMemcpyAsync(cells.data(), F->ranges, sizeof(uint2) * cells.size(), hipMemcpyDeviceToHost, F->st));
+    if (npairs) {
+        CS_HIP(hipMemcpyAsync(keys.data(), F->sorted_keys, 4 * npairs, hipMemcpyDeviceToHost, F->st));
+        CS_HIP(hipMemcpyAsync(cids.data(), F->sorted_ids, 4 * npairs, hipMemcpyDeviceToHost, F->st));
+    }
+    CS_HIP(hipStreamSynchronize(F->st));
+    std::vector<int32_t> lists, rg;
+    rg.reserve(2 * (size_t)hdr.total_tiles);
+    for (const ViewDesc &vd : views)
+        for (uint32_t ty = 0; ty < (uint32_t)vd.tiles_y; ++ty)
+            for (uint32_t tx = 0; tx < (uint32_t)vd.tiles_x; ++tx) {
+                const uint2 c = cells[tile_cell(vd, tx, ty)];
+                const uint32_t bit = tile_bit(vd, hdr.key_bits, tx, ty);
+                const size_t first = lists.size();
+                for (uint32_t p = c.x; p < c.y; ++p)
+                    if (keys[p] & bit) lists.push_back((int32_t)cids[p]);
+                const bool empty = lists.size() == first;
+                rg.push_back(empty ? 0 : (int32_t)first);
+                rg.push_back(empty ? 0 : (int32_t)lists.size());
+            }
+    if (ranges_len < (int64_t)rg.size() || ids_len < (int64_t)lists.size() || (!ids && !lists.empty()))
+        return fail(CS_EOVERFLOW, "host buffers too small (%lld ranges, %lld ids needed)", (long long)rg.size(),
+                    (long long)lists.size());
+    std::memcpy(ranges, rg.data(), 4 * rg.size());
+    if (!lists.empty()) std::memcpy(ids, lists.data(), 4 * lists.size());
+    return CS_OK;
+}
+} // namespace
+
 int cs_debug_tile_lists(cs_ctx *ctx, const cs_fwd_state *s, int32_t *ranges, int64_t ranges_len, int32_t *ids,
                         int64_t ids_len)
 {
     if (!ctx || !s || !s->frame || !ranges) return fail(CS_EINVAL, "NULL argument");
-    Frame *F = s->frame;
     CS_HIP(hipSetDevice(ctx->device));
-    uint32_t cnt[CNT_WORDS];
-    CS_HIP(hipMemcpyAsync(cnt, F->counters, sizeof(cnt), hipMemcpyDeviceToHost, F->st));
-    CS_HIP(hipStreamSynchronize(F->st));
-    const int64_t npairs = cnt[CNT_PAIRS_EFF];
-    FrameHeader hdr;
-    CS_HIP(hipMemcpy(&hdr, F->d_frame, sizeof(hdr), hipMemcpyDeviceToHost));
-    const int64_t nt = hdr.total_tiles;
-    if (ranges_len < 2 * nt || ids_len < npairs || (!ids && npairs))
-        return fail(CS_EOVERFLOW, "host buffers too small (%lld ranges, %lld ids needed)", (long long)(2 * nt),
-                    (long long)npairs);
-    CS_HIP(hipMemcpyAsync(ranges, F->ranges, sizeof(uint2) * nt, hipMemcpyDeviceToHost, F->st));
-    if (npairs)
-        CS_HIP(hipMemcpyAsync(ids, F->sorted_ids, sizeof(uint32_t) * npairs, hipMemcpyDeviceToHost, F->st));
-    CS_HIP(hipStreamSynchronize(F->st));
-    return CS_OK;
+    try {
+        return copy_tile_lists(s->frame, ranges, ranges_len, ids, ids_len);
+    } catch (const std::bad_alloc &) {
+        return fail(CS_ENOMEM, "tile lists: out of host memory");
+    }
 }
 
 int cs_l1_loss_grad(cs_ctx *ctx, const float *rgb, const float *target, int32_t width, int32_t height,

@@ -36,7 +36,14 @@ struct Frame {
     int tile = 16, longest = 0, digits = 8;
     size_t cap_inst = 0, cap_pairs = 0, cap_tiles = 0, cap_pix = 0;
     size_t ninst = 0; // instances of the current use (n V <= cap_inst)
+    // cells of the current view table, and the most that cap_tiles tiles can
+    // form in views of any shape (every cell holds a tile)
+    size_t cells = 0;
+    uint32_t key_bits = 16;
+    size_t cap_cells() const { return key_bits == 16 && cap_tiles > MAX_CELLS_16 ? (size_t)MAX_CELLS_16 : cap_tiles; }
     uint32_t npairs = 0;
+    bool by_tile_pairs = false; // pair buffers sized by the (tile, convex) pairs (pair_room)
+    size_t cap_tile_pairs = 0;  // then: the tile pairs of a frame that is not reported as overflowing
     hipStream_t st = nullptr;
     std::vector<void *> allocs;
     size_t bytes_held = 0;
@@ -68,7 +75,7 @@ struct Frame {
     hipEvent_t counters_ev = nullptr;
 
     // results of the last forward pass (point into the buffers above)
-    uint32_t *sorted_ids = nullptr;
+    uint32_t *sorted_keys = nullptr, *sorted_ids = nullptr; // (cell, convex) pairs by cell, then depth
     uint32_t *order = nullptr;
 
     // captured graphs (batched path): the forward (gfwd_zero: it clears the
@@ -91,6 +98,7 @@ struct Frame {
     int init_async_readback();
     int alloc(void **p, size_t bytes);
     void release_buffer(void *p);
+    size_t pair_room(uint32_t cell_pairs, uint32_t tile_pairs, double margin);
     int ensure_pairs(size_t m);
     int ensure_acc();
     int upload_views(const FrameHeader &hdr, const ViewDesc *views, int table = 0);

@@ -1,14 +1,15 @@
 // Tile binning and ordering (gfx950): the pair-offset scan, a stable LSD
-// radix sort of (u32 key, u32 value) pairs, (convex, tile) pair emission and
-// per-tile list ranges.
+// radix sort of (u32 key, u32 value) pairs, (cell, convex) pair emission and
+// per-cell list ranges.
 //
 // The front-to-back order within a tile (paper Sec. 3.2: convexes sorted by
-// increasing distance) comes from a two-stage LSD sort of the (tile | depth)
+// increasing distance) comes from a two-stage LSD sort of the (cell | depth)
 // key: the depth digits are sorted once over the N convexes, the convexes are
-// expanded into (tile, convex) pairs in that order, and a stable sort of the
-// pairs on the tile digits alone completes the lexicographic order.  This moves
-// the depth passes from the M pairs (about 13 per convex at 1080p) to the N
-// convexes.
+// expanded into (cell, convex) pairs in that order, and a stable sort of the
+// pairs on the cell digits alone completes the lexicographic order.  This moves
+// the depth passes from the pairs to the N convexes, and a pair carries the
+// mask of the cell's tiles (see FrameHeader), so that the pairs are a quarter
+// of the (tile, convex) pairs.
 #include <algorithm>
 #include <utility>
 
@@ -60,13 +61,19 @@ __device__ uint32_t block_scan_lds(uint32_t *s, uint32_t *s_wave)
     return total;
 }
 
-// Pair counts in depth order and their exclusive scan (the pair offsets), in
+// (cell, convex) pair counts in depth order and their exclusive scan (the pair offsets), in
 // one pass: each workgroup claims the next tile of SCAN_TILE ranks, gathers
 // the binning records bins[sorted_ids[r]] (copied out in depth order for the
 // pair emission) and their pair counts, scans the counts in LDS, publishes the tile's sum and
 // finds its prefix by a decoupled look-back in which one wave reads 64
 // predecessors' 64-bit status words at a time.  The last tile stores the total.
+// A status word: state in bits 62-63, cell pairs in bits 32-61 (saturating), tile
+// pairs (modulo 2^32) below.
 constexpr uint64_t SS_AGG = 1ull << 62, SS_INC = 2ull << 62, SS_VAL = SS_AGG - 1ull;
+__device__ __forceinline__ uint64_t ss_pack(uint64_t cells, uint32_t tiles)
+{
+    return (min(cells, (uint64_t)MAX_CELL_PAIRS) << 32) | tiles;
+}
 constexpr uint32_t SS_SPIN_LIMIT = 1u << 22;
 
 __device__ __forceinline__ uint64_t ss_load(const uint64_t *p)
@@ -78,16 +85,16 @@ __device__ __forceinline__ void ss_store(uint64_t *p, uint64_t v)
     __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// host_word (nullable): a word of coherent pinned host memory that also
-// receives the pair count, as tag << 32 | count: the host waits for its tag
-// there, with no copy or event in the stream.
+// host_word (nullable): two words of coherent pinned host memory that also
+// receive the counts of cell and tile pairs, each as tag << 32 | count: the
+// host waits for its tag there, with no copy or event in the stream.
 __global__ __launch_bounds__(SCAN_BLOCK) void gather_scan_kernel(
     uint32_t n, const uint32_t *__restrict__ sorted_ids, const uint4 *__restrict__ bins,
     uint4 *__restrict__ bins_sorted, uint32_t *__restrict__ counts_sorted, uint32_t *__restrict__ offsets,
     uint32_t *__restrict__ counters, uint64_t *__restrict__ status, unsigned long long *__restrict__ host_word,
     uint32_t tag, uint32_t capacity, ZeroSpans zero)
 {
-    zero_share(zero); // the tile ranges, when this scan also prepares the pair pass
+    zero_share(zero); // the cell ranges, when this scan also prepares the pair pass
     __shared__ uint32_t s[SCAN_TILE + SCAN_TILE / 32];
     __shared__ uint32_t s_wave[SCAN_BLOCK / 64];
     __shared__ uint32_t s_tile;
@@ -98,13 +105,15 @@ __global__ __launch_bounds__(SCAN_BLOCK) void gather_scan_kernel(
     const uint32_t t = s_tile;
     const size_t base = (size_t)t * SCAN_TILE;
     if (base >= n) return;
+    uint32_t tile_pairs = 0;
 #pragma unroll
     for (int k = 0; k < SCAN_ITEMS; ++k) {
         const size_t i = base + (size_t)k * SCAN_BLOCK + tid;
         uint32_t c = 0;
         if (i < n) {
             const uint4 b = bins[sorted_ids[i]]; // the one random read per instance
-            c = bin_count(b);
+            c = bin_cells(b);
+            tile_pairs += bin_count(b);
             bins_sorted[i] = b;
             counts_sorted[i] = c;
         }
@@ -112,9 +121,16 @@ __global__ __launch_bounds__(SCAN_BLOCK) void gather_scan_kernel(
     }
     __syncthreads();
     const uint32_t tile_total = block_scan_lds(s, s_wave);
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) tile_pairs += __shfl_xor(tile_pairs, o, 64);
+    if (lane == 0) s_wave[tid >> 6] = tile_pairs; // (the scan above ended with a barrier)
+    __syncthreads();
     if (tid < 64) {
-        if (tid == 0) ss_store(&status[t], (t == 0 ? SS_INC : SS_AGG) | (uint64_t)tile_total);
+        uint32_t block_tiles = 0;
+        for (int w = 0; w < SCAN_BLOCK / 64; ++w) block_tiles += s_wave[w];
+        if (tid == 0) ss_store(&status[t], (t == 0 ? SS_INC : SS_AGG) | ss_pack(tile_total, block_tiles));
         uint64_t excl = 0;
+        uint32_t excl_tiles = 0;
         if (t > 0) {
             int64_t j = (int64_t)t - 1; // the window's newest tile
             uint32_t spins = 0;
@@ -133,27 +149,35 @@ __global__ __launch_bounds__(SCAN_BLOCK) void gather_scan_kernel(
                     __builtin_amdgcn_s_sleep(1);
                     continue;
                 }
-                uint64_t v = (lane <= fi) ? (sv & SS_VAL) : 0ull;
+                uint64_t v = (lane <= fi) ? (sv & SS_VAL) >> 32 : 0ull;
+                uint32_t vt = (lane <= fi) ? (uint32_t)sv : 0u;
 #pragma unroll
-                for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
+                for (int o = 32; o > 0; o >>= 1) {
+                    v += __shfl_xor(v, o, 64);
+                    vt += __shfl_xor(vt, o, 64);
+                }
                 excl += v;
+                excl_tiles += vt;
                 if (fi < 64) break;
                 j -= 64;
             }
-            if (tid == 0) ss_store(&status[t], SS_INC | (excl + tile_total));
+            if (tid == 0) ss_store(&status[t], SS_INC | ss_pack(excl + tile_total, excl_tiles + block_tiles));
         }
         if (tid == 0) {
             s_excl = excl;
             if (base + SCAN_TILE >= n) {
-                const uint32_t m = (uint32_t)(excl + tile_total);
+                const uint32_t m = (uint32_t)min(excl + tile_total, (uint64_t)MAX_CELL_PAIRS);
                 counters[CNT_PAIRS] = m;
+                counters[CNT_TILE_PAIRS] = excl_tiles + block_tiles;
                 if (capacity) { // the pair pass's count, clamped to the buffers, and the overflow flag
                     counters[CNT_PAIRS_EFF] = m < capacity ? m : capacity;
                     counters[CNT_OVERFLOW] = m > capacity ? 1u : 0u;
                 }
-                if (host_word)
-                    __hip_atomic_store(host_word, ((unsigned long long)tag << 32) | (uint32_t)(excl + tile_total),
-                                       __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+                if (host_word) {
+                    const unsigned long long tg = (unsigned long long)tag << 32;
+                    __hip_atomic_store(host_word + 1, tg | (excl_tiles + block_tiles), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+                    __hip_atomic_store(host_word, tg | m, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+                }
             }
         }
     }
@@ -170,7 +194,8 @@ __global__ __launch_bounds__(SCAN_BLOCK) void gather_scan_kernel(
 size_t scan_status_words(uint32_t n) { return 2 * (((size_t)n + SCAN_TILE - 1) / SCAN_TILE + 1); }
 
 // bins_sorted[r] = bins[sorted_ids[r]], counts_sorted[r] its pair count,
-// offsets = their exclusive scan, counters[CNT_PAIRS] = the total.  counters
+// offsets = their exclusive scan, counters[CNT_PAIRS] = the total,
+// counters[CNT_TILE_PAIRS] = the (tile, convex) pairs.  counters
 // must hold CNT_WORDS words, zeroed, followed by scan_status_words(n) zeroed words.
 void launch_gather_scan(hipStream_t st, uint32_t n, const uint32_t *sorted_ids, const uint4 *bins,
                         uint4 *bins_sorted, uint32_t *counts_sorted, uint32_t *offsets, uint32_t *counters,
@@ -206,7 +231,7 @@ constexpr int OS_BLOCK = 512;
 constexpr int OS_WAVES = OS_BLOCK / 64;
 constexpr int OS_ITEMS_MIN = 8;                       // keys per thread of the smaller tiles
 constexpr int OS_TILE_MIN = OS_BLOCK * OS_ITEMS_MIN;  // 4096 keys
-constexpr int OS_RADIX = 256; // digits of up to 8 bits
+constexpr int OS_RADIX = 256; // digits of up to 8 bits (one pass of 9 bits: os_radix)
 constexpr int OS_MAX_PASSES = 8;
 constexpr uint32_t OS_AGG = 1u << 30, OS_INC = 2u << 30, OS_VAL = OS_AGG - 1u;
 constexpr uint32_t OS_SPIN_LIMIT = 1u << 22;
@@ -225,6 +250,10 @@ __host__ __device__ constexpr int os_shift(int end_bit, int passes, int p)
 {
     return p * (end_bit / passes) + (p < end_bit % passes ? p : end_bit % passes);
 }
+
+// Status words per tile of a pass.  Only a sort of one pass has digits of 9 bits
+// (its histogram takes the room of two).
+__host__ __device__ constexpr int os_radix(int width) { return width > 8 ? 1 << width : OS_RADIX; }
 
 __device__ __forceinline__ uint32_t os_load(const uint32_t *p)
 {
@@ -325,8 +354,9 @@ __global__ __launch_bounds__(OS_BLOCK) void os_scatter_kernel(
     const uint32_t *__restrict__ keys_in, const uint32_t *__restrict__ vals_in, uint32_t *__restrict__ keys_out,
     uint32_t *__restrict__ vals_out, const uint32_t *__restrict__ n_dev, uint32_t n_host, int shift,
     const uint32_t *__restrict__ hist, uint32_t *__restrict__ tile_counter, uint32_t *__restrict__ status,
-    uint32_t *__restrict__ err)
+    uint32_t *__restrict__ err, uint2 *__restrict__ ranges, uint32_t nranges)
 {
+    static_assert((1 << BITS) <= OS_BLOCK, "one digit per thread");
     constexpr int TILE = OS_BLOCK * ITEMS;
     constexpr int R = 1 << BITS;
     __shared__ uint32_t s_keys[TILE];
@@ -340,12 +370,15 @@ __global__ __launch_bounds__(OS_BLOCK) void os_scatter_kernel(
     const uint32_t n = n_dev ? *n_dev : n_host;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const uint64_t lt_mask = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
+    // a grid sized for a capacity: as many workgroups as there are tiles claim
+    // one each, the others leave without a claim (the claims are same-address
+    // atomics, about 18 ns each)
+    if ((size_t)blockIdx.x * TILE >= n) return;
     if (tid == 0) s_tile = atomicAdd(tile_counter, 1u);
     for (int d = tid; d < OS_WAVES * R; d += OS_BLOCK) (&s_wcnt[0][0])[d] = 0;
     __syncthreads();
     const uint32_t t = s_tile;
     const size_t tbase = (size_t)t * TILE;
-    if (tbase >= n) return; // past the data (capacity-sized grids): nobody waits on this tile
 
     // rank: element order within the tile is (wave, item, lane)
     uint32_t k[ITEMS], v[ITEMS], off[ITEMS];
@@ -384,6 +417,8 @@ __global__ __launch_bounds__(OS_BLOCK) void os_scatter_kernel(
     }
     const uint32_t dstart = os_block_excl(tid < R ? total : 0u, s_wsum);
     const uint32_t dbase = os_block_excl(tid < R ? hist[tid] : 0u, s_wsum);
+    // a sort of one pass: the digits are the keys, their runs the histogram's scan
+    if (ranges && t == 0 && tid < R && tid < (int)nranges) ranges[tid] = make_uint2(dbase, dbase + hist[tid]);
     if (tid < R) {
         s_dstart[tid] = dstart;
         uint32_t excl = 0;
@@ -461,10 +496,11 @@ static void os_launch_hist(hipStream_t st, const uint32_t *keys, uint32_t n_host
 template <int B, int I>
 static void os_launch_scatter(hipStream_t st, const uint32_t *keys, const uint32_t *vals, uint32_t *keys_out,
                               uint32_t *vals_out, uint32_t n_host, const uint32_t *n_dev, int tiles, int shift,
-                              const uint32_t *hist, uint32_t *ctr, uint32_t *status, uint32_t *err)
+                              const uint32_t *hist, uint32_t *ctr, uint32_t *status, uint32_t *err, uint2 *ranges,
+                              uint32_t nranges)
 {
     hipLaunchKernelGGL((os_scatter_kernel<B, I>), dim3(tiles), dim3(OS_BLOCK), 0, st, keys, vals, keys_out, vals_out, n_dev,
-                       n_host, shift, hist, ctr, status, err);
+                       n_host, shift, hist, ctr, status, err, ranges, nranges);
 }
 
 #define OS_DISPATCH(BITS, CALL)                                                                                    \
@@ -476,6 +512,7 @@ static void os_launch_scatter(hipStream_t st, const uint32_t *keys, const uint32
     case 5: { constexpr int BB = 5; CALL; } break;                                                                 \
     case 6: { constexpr int BB = 6; CALL; } break;                                                                 \
     case 7: { constexpr int BB = 7; CALL; } break;                                                                 \
+    case 9: { constexpr int BB = 9; CALL; } break;                                                                 \
     default: { constexpr int BB = 8; CALL; } break;                                                                \
     }
 
@@ -487,26 +524,37 @@ static void os_launch_scatter(hipStream_t st, const uint32_t *keys, const uint32
 // temp: sort_temp_words(n_capacity, end_bit, digit_bits) words.  *err (device)
 // gets bit 0 set if a look-back wait ran out of its bound.  The key arrays must
 // be 16-byte aligned (the histogram pass reads them in 16-byte loads).
+// Nine bits go in one pass of 512 digits where the caller allows 8-bit digits
+// (the widest that it can ask for): the 510 cells of 1920x1080 then take one
+// pass over their pairs instead of two.
+static int sort_digits(int end_bit, int digit_bits)
+{
+    digit_bits = std::min(8, std::max(4, digit_bits));
+    return digit_bits == 8 && end_bit == 9 ? 9 : digit_bits;
+}
+
 // Words of temp that radix_sort uses (and clears first, unless told that they
 // are clear) for these arguments.
 size_t radix_sort_words(uint32_t n_host, bool n_on_device, uint32_t n_capacity, int end_bit, int digit_bits)
 {
-    digit_bits = std::min(8, std::max(4, digit_bits));
+    digit_bits = sort_digits(end_bit, digit_bits);
     const uint32_t n_grid = n_on_device ? n_capacity : n_host;
     if (n_grid == 0 || end_bit <= 0) return 0;
     const int P = os_passes(end_bit, digit_bits);
     const int tile = n_grid <= (1u << 22) ? OS_TILE_MIN : 2 * OS_TILE_MIN;
     const size_t tiles = ((size_t)n_grid + tile - 1) / tile;
-    return OS_STATUS + (size_t)P * tiles * OS_RADIX;
+    return OS_STATUS + (size_t)P * tiles * os_radix(os_width(end_bit, P, 0));
 }
 
-void radix_sort(hipStream_t st, uint32_t **keys, uint32_t **vals, uint32_t **keys_alt, uint32_t **vals_alt,
+// ranges (nullable, nranges entries): a sort of one pass also stores the
+// [start, end) of every key below nranges there, and returns true.
+bool radix_sort(hipStream_t st, uint32_t **keys, uint32_t **vals, uint32_t **keys_alt, uint32_t **vals_alt,
                 uint32_t n_host, const uint32_t *n_dev, uint32_t n_capacity, int end_bit, uint32_t *temp,
-                int digit_bits, uint32_t *err, bool temp_clear)
+                int digit_bits, uint32_t *err, bool temp_clear, uint2 *ranges, uint32_t nranges)
 {
-    digit_bits = std::min(8, std::max(4, digit_bits));
+    digit_bits = sort_digits(end_bit, digit_bits);
     const uint32_t n_grid = n_dev ? n_capacity : n_host;
-    if (n_grid == 0 || end_bit <= 0) return;
+    if (n_grid == 0 || end_bit <= 0) return false;
     const int P = os_passes(end_bit, digit_bits);
     // up to 4M elements: tiles of OS_TILE_MIN (more workgroups in flight);
     // beyond: twice as large (half the look-back chain)
@@ -528,67 +576,82 @@ void radix_sort(hipStream_t st, uint32_t **keys, uint32_t **vals, uint32_t **key
     for (int p = 0; p < P; ++p) {
         const int shift = os_shift(end_bit, P, p);
         const int b = os_width(end_bit, P, p);
-        uint32_t *status = temp + OS_STATUS + (size_t)p * tiles * OS_RADIX;
+        uint32_t *status = temp + OS_STATUS + (size_t)p * tiles * os_radix(widest);
+        uint2 *rg = P == 1 ? ranges : nullptr;
         if (small) {
             OS_DISPATCH(b, (os_launch_scatter<BB, OS_ITEMS_MIN>(st, *keys, *vals, *keys_alt, *vals_alt, n_host, n_dev,
                                                                 tiles, shift, temp + (size_t)p * OS_RADIX,
-                                                                temp + OS_CTR + p, status, err)));
+                                                                temp + OS_CTR + p, status, err, rg, nranges)));
         } else {
             OS_DISPATCH(b, (os_launch_scatter<BB, 2 * OS_ITEMS_MIN>(st, *keys, *vals, *keys_alt, *vals_alt, n_host,
                                                                     n_dev, tiles, shift, temp + (size_t)p * OS_RADIX,
-                                                                    temp + OS_CTR + p, status, err)));
+                                                                    temp + OS_CTR + p, status, err, rg, nranges)));
         }
         std::swap(*keys, *keys_alt);
         std::swap(*vals, *vals_alt);
     }
+    return P == 1 && ranges != nullptr;
 }
 
 // ------------------------------------------------------------- binning ----
 
-// Pairs of 256 consecutive instances in depth order, written cooperatively:
-// their pair ranges are contiguous ([offsets[r], offsets[r] + counts[r]) in
-// rank order), so the workgroup strides over the whole run with one pair per
-// thread (coalesced stores) and finds each pair's instance by a binary search
-// over the offsets staged in LDS.  Within an instance the pairs run row-major
-// over its tile rectangle (over the kept tiles of a rectangle of at most 64
-// tiles), read from the binning records in depth order.  Instance id = view * n_convex + convex; the view's
-// tiles start at its tile_off.
+// (cell, convex) pairs of 256 consecutive instances in depth order, written
+// cooperatively: their pair ranges are contiguous ([offsets[r], offsets[r] +
+// counts[r]) in rank order), so the workgroup strides over the whole run with
+// one pair per thread (coalesced stores).  Within an instance the pairs run
+// row-major over the cells that its tile rectangle meets; a pair's key is the
+// cell with the mask of its kept tiles above (see FrameHeader).  Instance id =
+// view * n_convex + convex.
 constexpr int EMIT_BLOCK = 256;
 constexpr int EMIT_ITEMS = 8;
 constexpr int EMIT_CHUNK = EMIT_BLOCK * EMIT_ITEMS; // pairs whose owners are found per round
 
-// Position of the q-th set bit of m (q < popcount(m)).
-__device__ __forceinline__ uint32_t nth_set_bit(uint64_t m, uint32_t q)
+// The kept tiles of the cell whose first tile is (ctx, cty), one bit per tile
+// row-major over the cell: the rectangle's mask (at most 64 tiles) or its
+// bands' column intervals (larger), cut to the cell.
+__device__ __forceinline__ uint32_t cell_mask(uint64_t mask, int tx0, int ty0, int w, int th, int ctx, int cty,
+                                              int shift)
 {
-    uint32_t pos = 0;
-    uint32_t w = (uint32_t)m;
-    const uint32_t c32 = __popc(w);
-    if (q >= c32) { q -= c32; w = (uint32_t)(m >> 32); pos = 32; }
-#pragma unroll
-    for (int half = 16; half >= 1; half >>= 1) {
-        const uint32_t c = __popc(w & ((1u << half) - 1u));
-        if (q >= c) { q -= c; w >>= half; pos += half; }
+    const int side = 1 << shift;
+    const uint32_t sidemask = (1u << side) - 1u;
+    const int c0 = ctx - tx0; // the cell's first column, rectangle-relative (may be negative)
+    uint32_t m = 0;
+    if (w * th <= 64) {
+        const uint64_t rowmask = w < 64 ? (1ull << w) - 1ull : ~0ull;
+        for (int sy = 0; sy < side; ++sy) {
+            const int r = cty + sy - ty0;
+            if (r < 0 || r >= th) continue;
+            const uint64_t row = (mask >> (r * w)) & rowmask;
+            const uint32_t nib = (uint32_t)(c0 >= 0 ? row >> c0 : row << -c0) & sidemask;
+            m |= nib << (sy * side);
+        }
+    } else {
+        const int bh = big_bh(th);
+        for (int sy = 0; sy < side; ++sy) {
+            const int r = cty + sy - ty0;
+            if (r < 0 || r >= th) continue;
+            int row0, nrow, col0, ncol;
+            big_band(mask, w, th, r / bh, &row0, &nrow, &col0, &ncol);
+            const int lo = max(col0 - c0, 0), hi = min(col0 + ncol - 1 - c0, side - 1);
+            if (ncol > 0 && lo <= hi) m |= (((2u << hi) - 1u) & ~((1u << lo) - 1u)) << (sy * side);
+        }
     }
-    return pos;
+    return m;
 }
 
 __global__ __launch_bounds__(EMIT_BLOCK) void emit_pairs_kernel(
     uint32_t n, uint32_t n_convex, const uint32_t *__restrict__ sorted_ids, const uint32_t *__restrict__ offsets,
     const uint32_t *__restrict__ counts_sorted, const uint4 *__restrict__ bins_sorted,
-    const FrameHeader *__restrict__ frame, uint32_t capacity, uint32_t *__restrict__ pair_tiles,
+    const FrameHeader *__restrict__ frame, uint32_t capacity, uint32_t *__restrict__ pair_keys,
     uint32_t *__restrict__ pair_ids, ZeroSpans zero)
 {
-    zero_share(zero); // the tile sort's temporaries
+    zero_share(zero); // the cell sort's temporaries
     __shared__ uint32_t s_off[EMIT_BLOCK];
     __shared__ uint32_t s_id[EMIT_BLOCK];
-    __shared__ uint32_t s_x0w[EMIT_BLOCK];  // tx0 | rect width << 16
-    __shared__ uint32_t s_base[EMIT_BLOCK]; // global tile of the rectangle's first row start: toff + ty0 * tiles_x
-    __shared__ uint32_t s_tx[EMIT_BLOCK];   // the view's tiles_x
-    __shared__ uint64_t s_mask[EMIT_BLOCK]; // kept tiles (binning record encoding)
-    __shared__ uint32_t s_small[EMIT_BLOCK];
-    __shared__ uint32_t s_th[EMIT_BLOCK];    // rect height
-    __shared__ uint32_t s_bend[EMIT_BLOCK][BIG_BANDS]; // large rectangles: pairs up to the end of each band
-    __shared__ float s_rw[EMIT_BLOCK];       // 1 / rect width
+    __shared__ uint4 s_bin[EMIT_BLOCK];
+    __shared__ uint32_t s_base[EMIT_BLOCK]; // the view's cell_off
+    __shared__ uint32_t s_cx[EMIT_BLOCK];   // the view's cells per row
+    __shared__ float s_rw[EMIT_BLOCK];      // 1 / cells per row of the rectangle
     __shared__ uint32_t s_own[EMIT_CHUNK];  // owner (block-local convex) of each pair of the chunk
     __shared__ uint32_t s_wmax[EMIT_BLOCK / 64];
     __shared__ uint32_t s_end;
@@ -596,43 +659,23 @@ __global__ __launch_bounds__(EMIT_BLOCK) void emit_pairs_kernel(
     const int cnt = (int)min((uint32_t)EMIT_BLOCK, n - r0);
     const int tid = threadIdx.x;
     const ViewDesc *views = reinterpret_cast<const ViewDesc *>(frame + 1);
+    const uint32_t kbits = frame->key_bits;
     if (tid < cnt) {
         const uint32_t r = r0 + tid;
         const uint32_t id = sorted_ids[r];
-        const uint32_t off = offsets[r];
+        const uint32_t off = offsets[r], count = counts_sorted[r];
         s_off[tid] = off;
         s_id[tid] = id;
-        uint32_t x0w = 0, base = 0, tx = 1, small = 0, th = 0;
-        uint64_t mask = 0;
-        if (counts_sorted[r] > 0) {
+        if (count > 0) {
             const uint4 b = bins_sorted[r];
-            const uint32_t tx0 = b.x & 0xFFFFu, ty0 = b.x >> 16, tx1 = b.y & 0xFFFFu, ty1 = b.y >> 16;
             const ViewDesc &vd = views[id / n_convex];
-            tx = (uint32_t)vd.tiles_x;
-            x0w = tx0 | ((tx1 - tx0 + 1) << 16);
-            base = (uint32_t)vd.tile_off + ty0 * tx;
-            th = ty1 - ty0 + 1;
-            small = (tx1 - tx0 + 1) * th <= 64u;
-            mask = (uint64_t)b.z | ((uint64_t)b.w << 32);
+            s_bin[tid] = b;
+            s_base[tid] = (uint32_t)vd.cell_off;
+            const uint32_t shift = bin_shift(b);
+            s_cx[tid] = ((uint32_t)vd.tiles_x + (1u << shift) - 1u) >> shift;
+            s_rw[tid] = 1.0f / (float)((bin_tx1(b) >> shift) - (bin_tx0(b) >> shift) + 1u);
         }
-        s_x0w[tid] = x0w;
-        s_base[tid] = base;
-        s_tx[tid] = tx;
-        s_mask[tid] = mask;
-        s_small[tid] = small;
-        s_th[tid] = th;
-        if (!small && th > 0) {
-            uint32_t acc = 0;
-#pragma unroll
-            for (int r = 0; r < BIG_BANDS; ++r) {
-                int row0, nrow, col0, ncol;
-                big_band(mask, (int)(x0w >> 16), (int)th, r, &row0, &nrow, &col0, &ncol);
-                acc += (uint32_t)(nrow * ncol);
-                s_bend[tid][r] = acc;
-            }
-        }
-        s_rw[tid] = 1.0f / (float)max(x0w >> 16, 1u);
-        if (tid == cnt - 1) s_end = off + counts_sorted[r];
+        if (tid == cnt - 1) s_end = off + count;
     }
     __syncthreads();
     const uint32_t p0 = s_off[0], p1 = min(s_end, capacity);
@@ -683,48 +726,40 @@ __global__ __launch_bounds__(EMIT_BLOCK) void emit_pairs_kernel(
         for (uint32_t j = tid; j < cn; j += EMIT_BLOCK) {
             const uint32_t p = c0 + j;
             const int lo = (int)s_own[j];
-            uint32_t q = p - s_off[lo];
-            const uint32_t x0w = s_x0w[lo], w = x0w >> 16;
-            uint32_t row, col;
-            if (s_small[lo]) {
-                q = nth_set_bit(s_mask[lo], q); // the q-th kept tile of the rectangle
-                // q / w through the reciprocal (q < 2^24), corrected by one step
-                row = (uint32_t)((float)q * s_rw[lo]);
-                if (row * w > q) --row;
-                else if ((row + 1) * w <= q) ++row;
-                col = q - row * w;
-            } else { // the q-th tile of the kept bands, band by band, row-major in each
-                int r = 0;
-                uint32_t before = 0;
-#pragma unroll
-                for (int k = 0; k < BIG_BANDS - 1; ++k) {
-                    const uint32_t e = s_bend[lo][k];
-                    if (q >= e) { r = k + 1; before = e; }
-                }
-                int row0, nrow, col0, ncol;
-                big_band(s_mask[lo], (int)w, (int)s_th[lo], r, &row0, &nrow, &col0, &ncol);
-                const uint32_t qb = q - before, nc = (uint32_t)max(ncol, 1);
-                uint32_t rr = (uint32_t)((float)qb / (float)nc); // qb < 2^24, corrected by one step
-                if (rr * nc > qb) --rr;
-                else if ((rr + 1) * nc <= qb) ++rr;
-                row = (uint32_t)row0 + rr;
-                col = (uint32_t)col0 + (qb - rr * nc);
-            }
-            pair_tiles[p] = s_base[lo] + row * s_tx[lo] + (x0w & 0xFFFFu) + col;
+            const uint32_t q = p - s_off[lo];
+            const uint4 b = s_bin[lo];
+            const uint32_t tx0 = bin_tx0(b), ty0 = bin_ty0(b), tx1 = bin_tx1(b), ty1 = bin_ty1(b), shift = bin_shift(b);
+            const uint32_t cx0 = tx0 >> shift, cw = (tx1 >> shift) - cx0 + 1u;
+            // q / cw through the reciprocal (q < 2^24), corrected by one step
+            uint32_t row = (uint32_t)((float)q * s_rw[lo]);
+            if (row * cw > q) --row;
+            else if ((row + 1) * cw <= q) ++row;
+            const uint32_t cx = cx0 + (q - row * cw), cy = (ty0 >> shift) + row;
+            const uint32_t mask = cell_mask((uint64_t)b.z | ((uint64_t)b.w << 32), (int)tx0, (int)ty0, (int)(tx1 - tx0 + 1u),
+                                            (int)(ty1 - ty0 + 1u), (int)(cx << shift), (int)(cy << shift), (int)shift);
+            pair_keys[p] = (s_base[lo] + cy * s_cx[lo] + cx) | (mask << kbits);
             pair_ids[p] = s_id[lo];
         }
         __syncthreads();
     }
 }
 
-// Sort keys that put long tile lists first: key = 0xFFFF - min(length, 0xFFFF).
-__global__ void tile_length_keys_kernel(uint32_t ntiles, const uint2 *__restrict__ ranges,
-                                        uint32_t *__restrict__ keys, uint32_t *__restrict__ vals)
+// Sort keys that put the tiles of long cell lists first: key = 0xFFFF -
+// min(length, 0xFFFF); slots past the frame's tiles sort behind them.
+__global__ void tile_length_keys_kernel(uint32_t ntiles, const FrameHeader *__restrict__ frame,
+                                        const uint2 *__restrict__ ranges, uint32_t *__restrict__ keys,
+                                        uint32_t *__restrict__ vals)
 {
     const uint32_t t = blockIdx.x * blockDim.x + threadIdx.x;
     if (t >= ntiles) return;
-    const uint2 r = ranges[t];
-    const uint32_t len = r.y - r.x;
+    uint32_t len = 0;
+    if (t < frame->total_tiles) {
+        const ViewDesc *views = reinterpret_cast<const ViewDesc *>(frame + 1);
+        const ViewDesc &vd = views[find_view(views, (int)frame->nviews, (int)t)];
+        const uint32_t lt = t - (uint32_t)vd.tile_off, tx = lt % (uint32_t)vd.tiles_x, ty = lt / (uint32_t)vd.tiles_x;
+        const uint2 r = ranges[tile_cell(vd, tx, ty)];
+        len = r.y - r.x;
+    }
     keys[t] = 0xFFFFu - (len < 0xFFFFu ? len : 0xFFFFu);
     vals[t] = t;
 }
@@ -762,23 +797,24 @@ __global__ void fill_u32_kernel(uint32_t *__restrict__ p, size_t n, uint32_t v)
         p[i] = v;
 }
 
-// [start, end) of every tile's run in the sorted tile ids.  Each thread takes
-// RANGE_ITEMS consecutive ids in 16-byte loads (the sorted ids are 16-byte
-// aligned) plus the id before them, and marks the run boundaries among them.
+// [start, end) of every cell's run in the sorted keys (the cell is a key's low
+// bits).  Each thread takes RANGE_ITEMS consecutive keys in 16-byte loads (the
+// sorted keys are 16-byte aligned) plus the key before them, and marks the run
+// boundaries among them.
 constexpr int RANGE_ITEMS = 8;
 
-// ntiles bounds the tile ids written (every id of a pair is below it; the
+// ncells bounds the cells written (every cell of a pair is below it; the
 // bound keeps a wrong count from writing past the ranges).
-__global__ __launch_bounds__(256) void tile_ranges_kernel(const uint32_t *__restrict__ tiles,
+__global__ __launch_bounds__(256) void cell_ranges_kernel(const uint32_t *__restrict__ keys,
                                                           const uint32_t *__restrict__ n_dev, uint32_t n_host,
-                                                          uint2 *__restrict__ ranges, uint32_t ntiles)
+                                                          uint2 *__restrict__ ranges, uint32_t ncells, uint32_t cmask)
 {
     const uint32_t n = n_dev ? *n_dev : n_host;
     const size_t i0 = ((size_t)blockIdx.x * blockDim.x + threadIdx.x) * RANGE_ITEMS;
     if (i0 >= n) return;
     uint32_t t[RANGE_ITEMS];
     if (i0 + RANGE_ITEMS <= n) {
-        const uint4 *src = reinterpret_cast<const uint4 *>(tiles + i0);
+        const uint4 *src = reinterpret_cast<const uint4 *>(keys + i0);
 #pragma unroll
         for (int q = 0; q < RANGE_ITEMS / 4; ++q) {
             const uint4 w = src[q];
@@ -786,20 +822,22 @@ __global__ __launch_bounds__(256) void tile_ranges_kernel(const uint32_t *__rest
         }
     } else {
 #pragma unroll
-        for (int k = 0; k < RANGE_ITEMS; ++k) t[k] = i0 + k < n ? tiles[i0 + k] : 0u;
+        for (int k = 0; k < RANGE_ITEMS; ++k) t[k] = i0 + k < n ? keys[i0 + k] : 0u;
     }
-    uint32_t prev = i0 > 0 ? tiles[i0 - 1] : 0xFFFFFFFFu;
+#pragma unroll
+    for (int k = 0; k < RANGE_ITEMS; ++k) t[k] &= cmask;
+    uint32_t prev = i0 > 0 ? (keys[i0 - 1] & cmask) : 0xFFFFFFFFu;
 #pragma unroll
     for (int k = 0; k < RANGE_ITEMS; ++k) {
         const size_t i = i0 + k;
         if (i >= n) break;
         if (t[k] != prev) { // a run starts at i and the previous one ends there
-            if (t[k] < ntiles) ranges[t[k]].x = (uint32_t)i;
-            if (i > 0 && prev < ntiles) ranges[prev].y = (uint32_t)i;
+            if (t[k] < ncells) ranges[t[k]].x = (uint32_t)i;
+            if (i > 0 && prev < ncells) ranges[prev].y = (uint32_t)i;
         }
         prev = t[k];
     }
-    if (i0 + RANGE_ITEMS >= n && prev < ntiles) ranges[prev].y = n; // the last run
+    if (i0 + RANGE_ITEMS >= n && prev < ncells) ranges[prev].y = n; // the last run
 }
 
 void launch_fill_u32(hipStream_t st, uint32_t *p, size_t n, uint32_t v)
@@ -837,20 +875,21 @@ void launch_zero_ranges(hipStream_t st, uint32_t *p0, size_t n0, uint32_t *p1, s
     hipLaunchKernelGGL(zero_ranges_kernel, dim3((unsigned)blocks), dim3(256), 0, st, r);
 }
 
-void launch_tile_length_keys(hipStream_t st, uint32_t ntiles, const uint2 *ranges, uint32_t *keys, uint32_t *vals)
+void launch_tile_length_keys(hipStream_t st, uint32_t ntiles, const FrameHeader *frame, const uint2 *ranges,
+                             uint32_t *keys, uint32_t *vals)
 {
     if (ntiles == 0) return;
-    hipLaunchKernelGGL(tile_length_keys_kernel, dim3((ntiles + 255) / 256), dim3(256), 0, st, ntiles, ranges, keys,
-                       vals);
+    hipLaunchKernelGGL(tile_length_keys_kernel, dim3((ntiles + 255) / 256), dim3(256), 0, st, ntiles, frame, ranges,
+                       keys, vals);
 }
 
-void launch_tile_ranges(hipStream_t st, const uint32_t *tiles, uint32_t n_host, const uint32_t *n_dev,
-                        uint32_t n_capacity, uint2 *ranges, uint32_t ntiles)
+void launch_cell_ranges(hipStream_t st, const uint32_t *keys, uint32_t n_host, const uint32_t *n_dev,
+                        uint32_t n_capacity, uint2 *ranges, uint32_t ncells, uint32_t cmask)
 {
     if (n_capacity == 0) return;
     const size_t threads = ((size_t)n_capacity + RANGE_ITEMS - 1) / RANGE_ITEMS;
-    hipLaunchKernelGGL(tile_ranges_kernel, dim3((unsigned)((threads + 255) / 256)), dim3(256), 0, st, tiles, n_dev,
-                       n_host, ranges, ntiles);
+    hipLaunchKernelGGL(cell_ranges_kernel, dim3((unsigned)((threads + 255) / 256)), dim3(256), 0, st, keys, n_dev,
+                       n_host, ranges, ncells, cmask);
 }
 
 } // namespace cs

@@ -2,12 +2,14 @@
 // "Initialization and losses":
 //
 // * the photometric loss L = (1 - lambda) L1 + lambda (1 - SSIM) and its
-//   gradient with respect to the rendered image, in two tiled passes: the
-//   first blurs x, y, x^2, y^2 and xy with the 11x11 Gaussian window
-//   (separably, through LDS, zero padding), forms the SSIM map and its
-//   partial derivatives with respect to the blurred moments; the second blurs
-//   those partials (the window is symmetric: the same blur is its adjoint)
-//   and combines them with x and y into dL/dx;
+//   gradient with respect to the rendered image, in one pass down strips of
+//   columns: the rows' moments x, y, x^2 + y^2 and xy are blurred with the
+//   11x11 Gaussian window (separably, zero padding), each row of blurred
+//   moments gives the SSIM map and its partial derivatives with respect to
+//   them, and the partials' rows are blurred in turn (the window is symmetric:
+//   the same blur is its adjoint) and combined with x and y into dL/dx; images
+//   that fill the chip only a few times over take the two blurs as two passes
+//   over tiles, with the partials in memory between them;
 // * the fused Adam step on the raw parameters with their activations
 //   (sigmoid opacity, exponential delta and sigma): one launch per parameter
 //   array, one element per thread and iteration, read raw, m, v and
@@ -25,18 +27,24 @@ namespace {
 
 // ------------------------------------------------------- L1 + D-SSIM ----
 
-constexpr int SS_TILE = 16;                 // output pixels per side of a workgroup
-constexpr int SS_R = 5;                     // window radius (11 taps)
-constexpr int SS_IN = SS_TILE + 2 * SS_R;   // input rows / columns with the halo
+constexpr int SS_R = 5;                     // window radius
+constexpr int SS_N = 2 * SS_R + 1;          // taps
 constexpr float SS_C1 = 0.01f * 0.01f;      // SSIM constants for values in [0, 1]
 constexpr float SS_C2 = 0.03f * 0.03f;
 
 struct SsimArgs {
-    int W, H;
+    int W, W3, H;     // pixels and floats per row (three interleaved channels), rows
+    int rows;         // output rows of a workgroup
     float lambda;
     float inv_n;      // 1 / (3 W H): the means run over pixels and channels
-    float g[2 * SS_R + 1]; // normalised Gaussian window, sigma 1.5
+    float g[SS_N];    // normalised Gaussian window, sigma 1.5
 };
+
+// ---- two passes over tiles, with the partials of every pixel in memory between
+//      them: images of SS_TILES_FROM to SS_TILES_TO pixels (see there)
+
+constexpr int SS_TILE = 16;                 // output pixels per side of a workgroup
+constexpr int SS_IN = SS_TILE + 2 * SS_R;   // input rows / columns with the halo
 
 // Pass 1: per pixel and channel the SSIM value S and its partial derivatives
 // with respect to the blurred moments mu_x, E[x^2] and E[xy] (mu_y and E[y^2]
@@ -147,24 +155,6 @@ __global__ __launch_bounds__(SS_TILE * SS_TILE) void ssim_moments_kernel(const f
     }
 }
 
-// loss += lambda + inv_n * (sum of the blocks' terms): one workgroup.
-__global__ __launch_bounds__(1024) void ssim_loss_sum_kernel(const float *__restrict__ block_loss, int nb, SsimArgs a,
-                                                             float *__restrict__ loss)
-{
-    __shared__ float s_w[16];
-    float t = 0.0f;
-    for (int b = threadIdx.x; b < nb; b += 1024) t += block_loss[b];
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) t += __shfl_xor(t, o, 64);
-    if ((threadIdx.x & 63) == 0) s_w[threadIdx.x >> 6] = t;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        float u = 0.0f;
-        for (int w = 0; w < 16; ++w) u += s_w[w];
-        *loss += a.lambda + u * a.inv_n;
-    }
-}
-
 // Pass 2: dL/dx = (1 - lambda) sign(x - y) / n - lambda / n (G*d_mu + 2 x G*d_xx + y G*d_xy).
 __global__ __launch_bounds__(SS_TILE * SS_TILE) void ssim_grad_kernel(const float *__restrict__ x,
                                                                       const float *__restrict__ y, SsimArgs a,
@@ -231,6 +221,213 @@ __global__ __launch_bounds__(SS_TILE * SS_TILE) void ssim_grad_kernel(const floa
         const float sg = d > 0.0f ? 1.0f : (d < 0.0f ? -1.0f : 0.0f);
         const float ds = b[3 * ch] + 2.0f * xv * b[3 * ch + 1] + yv * b[3 * ch + 2];
         grad[p + ch] = a.inv_n * ((1.0f - a.lambda) * sg - a.lambda * ds);
+    }
+}
+
+// ---- one pass down strips of columns
+
+// A workgroup takes SS_OUT float columns of `rows` output rows and walks down
+// them, one thread per column (columns are channels of pixels, so taps are 3
+// floats apart).  Per step a thread blurs a row of moments horizontally out of
+// LDS and adds it to the vertical sums of the 11 rows it belongs to; the row
+// that completes gives its partial derivatives, which go through LDS and a
+// second pair of blurs in the step after; the row of partials that completes
+// there gives an output row.  The sums are registers (the row loop is unrolled
+// over the 11 phases of their rotation), input rows are loaded two steps ahead,
+// and one barrier a step suffices with both LDS rows double-buffered.
+//
+// Bound by VALU issue: 154 fused multiply-adds of the blurs and about 80 other
+// instructions per column and step, 20 warm-up rows per workgroup and 30 of 256
+// columns of halo.  Two passes over tiles with the nine partials of a pixel in
+// memory between them, which read 26 x 26 pixels for 16 x 16, took 157 us at
+// 1920x1080; this takes 106 us.
+template <int P> struct Phase { static constexpr int value = P; };
+constexpr int SS_BLOCK = 256;
+constexpr int SS_HALO = 3 * SS_R;
+constexpr int SS_OUT = SS_BLOCK - 2 * SS_HALO;
+__global__ __launch_bounds__(SS_BLOCK) void ssim_kernel(const float *__restrict__ x, const float *__restrict__ y, SsimArgs a,
+                                                        float *__restrict__ grad, float *__restrict__ block_loss)
+{
+    __shared__ float4 s_in[2][SS_BLOCK + 2 * SS_HALO]; // x, y, x^2 + y^2, xy
+    __shared__ float4 s_p[2][SS_BLOCK + 2 * SS_HALO];  // dS/dmu_x, dS/dE[x^2], dS/dE[xy]
+    const int t = threadIdx.x;
+    const int c = blockIdx.x * SS_OUT - SS_HALO + t; // the thread's column
+    const int r0 = blockIdx.y * a.rows, r1 = min(r0 + a.rows, a.H);
+    const bool col_in = c >= 0 && c < a.W3;
+    const bool owner = col_in && t >= SS_HALO && t < SS_HALO + SS_OUT; // of the column's outputs and loss terms
+    // the input columns: entry t (column c - SS_HALO) and, for the first 2
+    // SS_HALO threads, entry SS_BLOCK + t
+    const int ca = c - SS_HALO, cb = ca + SS_BLOCK;
+    const bool in_a = ca >= 0 && ca < a.W3, in_b = t < 2 * SS_HALO && cb >= 0 && cb < a.W3;
+    float xa, ya, xb, yb; // the row in flight
+    auto load = [&](int r) { // unconditional loads (a clamped address), zeroed after
+        const bool ok = r >= 0 && r < a.H && r < r1 + 2 * SS_R;
+        const size_t row = (size_t)(ok ? r : 0) * a.W3;
+        const size_t pa = row + (in_a ? ca : 0), pb = row + (in_b ? cb : 0);
+        xa = x[pa]; ya = y[pa]; xb = x[pb]; yb = y[pb];
+        if (!(ok && in_a)) xa = ya = 0.0f;
+        if (!(ok && in_b)) xb = yb = 0.0f;
+    };
+    auto store = [&](int buf) {
+        s_in[buf][t] = make_float4(xa, ya, fmaf(xa, xa, ya * ya), xa * ya);
+        if (t < 2 * SS_HALO) s_in[buf][SS_BLOCK + t] = make_float4(xb, yb, fmaf(xb, xb, yb * yb), xb * yb);
+    };
+    // the halves of s_p's halo that no thread writes are read only for columns
+    // without an output
+    float m[SS_N][4] = {}; // vertical sums of the moments, one slot per row under way
+    float b[SS_N][3] = {}; // of the partials
+    for (int j = t; j < 2 * (SS_BLOCK + 2 * SS_HALO); j += SS_BLOCK) (&s_p[0][0])[j] = make_float4(0.f, 0.f, 0.f, 0.f);
+    float sum = 0.0f; // loss terms
+    float nx = 0.0f, ny = 0.0f;
+    const int top = r0 - 2 * SS_R, steps = r1 - r0 + 4 * SS_R + 1;
+    load(top);
+    store(0);
+    load(top + 1);
+    __syncthreads();
+    // one step; its phase (i modulo 11) is a constant, so that the slots are registers
+    auto step = [&](auto phase, int i) __attribute__((always_inline)) {
+        constexpr int p = decltype(phase)::value;
+        const int r = top + i, out_row = r - 2 * SS_R - 1;
+        // the next row leaves its registers, the one after it starts
+        store((i + 1) & 1);
+        load(r + 2);
+        // x and y of this step's output row, loaded in the last one
+        const bool out_ok = owner && out_row >= r0;
+        const float ox = nx, oy = ny;
+        const size_t op = out_ok ? (size_t)out_row * a.W3 + c : 0;
+        const size_t np = owner && out_row + 1 >= r0 && out_row + 1 < r1 ? (size_t)(out_row + 1) * a.W3 + c : 0;
+        nx = x[np];
+        ny = y[np];
+        // moments of input row r, horizontally, into the rows r - 5 .. r + 5
+        float4 h = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+        for (int k = 0; k < SS_N; ++k) {
+            const float4 e = s_in[i & 1][t + 3 * k];
+            h.x = fmaf(a.g[k], e.x, h.x);
+            h.y = fmaf(a.g[k], e.y, h.y);
+            h.z = fmaf(a.g[k], e.z, h.z);
+            h.w = fmaf(a.g[k], e.w, h.w);
+        }
+#pragma unroll
+        for (int j = 0; j < SS_N; ++j) {
+            float *q = m[(p + SS_R - j + SS_N) % SS_N]; // row r + 5 - j
+            q[0] = j == 0 ? a.g[0] * h.x : fmaf(a.g[j], h.x, q[0]);
+            q[1] = j == 0 ? a.g[0] * h.y : fmaf(a.g[j], h.y, q[1]);
+            q[2] = j == 0 ? a.g[0] * h.z : fmaf(a.g[j], h.z, q[2]);
+            q[3] = j == 0 ? a.g[0] * h.w : fmaf(a.g[j], h.w, q[3]);
+        }
+        {   // row r - 5 is complete: S = A1 A2 / (B1 B2) and its partials
+            const float *q = m[(p + SS_R + 1) % SS_N];
+            const int s = r - SS_R;
+            const float mx = q[0], my = q[1], mm = mx * mx + my * my, mxy = mx * my;
+            const float A1 = 2.0f * mxy + SS_C1, A2 = 2.0f * (q[3] - mxy) + SS_C2;
+            const float B1 = mm + SS_C1, B2 = (q[2] - mm) + SS_C2;
+            const float i1 = 1.0f / B1, i2 = 1.0f / B2, ii = i1 * i2;
+            const float S = A1 * A2 * ii;
+            const bool ok = col_in && s >= 0 && s < a.H;
+            const float d0 = 2.0f * (my * (A2 - A1) * ii + mx * S * (i2 - i1));
+            s_p[i & 1][SS_HALO + t] =
+                make_float4(ok ? d0 : 0.0f, ok ? -S * i2 : 0.0f, ok ? 2.0f * A1 * ii : 0.0f, 0.0f);
+            if (owner && s >= r0 && s < r1) sum -= a.lambda * S;
+        }
+        // partials of row r - 6 (last step's), into the rows r - 11 .. r - 1
+        float3 u = make_float3(0.f, 0.f, 0.f);
+#pragma unroll
+        for (int k = 0; k < SS_N; ++k) {
+            const float4 e = s_p[(i + 1) & 1][t + 3 * k];
+            u.x = fmaf(a.g[k], e.x, u.x);
+            u.y = fmaf(a.g[k], e.y, u.y);
+            u.z = fmaf(a.g[k], e.z, u.z);
+        }
+#pragma unroll
+        for (int j = 0; j < SS_N; ++j) {
+            float *q = b[(p + SS_R - j + SS_N) % SS_N];
+            q[0] = j == 0 ? a.g[0] * u.x : fmaf(a.g[j], u.x, q[0]);
+            q[1] = j == 0 ? a.g[0] * u.y : fmaf(a.g[j], u.y, q[1]);
+            q[2] = j == 0 ? a.g[0] * u.z : fmaf(a.g[j], u.z, q[2]);
+        }
+        if (out_ok) { // dL/dx = (1 - lambda) sign(x - y) / n - lambda / n (G*d_mu + 2 x G*d_xx + y G*d_xy)
+            const float *q = b[(p + SS_R + 1) % SS_N];
+            const float d = ox - oy;
+            const float sg = d > 0.0f ? 1.0f : (d < 0.0f ? -1.0f : 0.0f);
+            const float ds = q[0] + 2.0f * ox * q[1] + oy * q[2];
+            grad[op] = a.inv_n * ((1.0f - a.lambda) * sg - a.lambda * ds);
+            sum += (1.0f - a.lambda) * fabsf(d);
+        }
+        __syncthreads();
+    };
+    for (int i = 0; i < steps; i += SS_N) {
+        step(Phase<0>{}, i);
+        if (i + 1 < steps) step(Phase<1>{}, i + 1);
+        if (i + 2 < steps) step(Phase<2>{}, i + 2);
+        if (i + 3 < steps) step(Phase<3>{}, i + 3);
+        if (i + 4 < steps) step(Phase<4>{}, i + 4);
+        if (i + 5 < steps) step(Phase<5>{}, i + 5);
+        if (i + 6 < steps) step(Phase<6>{}, i + 6);
+        if (i + 7 < steps) step(Phase<7>{}, i + 7);
+        if (i + 8 < steps) step(Phase<8>{}, i + 8);
+        if (i + 9 < steps) step(Phase<9>{}, i + 9);
+        if (i + 10 < steps) step(Phase<10>{}, i + 10);
+    }
+    // the block's loss terms into its own slot (same-address atomics from
+    // every block would serialise); a last pass adds the slots
+    __shared__ float s_w[SS_BLOCK / 64];
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) sum += __shfl_xor(sum, o, 64);
+    if ((t & 63) == 0) s_w[t >> 6] = sum;
+    __syncthreads();
+    if (t == 0) block_loss[blockIdx.y * gridDim.x + blockIdx.x] = (s_w[0] + s_w[1]) + (s_w[2] + s_w[3]);
+}
+
+// Output rows of a workgroup: fewer rows mean more workgroups on a CU, which
+// hide each other's latencies, and more warm-up steps.  A step of k workgroups
+// on one CU (at most 4 fit) was measured at 1.08, 1.40, 1.74 and 2.1 us for k = 1
+// to 4 (120, 60, 40 and 30 rows at 1920x1080: 152, 113, 106, 108 us): 0.74 + 0.34
+// k; the rows with the least steps x price are taken.
+int ssim_rows(int strips, int H, int cus)
+{
+    int best = H;
+    double least = 1e300;
+    for (int segs = 1; segs <= H; ++segs) {
+        const int rows = (H + segs - 1) / segs, wgs = strips * ((H + rows - 1) / rows);
+        const int k = (wgs + cus - 1) / cus;
+        if (k > 8 && segs > 1) break;
+        const double cost = (rows + 4 * SS_R + 1) * (k / 4 * 2.1 + (k % 4 ? 0.74 + 0.34 * (k % 4) : 0.0));
+        if (cost < least) {
+            least = cost;
+            best = rows;
+        }
+    }
+    return best;
+}
+
+// Pixels of the images that go through the tiles.  A strip's step costs about a
+// microsecond however few workgroups run, which tiles undercut while the image
+// fills the chip but a few times over (us, strips / tiles: 200x120 29 / 33,
+// 400x300 34 / 32, 640x427 41 / 34, 979x546 51 / 52, 1297x840 72 / 83,
+// 1920x1080 109 / 147).
+constexpr size_t SS_TILES_FROM = 96 * 1024, SS_TILES_TO = 512 * 1024;
+
+__global__ __launch_bounds__(256) void copy_floats_kernel(size_t n, const float *__restrict__ from, float *__restrict__ to)
+{
+    for (size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x) to[i] = from[i];
+}
+
+// loss += lambda + inv_n * (sum of the blocks' terms): one workgroup.
+__global__ __launch_bounds__(1024) void ssim_loss_sum_kernel(const float *__restrict__ block_loss, int nb, SsimArgs a,
+                                                             float *__restrict__ loss)
+{
+    __shared__ float s_w[16];
+    float t = 0.0f;
+    for (int b = threadIdx.x; b < nb; b += 1024) t += block_loss[b];
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) t += __shfl_xor(t, o, 64);
+    if ((threadIdx.x & 63) == 0) s_w[threadIdx.x >> 6] = t;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        float u = 0.0f;
+        for (int w = 0; w < 16; ++w) u += s_w[w];
+        *loss += a.lambda + u * a.inv_n;
     }
 }
 
@@ -402,24 +599,42 @@ int cs_ssim_loss_grad(cs_ctx *ctx, const float *rgb, const float *target, int32_
     hipStream_t st = (hipStream_t)hip_stream;
     SsimArgs a;
     a.W = width;
+    a.W3 = 3 * width;
     a.H = height;
     a.lambda = lambda;
     a.inv_n = (float)(1.0 / (3.0 * (double)width * (double)height));
-    double gs[2 * SS_R + 1], tot = 0.0;
+    double gs[SS_N], tot = 0.0;
     for (int t = -SS_R; t <= SS_R; ++t) tot += gs[t + SS_R] = std::exp(-(double)(t * t) / (2.0 * 1.5 * 1.5));
-    for (int t = 0; t <= 2 * SS_R; ++t) a.g[t] = (float)(gs[t] / tot);
-    const dim3 grid((width + SS_TILE - 1) / SS_TILE, (height + SS_TILE - 1) / SS_TILE), block(SS_TILE * SS_TILE);
+    for (int t = 0; t < SS_N; ++t) a.g[t] = (float)(gs[t] / tot);
+    int cus = 256;
+    (void)hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, ctx->device);
+    const int strips = (a.W3 + SS_OUT - 1) / SS_OUT;
+    a.rows = ssim_rows(strips, height, std::max(1, cus));
+    const size_t pixels = (size_t)width * height, n = 3 * pixels;
+    const bool tiles = pixels >= SS_TILES_FROM && pixels < SS_TILES_TO;
+    const dim3 grid = tiles ? dim3((width + SS_TILE - 1) / SS_TILE, (height + SS_TILE - 1) / SS_TILE)
+                            : dim3(strips, (height + a.rows - 1) / a.rows);
     const int nb = (int)(grid.x * grid.y);
-    float *part = nullptr;
-    const size_t part_floats = (size_t)width * height * 9;
-    hipError_t e = hipMallocAsync((void **)&part, (part_floats + nb) * sizeof(float), st);
+    // strips read rows that other workgroups have done: a gradient written over
+    // an input goes through scratch
+    auto overlaps = [&](const float *p) { return dl_drgb < p + n && p < dl_drgb + n; };
+    const bool aside = !tiles && (overlaps(rgb) || overlaps(target));
+    float *block_loss = nullptr;
+    hipError_t e = hipMallocAsync((void **)&block_loss, (nb + (tiles ? 3 * n : aside ? n : 0)) * sizeof(float), st);
     if (e != hipSuccess) return fail(CS_ENOMEM, "ssim scratch: %s", hipGetErrorString(e));
-    float *block_loss = part + part_floats;
-    hipLaunchKernelGGL(ssim_moments_kernel, grid, block, 0, st, rgb, target, a, part, block_loss);
+    float *rest = block_loss + nb; // the partials, or the gradient aside
+    if (tiles)
+        hipLaunchKernelGGL(ssim_moments_kernel, grid, dim3(SS_TILE * SS_TILE), 0, st, rgb, target, a, rest, block_loss);
+    else
+        hipLaunchKernelGGL(ssim_kernel, grid, dim3(SS_BLOCK), 0, st, rgb, target, a, aside ? rest : dl_drgb, block_loss);
     hipLaunchKernelGGL(ssim_loss_sum_kernel, dim3(1), dim3(1024), 0, st, block_loss, nb, a, loss);
-    hipLaunchKernelGGL(ssim_grad_kernel, grid, block, 0, st, rgb, target, a, part, dl_drgb);
+    if (tiles)
+        hipLaunchKernelGGL(ssim_grad_kernel, grid, dim3(SS_TILE * SS_TILE), 0, st, rgb, target, a, rest, dl_drgb);
+    else if (aside)
+        hipLaunchKernelGGL(copy_floats_kernel, dim3((unsigned)std::min<size_t>((n + 255) / 256, 4096)), dim3(256), 0, st, n,
+                           rest, dl_drgb);
     e = hipGetLastError();
-    (void)hipFreeAsync(part, st);
+    (void)hipFreeAsync(block_loss, st);
     return e == hipSuccess ? CS_OK : fail(CS_EHIP, "ssim launch: %s", hipGetErrorString(e));
 }
 

@@ -259,13 +259,26 @@ template <int TILE> __device__ __forceinline__ void tile_pixel(int &dx, int &dy)
 }
 
 
-// Can a record reach alpha >= eps_alpha at a pixel centre of the RW x RH
-// rectangle [su, su + RW - 1] x [sv, sv + RH - 1] (a wavefront's pixels)?  Its pixel box must meet the square, and no
+// The bounding rectangle, in the square, of the pixels whose lanes are in the
+// (nonempty) mask: x0 | x1 << 4 | y0 << 8 | y1 << 12.
+__device__ __forceinline__ uint32_t lanes_box(uint64_t mask)
+{
+    const uint32_t y0 = (uint32_t)__builtin_ctzll(mask) >> 3, y1 = (63u - (uint32_t)__builtin_clzll(mask)) >> 3;
+    uint32_t c = (uint32_t)mask | (uint32_t)(mask >> 32);
+    c |= c >> 16;
+    c = (c | (c >> 8)) & 0xFFu;
+    const uint32_t x0 = (uint32_t)__builtin_ctz(c), x1 = 31u - (uint32_t)__builtin_clz(c);
+    return x0 | (x1 << 4) | (y0 << 8) | (y1 << 12);
+}
+
+// Can a record reach alpha >= eps_alpha at a pixel centre of the rectangle `lb`
+// (lanes_box: of the pixels that still take convexes) of the square at (su,
+// sv)?  Its pixel box must meet the rectangle, and no
 // hull line may keep x2 above the skip threshold over all pixel centres of
-// the square's part of the box (then the pair evaluation skips every one of
+// the rectangle's part of the box (then the pair evaluation skips every one of
 // them).  A line's minimum over a rectangle is at a corner; the margin covers
 // the rounding of this test and of the pair evaluation.
-template <int K, int RW = 8, int RH = 8> __device__ __forceinline__ bool square_meets(const uint8_t *rec, int su, int sv)
+template <int K> __device__ __forceinline__ bool square_meets(const uint8_t *rec, int su, int sv, uint32_t lb)
 {
     const RecHeader h = *reinterpret_cast<const RecHeader *>(rec);
     double L[3 * K + 1];
@@ -276,8 +289,10 @@ template <int K, int RW = 8, int RH = 8> __device__ __forceinline__ bool square_
         L[2 * q] = w.x;
         L[2 * q + 1] = w.y;
     }
-    const int u0 = max(su, (int)(h.box_u & 0xFFFFu)), u1 = min(su + RW - 1, (int)(h.box_u >> 16));
-    const int v0 = max(sv, (int)(h.box_v & 0xFFFFu)), v1 = min(sv + RH - 1, (int)(h.box_v >> 16));
+    const int u0 = max(su + (int)(lb & 15u), (int)(h.box_u & 0xFFFFu));
+    const int u1 = min(su + (int)((lb >> 4) & 15u), (int)(h.box_u >> 16));
+    const int v0 = max(sv + (int)((lb >> 8) & 15u), (int)(h.box_v & 0xFFFFu));
+    const int v1 = min(sv + (int)(lb >> 12), (int)(h.box_v >> 16));
     if (u0 > u1 || v0 > v1) return false;
     const double a0 = (double)u0 + 0.5 - (double)h.ox, a1 = (double)u1 + 0.5 - (double)h.ox;
     const double c0 = (double)v0 + 0.5 - (double)h.oy, c1 = (double)v1 + 0.5 - (double)h.oy;
@@ -350,46 +365,71 @@ __device__ __forceinline__ void pipe_store_records(const u32x4 (&pre)[NL], uint4
 
 // Work distribution of the persistent compositing grid.  Items (tiles of all
 // views, in the order given by `order`, or natural order) are split into one
-// contiguous band per XCD; a workgroup takes items from the queue of its own XCD
+// contiguous band per XCD; a workgroup takes items from the band of its own XCD
 // (workgroups are dealt to the 8 XCDs round-robin), so neighbouring tiles, which
-// share convex records, meet in one L2, and steals from the other queues when
-// its own runs dry.  Every workgroup exits once all queues are empty.
-// CHUNK items are claimed per atomic (the workgroup keeps the rest of its
-// run in cnext..cend).
-template <uint32_t CHUNK>
-__device__ __forceinline__ uint32_t next_item(uint32_t *queues, uint32_t total, int &q, int &tried,
-                                              uint32_t &cnext, uint32_t &cend, uint32_t *s_item)
-{
-    if (threadIdx.x == 0) {
-        uint32_t item = 0xFFFFFFFFu;
-        if (cnext < cend) {
-            item = cnext++;
-        } else {
-            const uint32_t per = (total + NUM_QUEUES - 1) / NUM_QUEUES;
-            while (tried < NUM_QUEUES) {
-                const uint32_t lo = q * per, hi = min(total, lo + per);
-                if (lo < hi) {
-                    const uint32_t k = atomicAdd(&queues[QUEUE_STRIDE * q], CHUNK);
-                    if (lo + k < hi) {
-                        item = lo + k;
-                        cnext = item + 1;
-                        cend = min(hi, item + CHUNK);
-                        break;
-                    }
-                }
+// share convex records, meet in one L2, and steals from the other bands when
+// its own runs dry.  Every workgroup exits once all bands are through.
+// CHUNK items are claimed at once (the workgroup keeps the rest of its run in
+// cnext..cend).  A claim's round trip is a microsecond or two: a workgroup's
+// first items are its own by its index, without a claim, and a band whose items
+// are all given out that way is not claimed from (a 128 x 128 view of one convex:
+// 20 -> 11 us).  A claim made ahead, while the last item is worked on, is no gain: it ties an
+// item to a workgroup that may be long busy (100k convexes at 1297 x 840: 0.102
+// -> 0.139 ms).
+template <uint32_t CHUNK> struct Claims {
+    uint32_t *queues;
+    uint32_t total;
+    int q, tried;         // the band that items are taken from, bands found dry
+    bool first;
+    uint32_t cnext, cend;
+
+    __device__ __forceinline__ Claims(uint32_t *queues_, uint32_t total_)
+        : queues(queues_), total(total_), q(blockIdx.x % NUM_QUEUES), tried(0), first(true), cnext(0), cend(0)
+    {
+    }
+    __device__ __forceinline__ uint32_t per() const { return (total + NUM_QUEUES - 1) / NUM_QUEUES; }
+    __device__ __forceinline__ uint32_t lo(int b) const { return min(total, (uint32_t)b * per()); }
+    __device__ __forceinline__ uint32_t size(int b) const { return min(total, ((uint32_t)b + 1u) * per()) - lo(b); }
+    // items of a band that belong to workgroups by their index
+    __device__ __forceinline__ uint32_t given(int b) const
+    {
+        return CHUNK * ((gridDim.x + (uint32_t)(NUM_QUEUES - 1 - b)) / NUM_QUEUES);
+    }
+    __device__ __forceinline__ bool take(uint32_t k) // item k of band q
+    {
+        if (k >= size(q)) return false;
+        cnext = lo(q) + k;
+        cend = lo(q) + min(size(q), k + CHUNK);
+        return true;
+    }
+    // thread 0 only
+    __device__ __forceinline__ uint32_t one()
+    {
+        if (cnext < cend) return cnext++;
+        bool got = first && take(CHUNK * (blockIdx.x / NUM_QUEUES));
+        first = false;
+        while (!got && tried < NUM_QUEUES) {
+            if (given(q) < size(q)) got = take(given(q) + atomicAdd(&queues[QUEUE_STRIDE * q], CHUNK));
+            if (!got) {
                 q = (q + 1) % NUM_QUEUES;
                 ++tried;
             }
         }
-        *s_item = item;
+        if (!got) return 0xFFFFFFFFu;
+        return cnext++;
     }
-    __syncthreads();
-    // a scalar: what hangs on the item (view, cell, list, image size) then stays
-    // in scalar registers
-    const uint32_t item = (uint32_t)__builtin_amdgcn_readfirstlane((int)*s_item);
-    __syncthreads();
-    return item;
-}
+    // The next item, for the whole workgroup (0xFFFFFFFF: none left).
+    __device__ __forceinline__ uint32_t next(uint32_t *s_item)
+    {
+        if (threadIdx.x == 0) *s_item = one();
+        __syncthreads();
+        // a scalar: what hangs on the item (view, cell, list, image size) then stays
+        // in scalar registers
+        const uint32_t item = (uint32_t)__builtin_amdgcn_readfirstlane((int)*s_item);
+        __syncthreads();
+        return item;
+    }
+};
 
 // A tile's depth-ordered convex list, streamed out of its cell's list into a
 // ring in LDS that the batches of records are taken from.  A round reads the
@@ -547,8 +587,7 @@ __global__ __launch_bounds__(TILE *TILE) __attribute__((amdgpu_waves_per_eu(fwd_
     const ViewDesc *views = reinterpret_cast<const ViewDesc *>(frame + 1);
     const int nviews = (int)frame->nviews;
     const uint32_t total_tiles = frame->total_tiles;
-    int q = blockIdx.x % NUM_QUEUES, tried = 0;
-    uint32_t cnext = 0, cend = 0;
+    Claims<FWD_CHUNK> claims(queues, total_tiles);
     // work counters: pairs tested / pairs past the max-line test (the hull
     // sizes and wavefront evaluations of the same pairs are counted by the
     // backward walk, where they cost less)
@@ -557,7 +596,7 @@ __global__ __launch_bounds__(TILE *TILE) __attribute__((amdgpu_waves_per_eu(fwd_
     // here, one slice per tile item, by stores that overlap the compositing
     const uint32_t zper = total_tiles ? (zero_n4 + total_tiles - 1) / total_tiles : 0u;
     for (;;) {
-        const uint32_t item = next_item<FWD_CHUNK>(queues, total_tiles, q, tried, cnext, cend, &s_item);
+        const uint32_t item = claims.next(&s_item);
         if (item == 0xFFFFFFFFu) break;
         if (zper) {
             const uint32_t z0 = min(item * zper, zero_n4), z1 = min(z0 + zper, zero_n4);
@@ -609,8 +648,9 @@ __global__ __launch_bounds__(TILE *TILE) __attribute__((amdgpu_waves_per_eu(fwd_
             // the wave's square), front to back in a wave-uniform walk
             uint64_t M = 0;
             int last = -1; // the pixel's last contributor of this batch
-            if (!__all(done)) {
-                const bool meets = lane < cnt && square_meets<K>(reinterpret_cast<const uint8_t *>(&lds[min(lane, BATCH - 1) * CH]), su, sv);
+            if (const uint64_t live = __ballot(!done)) {
+                const bool meets = lane < cnt && square_meets<K>(reinterpret_cast<const uint8_t *>(&lds[min(lane, BATCH - 1) * CH]),
+                                                                 su, sv, lanes_box(live));
                 M = __ballot(meets);
             }
             while (M) {
@@ -686,18 +726,31 @@ struct BwdPixel {
     bool first;
 };
 
-// A pixel's compact gradient values of one record (see bwd_values), stored
-// into val (ADD: added to it), and the pixel's walk advanced past the record.
-template <int K, int NL, bool ADD>
-__device__ __forceinline__ void pixel_values(const RecHeader &h, const PairEval<K> &pe, bool contrib, BwdPixel &P,
-                                             float pxf, float pyf, float *val)
+// The pixel's transmittance before a contributing record (0 for a lane that does
+// not contribute: it zeroes all of its values) and dL/dalpha.
+__device__ __forceinline__ float pixel_before(const BwdPixel &P, bool contrib, float oma)
 {
-    // branch-free: a lane that does not contribute takes Tn = 0, which zeroes
-    // all of its values (every pe field is finite)
-    const float Tn = contrib ? (P.first ? P.Tlast : P.Tcur * __builtin_amdgcn_rcpf(pe.oma)) : 0.0f;
-    const float dLda = Tn * (P.g0 * (h.rgb[0] - P.B0) + P.g1 * (h.rgb[1] - P.B1) + P.g2 * (h.rgb[2] - P.B2));
+    return contrib ? (P.first ? P.Tlast : P.Tcur * __builtin_amdgcn_rcpf(oma)) : 0.0f;
+}
+__device__ __forceinline__ float pixel_dalpha(const BwdPixel &P, const float *rgb, float Tn)
+{
+    return Tn * (P.g0 * (rgb[0] - P.B0) + P.g1 * (rgb[1] - P.B1) + P.g2 * (rgb[2] - P.B2));
+}
+// The pixel's walk advanced past a contributing record.
+__device__ __forceinline__ void pixel_pass(BwdPixel &P, const float *rgb, float Tn, float alpha, float oma)
+{
+    P.first = false;
+    P.Tcur = Tn;
+    P.B0 = fmaf(alpha, rgb[0], oma * P.B0);
+    P.B1 = fmaf(alpha, rgb[1], oma * P.B1);
+    P.B2 = fmaf(alpha, rgb[2], oma * P.B2);
+}
+// A pixel's compact gradient values of one record (see bwd_values), stored into v.
+template <int K, int NL>
+__device__ __forceinline__ void pair_values(const RecHeader &h, const PairEval<K> &pe, const BwdPixel &P, float Tn, float dLda,
+                                            float pxf, float pyf, float *v)
+{
     const float ta = Tn * pe.alpha;
-    float v[bwd_values<NL>()];
     v[3 * NL + 2] = P.g0 * ta;
     v[3 * NL + 3] = P.g1 * ta;
     v[3 * NL + 4] = P.g2 * ta;
@@ -718,33 +771,14 @@ __device__ __forceinline__ void pixel_values(const RecHeader &h, const PairEval<
     }
     v[3 * NL + 5] = gdl;
 #pragma unroll
-    for (int qv = 0; qv < bwd_values<NL>(); ++qv) val[qv] = ADD ? val[qv] + v[qv] : v[qv];
-    if (contrib) {
-        P.first = false;
-        P.Tcur = Tn;
-        P.B0 = fmaf(pe.alpha, h.rgb[0], pe.oma * P.B0);
-        P.B1 = fmaf(pe.alpha, h.rgb[1], pe.oma * P.B1);
-        P.B2 = fmaf(pe.alpha, h.rgb[2], pe.oma * P.B2);
-    }
+    for (int qv = bwd_values<NL>(); qv < bwd_padded<NL>(); ++qv) v[qv] = 0.0f;
 }
-
-template <int K, int NL>
-__device__ __forceinline__ void bwd_record(const uint8_t *rec, bool live, int u, int y, float pxf, float pyf,
-                                           float eps, BwdPixel &P, float *slot, bool &full)
+// The wavefront's sums of a record's values, added to its LDS slot: whole-wave
+// sums even when few lanes contribute (lane-by-lane LDS atomics serialise badly
+// when a record covers the square).
+template <int NP> __device__ __forceinline__ void add_wave_sums(float *val, float *slot)
 {
-    constexpr int NP = bwd_padded<NL>();
     constexpr int Q = NP / 4;
-    PairEval<K> pe;
-    bool tested;
-    const bool contrib = eval_pair<K, NL>(rec, live, u, y, pxf, pyf, eps, pe, tested, full);
-    if (__ballot(contrib) == 0ull) return; // wave-uniform
-    const RecHeader &h = *reinterpret_cast<const RecHeader *>(rec);
-    float val[NP];
-    pixel_values<K, NL, false>(h, pe, contrib, P, pxf, pyf, val);
-#pragma unroll
-    for (int qv = bwd_values<NL>(); qv < NP; ++qv) val[qv] = 0.0f;
-    // whole-wave sums even when few lanes contribute: lane-by-lane LDS atomics
-    // serialise badly when a record covers the square
     wave_to_rows<NP>(val);
     const float total = row_reduce<Q>(val);
     const int li = threadIdx.x & 15;
@@ -752,6 +786,23 @@ __device__ __forceinline__ void bwd_record(const uint8_t *rec, bool live, int u,
         const int qv = (int)((rr_map(Q) >> (4 * li)) & 15u);
         atomicAdd(slot + ((threadIdx.x & 63) >> 4) * Q + qv, total);
     }
+}
+
+template <int K, int NL>
+__device__ __forceinline__ void bwd_record(const uint8_t *rec, bool live, int u, int y, float pxf, float pyf,
+                                           float eps, BwdPixel &P, float *slot, bool &full)
+{
+    PairEval<K> pe;
+    bool tested;
+    const bool contrib = eval_pair<K, NL>(rec, live, u, y, pxf, pyf, eps, pe, tested, full);
+    if (__ballot(contrib) == 0ull) return; // wave-uniform
+    const RecHeader &h = *reinterpret_cast<const RecHeader *>(rec);
+    // branch-free: every pe field is finite
+    const float Tn = pixel_before(P, contrib, pe.oma);
+    float val[bwd_padded<NL>()];
+    pair_values<K, NL>(h, pe, P, Tn, pixel_dalpha(P, h.rgb, Tn), pxf, pyf, val);
+    if (contrib) pixel_pass(P, h.rgb, Tn, pe.alpha, pe.oma);
+    add_wave_sums<bwd_padded<NL>()>(val, slot);
 }
 
 template <int K, int TILE, int BATCH>
@@ -783,12 +834,11 @@ __global__ __launch_bounds__(TILE *TILE) __attribute__((amdgpu_waves_per_eu(K <=
     const int nviews = (int)frame->nviews;
     const uint32_t total_tiles = frame->total_tiles;
     const int lane = threadIdx.x & 63, wbit = threadIdx.x >> 6;
-    int q = blockIdx.x % NUM_QUEUES, tried = 0;
-    uint32_t cnext = 0, cend = 0;
+    Claims<1> claims(queues, total_tiles);
     uint32_t nfull = 0, nsumT = 0, nwave = 0;
     TileFeed<NT, RING, true> feed;
     for (;;) {
-        const uint32_t item = next_item<1>(queues, total_tiles, q, tried, cnext, cend, &s_item);
+        const uint32_t item = claims.next(&s_item);
         if (item == 0xFFFFFFFFu) break;
         const int gt = order ? (int)order[item] : (int)item;
         const int v = find_view(views, nviews, gt);
@@ -857,7 +907,9 @@ __global__ __launch_bounds__(TILE *TILE) __attribute__((amdgpu_waves_per_eu(K <=
             const int mine_e = min(lane, cnt - 1);
             const uint8_t *mine = reinterpret_cast<const uint8_t *>(&lds[mine_e * CH]);
             const int mypos = (int)s_ring[(head + (uint32_t)mine_e) & (RING - 1)].y; // lane e: list position of entry e
-            const bool meets = lane < cnt && mypos < wmaxn && square_meets<K>(mine, su, sv);
+            // (of the pixels whose last contributor is not before the batch's last entry)
+            const uint64_t live = __ballot(nend > __builtin_amdgcn_readlane(mypos, cnt - 1));
+            const bool meets = live != 0ull && lane < cnt && mypos < wmaxn && square_meets<K>(mine, su, sv, lanes_box(live));
             const int myT = reinterpret_cast<const RecHeader *>(mine)->T; // lane e: hull size of entry e
             uint64_t M = __ballot(meets);
             while (M) {
@@ -883,6 +935,334 @@ __global__ __launch_bounds__(TILE *TILE) __attribute__((amdgpu_waves_per_eu(K <=
                     const int T = reinterpret_cast<const RecHeader *>(&lds[e * CH])->T;
                     unsafeAtomicAdd(&acc[(size_t)s_ring[(head + (uint32_t)e) & (RING - 1)].x * AS + acc_slot<K>(qv, T)], a);
                     *src = 0.0f;
+                }
+            }
+        }
+    }
+    if (evalcount) store_work_counts(evalcount, s_ev, 0u, nfull, nsumT, nwave);
+}
+
+// ---------------------------------------------- compositing, split by record
+//
+// A wavefront walks its square's records one after another, 0.4 us each in the
+// forward when it has a SIMD to itself, so a small view takes as long as its
+// longest walk however many CUs are idle.  What takes the time, evaluating a
+// record's alpha at the pixels, does not depend on the records before it: here a
+// workgroup of four wavefronts takes one 8 x 8 square, each evaluates two of the
+// next SPLIT records (both at once, one's latencies behind the other's), passes
+// alpha and 1 - alpha through LDS, and all four composite the SPLIT records in
+// order, each for itself (the same operations on the same values: the image and
+// the walk's decisions are the other kernels' bit for bit).  The backward does
+// the same: alphas by record, T_n and the colour behind in order by every
+// wavefront, then each forms and sums the gradient values of its two records.
+// This costs about half as much again in instructions, and a record is loaded
+// and tested for every square instead of every tile, so it is for views whose
+// squares do not fill the chip (split_squares below).
+constexpr int SPLIT = 8;
+constexpr float NOT_FULL = -1.0f, NOT_TESTED = -2.0f; // in place of alpha
+
+// The square of a work item: tile gt, square (sx, sy) of it.
+struct SquareItem { int gt, sx, sy; };
+__device__ __forceinline__ SquareItem square_item(uint32_t item, const uint32_t *order, uint32_t side)
+{
+    const uint32_t per = side * side, t = item / per, s = item - t * per;
+    return {order ? __builtin_amdgcn_readfirstlane((int)order[t]) : (int)t, (int)(s % side), (int)(s / side)};
+}
+// The set of M without its i lowest members.
+__device__ __forceinline__ uint64_t drop_lowest(uint64_t M, int i)
+{
+    for (; i > 0; --i) M &= M - 1;
+    return M;
+}
+
+template <int K>
+__global__ __launch_bounds__(256) void render_fwd_split_kernel(
+    const FrameHeader *__restrict__ frame, const uint32_t *__restrict__ order, uint32_t *__restrict__ queues,
+    const uint2 *__restrict__ ranges, const uint32_t *__restrict__ keys, const uint32_t *__restrict__ ids,
+    const uint8_t *__restrict__ records, RenderArgs ra, uint2 *__restrict__ pixstate,
+    unsigned long long *__restrict__ evalcount, u32x4 *__restrict__ zero_acc, uint32_t zero_n4)
+{
+    constexpr int NT = 256, BATCH = 64, RING = feed_ring<NT>(), WANT = RING - NT - BATCH;
+    constexpr int CH = rec_stride(K) / 16, NL = pipe_regs<K, NT, BATCH>();
+    __shared__ uint4 lds[BATCH * CH];
+    __shared__ uint2 s_ring[RING];
+    __shared__ uint32_t s_cnt[FEED_SUB][NT / 64];
+    __shared__ float2 s_ab[2][SPLIT][64]; // alpha (or why there is none) and 1 - alpha by record and pixel
+    __shared__ uint32_t s_item;
+    __shared__ unsigned long long s_ev[EVAL_FIELDS];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    if (threadIdx.x < EVAL_FIELDS) s_ev[threadIdx.x] = 0ull;
+    u32x4 pre[NL];
+    TileFeed<NT, RING, false> feed;
+    const ViewDesc *views = reinterpret_cast<const ViewDesc *>(frame + 1);
+    const int nviews = (int)frame->nviews;
+    const uint32_t side = (uint32_t)ra.tile / 8u, total = frame->total_tiles * side * side;
+    Claims<1> claims(queues, total);
+    uint32_t nevals = 0, nfull = 0;
+    const uint32_t zper = total ? (zero_n4 + total - 1) / total : 0u;
+    int buf = 0;
+    for (;;) {
+        const uint32_t item = claims.next(&s_item);
+        if (item == 0xFFFFFFFFu) break;
+        if (zper) {
+            const uint32_t z0 = min(item * zper, zero_n4), z1 = min(z0 + zper, zero_n4);
+            for (uint32_t z = z0 + threadIdx.x; z < z1; z += NT) zero_acc[z] = u32x4{0u, 0u, 0u, 0u};
+        }
+        const SquareItem it = square_item(item, order, side);
+        const ViewDesc &vd = views[find_view(views, nviews, it.gt)];
+        const int lt = it.gt - vd.tile_off, tx = lt % vd.tiles_x, ty = lt / vd.tiles_x;
+        const int W = vd.cam.W, H = vd.cam.H;
+        const int su = tx * ra.tile + 8 * it.sx, sv = ty * ra.tile + 8 * it.sy;
+        if (su >= W || sv >= H) continue; // a square past the image's edge
+        const int u = su + (lane & 7), y = sv + (lane >> 3);
+        const bool inside = u < W && y < H;
+        const float pxf = (float)u + 0.5f, pyf = (float)y + 0.5f;
+        const uint2 rg = ranges[tile_cell(vd, (uint32_t)tx, (uint32_t)ty)];
+        const uint32_t hitmask = tile_bit(vd, frame->key_bits, (uint32_t)tx, (uint32_t)ty);
+
+        float T = 1.0f, C0 = 0.0f, C1 = 0.0f, C2 = 0.0f, Tlast = 1.0f;
+        uint32_t nend = 0;
+        bool done = !inside;
+        int cnt = 0;
+        if (rg.y > rg.x) {
+            feed.start(keys + rg.x, ids + rg.x, (int)(rg.y - rg.x), hitmask);
+            feed.fill(2 * BATCH, s_cnt, s_ring);
+            feed.request();
+            cnt = min(BATCH, feed.queued());
+            if (cnt > 0) pipe_load_records<K, NT, NL>(pre, s_ring, feed.head, RING - 1, records, cnt);
+        }
+        while (cnt > 0) {
+            pipe_store_records<K, NT, NL>(pre, lds, cnt);
+            const bool refill = feed.queued() <= RING - NT && feed.more();
+            if (refill) feed.publish(s_cnt);
+            __syncthreads();
+            const uint32_t head = feed.head;
+            feed.head += (uint32_t)cnt;
+            const int ncnt = feed.queued() >= BATCH / 2 || !feed.more() ? min(BATCH, feed.queued()) : 0;
+            if (refill) {
+                feed.append(feed.k0, feed.v0, true, opaque_tid(), s_cnt[0], s_ring);
+                feed.request();
+            }
+            if (ncnt > 0) pipe_load_records<K, NT, NL>(pre, s_ring, feed.head, RING - 1, records, ncnt);
+            uint64_t M = 0;
+            if (const uint64_t live = __ballot(!done))
+                M = __ballot(lane < cnt && square_meets<K>(reinterpret_cast<const uint8_t *>(&lds[min(lane, BATCH - 1) * CH]), su, sv,
+                                                           lanes_box(live)));
+            int last = -1;
+            while (M && !__all(done)) {
+                // the next SPLIT records: this wavefront's two, evaluated together
+                uint64_t mine = drop_lowest(M, 2 * wave);
+                if (mine) {
+                    const int e0 = __builtin_ctzll(mine);
+                    mine &= mine - 1;
+                    const int e1 = mine ? __builtin_ctzll(mine) : e0;
+                    PairEval<K> p0, p1;
+                    bool t0, f0, t1, f1;
+                    p0.alpha = p0.oma = p1.alpha = p1.oma = 0.0f;
+                    eval_pair<K, K>(reinterpret_cast<const uint8_t *>(&lds[e0 * CH]), !done, u, y, pxf, pyf, ra.eps_alpha, p0, t0, f0);
+                    eval_pair<K, K>(reinterpret_cast<const uint8_t *>(&lds[e1 * CH]), !done, u, y, pxf, pyf, ra.eps_alpha, p1, t1, f1);
+                    s_ab[buf][2 * wave][lane] = make_float2(f0 ? p0.alpha : t0 ? NOT_FULL : NOT_TESTED, p0.oma);
+                    s_ab[buf][2 * wave + 1][lane] = make_float2(f1 ? p1.alpha : t1 ? NOT_FULL : NOT_TESTED, p1.oma);
+                }
+                __syncthreads();
+#pragma unroll
+                for (int j = 0; j < SPLIT; ++j) {
+                    if (M == 0) break;
+                    const int e = __builtin_ctzll(M);
+                    M &= M - 1;
+                    const float2 ab = s_ab[buf][j][lane];
+                    const RecHeader &h = *reinterpret_cast<const RecHeader *>(&lds[e * CH]);
+                    const float c0 = h.rgb[0], c1 = h.rgb[1], c2 = h.rgb[2];
+                    const bool tested = !done && ab.x != NOT_TESTED, full = tested && ab.x != NOT_FULL;
+                    nevals += tested;
+                    nfull += full;
+                    if (full && !(ab.x < ra.eps_alpha)) {
+                        const float w = T * ab.x;
+                        C0 = fmaf(w, c0, C0);
+                        C1 = fmaf(w, c1, C1);
+                        C2 = fmaf(w, c2, C2);
+                        Tlast = T;
+                        T = T * ab.y;
+                        last = e;
+                        done = T < ra.t_min;
+                    }
+                }
+                buf ^= 1; // (a wavefront two steps ahead would wait at the barrier between)
+            }
+            if (last >= 0) nend = s_ring[(head + (uint32_t)last) & (RING - 1)].y + 1u;
+            if (__syncthreads_and(done)) break;
+            cnt = ncnt;
+            if (cnt == 0 && feed.queued() < BATCH && feed.more()) {
+                feed.fill(WANT, s_cnt, s_ring);
+                feed.request();
+            }
+            if (cnt == 0) {
+                cnt = min(BATCH, feed.queued());
+                if (cnt > 0) pipe_load_records<K, NT, NL>(pre, s_ring, feed.head, RING - 1, records, cnt);
+            }
+        }
+        if (inside && wave == 0) {
+            const size_t pix = (size_t)y * W + u;
+            float *o = vd.out_rgb + 3 * pix;
+            o[0] = fmaf(T, ra.bg[0], C0);
+            o[1] = fmaf(T, ra.bg[1], C1);
+            o[2] = fmaf(T, ra.bg[2], C2);
+            pixstate[vd.pix_off + pix] = make_uint2(nend, __float_as_uint(Tlast));
+        }
+    }
+    // every wavefront walked the same pairs: one counts them
+    if (wave != 0) nevals = nfull = 0;
+    if (evalcount) store_work_counts(evalcount, s_ev, nevals, nfull, 0u, 0u);
+}
+
+template <int K>
+__global__ __launch_bounds__(256) void render_bwd_split_kernel(
+    const FrameHeader *__restrict__ frame, const uint32_t *__restrict__ order, uint32_t *__restrict__ queues,
+    const uint2 *__restrict__ ranges, const uint32_t *__restrict__ keys, const uint32_t *__restrict__ ids,
+    const uint8_t *__restrict__ records, RenderArgs ra, const uint2 *__restrict__ pixstate,
+    float *__restrict__ acc, unsigned long long *__restrict__ evalcount)
+{
+    constexpr int NT = 256, BATCH = 64, RING = feed_ring<NT>(), WANT = RING - NT - BATCH;
+    constexpr int CH = rec_stride(K) / 16, AS = acc_stride(K), NP = bwd_padded<K>();
+    __shared__ uint4 lds[BATCH * CH];
+    __shared__ uint2 s_ring[RING];
+    __shared__ uint32_t s_cnt[FEED_SUB][NT / 64];
+    __shared__ float s_acc[BATCH * NP];
+    __shared__ float2 s_ab[2][SPLIT][64]; // alpha (NOT_FULL: no contribution) and 1 - alpha
+    __shared__ uint32_t s_item;
+    __shared__ unsigned long long s_ev[EVAL_FIELDS];
+    for (int c = threadIdx.x; c < BATCH * NP; c += NT) s_acc[c] = 0.0f;
+    if (threadIdx.x < EVAL_FIELDS) s_ev[threadIdx.x] = 0ull;
+    const ViewDesc *views = reinterpret_cast<const ViewDesc *>(frame + 1);
+    const int nviews = (int)frame->nviews;
+    const uint32_t side = (uint32_t)ra.tile / 8u, total = frame->total_tiles * side * side;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    Claims<1> claims(queues, total);
+    uint32_t nfull = 0, nsumT = 0, nwave = 0;
+    TileFeed<NT, RING, true> feed;
+    int buf = 0;
+    for (;;) {
+        const uint32_t item = claims.next(&s_item);
+        if (item == 0xFFFFFFFFu) break;
+        const SquareItem it = square_item(item, order, side);
+        const ViewDesc &vd = views[find_view(views, nviews, it.gt)];
+        const int lt = it.gt - vd.tile_off, tx = lt % vd.tiles_x, ty = lt / vd.tiles_x;
+        const int W = vd.cam.W, H = vd.cam.H;
+        const int su = tx * ra.tile + 8 * it.sx, sv = ty * ra.tile + 8 * it.sy;
+        if (su >= W || sv >= H) continue;
+        const int u = su + (lane & 7), y = sv + (lane >> 3);
+        const bool inside = u < W && y < H;
+        const float pxf = (float)u + 0.5f, pyf = (float)y + 0.5f;
+        const uint2 rg = ranges[tile_cell(vd, (uint32_t)tx, (uint32_t)ty)];
+        const uint32_t hitmask = tile_bit(vd, frame->key_bits, (uint32_t)tx, (uint32_t)ty);
+
+        BwdPixel P{0.f, 0.f, 0.f, 1.f, 1.f, ra.bg[0], ra.bg[1], ra.bg[2], true};
+        int nend = 0;
+        if (inside) {
+            const size_t pix = (size_t)y * W + u;
+            const float *g = vd.dl_drgb + 3 * pix;
+            P.g0 = g[0];
+            P.g1 = g[1];
+            P.g2 = g[2];
+            const uint2 ps = pixstate[vd.pix_off + pix];
+            nend = (int)ps.x;
+            P.Tlast = __uint_as_float(ps.y);
+            P.Tcur = P.Tlast;
+        }
+        int wmaxn = nend; // the square's last contributor
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) wmaxn = max(wmaxn, __shfl_xor(wmaxn, o, 64));
+        const int maxn = min(__builtin_amdgcn_readfirstlane(wmaxn), (int)(rg.y - rg.x));
+        if (maxn > 0) {
+            feed.start(keys + rg.x, ids + rg.x, maxn, hitmask);
+            feed.request();
+        }
+        while (maxn > 0) {
+            __syncthreads(); // the previous batch's records are flushed
+            if (feed.queued() < BATCH && feed.more()) {
+                feed.fill(2 * BATCH, s_cnt, s_ring);
+                feed.request();
+            }
+            const int cnt = min(BATCH, feed.queued());
+            if (cnt == 0) break;
+            load_records_direct<K, NT>(lds, s_ring, feed.head, RING - 1, records, cnt);
+            const bool refill = feed.queued() <= RING - NT && feed.more();
+            if (refill) feed.publish(s_cnt);
+            __syncthreads();
+            const uint32_t head = feed.head;
+            feed.head += (uint32_t)cnt;
+            if (refill) {
+                feed.append(feed.k0, feed.v0, true, opaque_tid(), s_cnt[0], s_ring);
+                feed.request();
+            }
+            const int mine_e = min(lane, cnt - 1);
+            const uint8_t *mine_r = reinterpret_cast<const uint8_t *>(&lds[mine_e * CH]);
+            const int mypos = (int)s_ring[(head + (uint32_t)mine_e) & (RING - 1)].y; // lane e: list position of entry e
+            const int myT = reinterpret_cast<const RecHeader *>(mine_r)->T;
+            const uint64_t live = __ballot(nend > __builtin_amdgcn_readlane(mypos, cnt - 1));
+            uint64_t M = 0;
+            if (live) M = __ballot(lane < cnt && square_meets<K>(mine_r, su, sv, lanes_box(live)));
+            while (M) {
+                uint64_t mine = drop_lowest(M, 2 * wave);
+                const bool some = mine != 0ull, both = (mine & (mine - 1)) != 0ull;
+                int e0 = 0, e1 = 0;
+                PairEval<K> p0, p1;
+                bool c0 = false, c1 = false;
+                if (some) {
+                    e0 = __builtin_ctzll(mine);
+                    mine &= mine - 1;
+                    e1 = both ? __builtin_ctzll(mine) : e0;
+                    bool tested, f0, f1;
+                    c0 = eval_pair<K, K>(reinterpret_cast<const uint8_t *>(&lds[e0 * CH]),
+                                         __builtin_amdgcn_readlane(mypos, e0) < nend, u, y, pxf, pyf, ra.eps_alpha, p0, tested, f0);
+                    c1 = eval_pair<K, K>(reinterpret_cast<const uint8_t *>(&lds[e1 * CH]),
+                                         both && __builtin_amdgcn_readlane(mypos, e1) < nend, u, y, pxf, pyf, ra.eps_alpha, p1, tested, f1);
+                    s_ab[buf][2 * wave][lane] = c0 ? make_float2(p0.alpha, p0.oma) : make_float2(NOT_FULL, 1.0f);
+                    s_ab[buf][2 * wave + 1][lane] = c1 ? make_float2(p1.alpha, p1.oma) : make_float2(NOT_FULL, 1.0f);
+                    const uint32_t T0 = (uint32_t)__builtin_amdgcn_readlane(myT, e0), T1 = (uint32_t)__builtin_amdgcn_readlane(myT, e1);
+                    nfull += (f0 ? 1u : 0u) + (f1 ? 1u : 0u);
+                    nsumT += (f0 ? T0 : 0u) + (f1 ? T1 : 0u);
+                    nwave += (__any(f0) ? 1u : 0u) + (__any(f1) ? 1u : 0u);
+                }
+                __syncthreads();
+                // in order: T_n and dL/dalpha of this wavefront's records
+                float Tn0 = 0.0f, Tn1 = 0.0f, da0 = 0.0f, da1 = 0.0f;
+#pragma unroll
+                for (int j = 0; j < SPLIT; ++j) {
+                    if (M == 0) break;
+                    const int e = __builtin_ctzll(M);
+                    M &= M - 1;
+                    const float2 ab = s_ab[buf][j][lane];
+                    const RecHeader &h = *reinterpret_cast<const RecHeader *>(&lds[e * CH]);
+                    const float rgb[3] = {h.rgb[0], h.rgb[1], h.rgb[2]};
+                    const bool contrib = ab.x != NOT_FULL;
+                    const float Tn = pixel_before(P, contrib, ab.y);
+                    if (j / 2 == wave) {
+                        const float da = pixel_dalpha(P, rgb, Tn);
+                        if (j % 2) { Tn1 = Tn; da1 = da; }
+                        else { Tn0 = Tn; da0 = da; }
+                    }
+                    if (contrib) pixel_pass(P, rgb, Tn, ab.x, ab.y);
+                }
+                buf ^= 1;
+                // their gradient values (null lines past T give zeros)
+                float val[NP];
+                if (__any(c0)) {
+                    pair_values<K, K>(*reinterpret_cast<const RecHeader *>(&lds[e0 * CH]), p0, P, Tn0, da0, pxf, pyf, val);
+                    add_wave_sums<NP>(val, &s_acc[e0 * NP]);
+                }
+                if (__any(c1)) {
+                    pair_values<K, K>(*reinterpret_cast<const RecHeader *>(&lds[e1 * CH]), p1, P, Tn1, da1, pxf, pyf, val);
+                    add_wave_sums<NP>(val, &s_acc[e1 * NP]);
+                }
+            }
+            __syncthreads();
+            for (int c = opaque_tid(); c < cnt * NP; c += NT) {
+                const int e = c / NP, qv = c - e * NP;
+                const float a = s_acc[c];
+                if (a != 0.0f) {
+                    unsafeAtomicAdd(&acc[(size_t)s_ring[(head + (uint32_t)e) & (RING - 1)].x * AS + acc_slot<K>(qv, K)], a);
+                    s_acc[c] = 0.0f;
                 }
             }
         }
@@ -930,45 +1310,66 @@ template <class F> int persistent_grid(F kernel, int threads)
     cache[key] = g;
     return g;
 }
+int split_grid(int resident, uint32_t max_items, int tile)
+{
+    const uint64_t squares = (uint64_t)max_items * (uint64_t)(tile / 8) * (uint64_t)(tile / 8);
+    return (int)std::min<uint64_t>({(uint64_t)resident, squares, (uint64_t)EVAL_SLOTS});
+}
 } // namespace
 
-// max_items bounds the grid (a persistent grid larger than the work only idles).
-// Returns the grid size (the number of evalcount slots written).
+// max_items bounds the grid (a persistent grid larger than the work only idles);
+// split: by squares with the records split over wavefronts.  Returns the grid
+// size (the number of evalcount slots written).
 int launch_render_fwd(hipStream_t st, int K, int tile, const FrameHeader *frame, const uint32_t *order,
                       uint32_t max_items, uint32_t *queues, const uint2 *ranges, const uint32_t *keys,
-                      const uint32_t *ids, const uint8_t *records, const RenderArgs &ra, uint2 *pixstate, unsigned long long *evalcount,
-                      float *zero_acc, size_t zero_floats)
+                      const uint32_t *ids, const uint8_t *records, const RenderArgs &ra, uint2 *pixstate,
+                      unsigned long long *evalcount, float *zero_acc, size_t zero_floats, bool split)
 {
     // the accumulator rows are whole 16-byte words (acc_stride is a multiple of 4)
     u32x4 *z4 = reinterpret_cast<u32x4 *>(zero_acc);
     const uint32_t n4 = zero_acc ? (uint32_t)(zero_floats / 4) : 0u;
     if (max_items == 0) return 0;
     int used = 0;
-    CS_DISPATCH_K(K, CS_DISPATCH_TILE(tile, {
-        auto kern = render_fwd_kernel<KK, TT, BF>;
-        const int grid = std::min({persistent_grid(kern, TT * TT), (int)max_items, EVAL_SLOTS});
-        hipLaunchKernelGGL(kern, dim3(grid), dim3(TT * TT), 0, st, frame, order, queues, ranges, keys, ids, records, ra,
-                           pixstate, evalcount, z4, n4);
-        used = grid;
-    }));
+    if (split) {
+        CS_DISPATCH_K(K, {
+            auto kern = render_fwd_split_kernel<KK>;
+            used = split_grid(persistent_grid(kern, 256), max_items, tile);
+            hipLaunchKernelGGL(kern, dim3(used), dim3(256), 0, st, frame, order, queues, ranges, keys, ids, records, ra,
+                               pixstate, evalcount, z4, n4);
+        });
+    } else {
+        CS_DISPATCH_K(K, CS_DISPATCH_TILE(tile, {
+            auto kern = render_fwd_kernel<KK, TT, BF>;
+            used = std::min({persistent_grid(kern, TT * TT), (int)max_items, EVAL_SLOTS});
+            hipLaunchKernelGGL(kern, dim3(used), dim3(TT * TT), 0, st, frame, order, queues, ranges, keys, ids, records, ra,
+                               pixstate, evalcount, z4, n4);
+        }));
+    }
     return used;
 }
 
-// Returns the grid size (the number of evalcount slots written).
 int launch_render_bwd(hipStream_t st, int K, int tile, const FrameHeader *frame, const uint32_t *order,
                       uint32_t max_items, uint32_t *queues, const uint2 *ranges, const uint32_t *keys,
                       const uint32_t *ids, const uint8_t *records, const RenderArgs &ra, const uint2 *pixstate, float *acc,
-                      unsigned long long *evalcount)
+                      unsigned long long *evalcount, bool split)
 {
     if (max_items == 0) return 0;
     int used = 0;
-    CS_DISPATCH_K(K, CS_DISPATCH_TILE(tile, {
-        auto kern = render_bwd_kernel<KK, TT, BBW>;
-        const int grid = std::min({persistent_grid(kern, TT * TT), (int)max_items, EVAL_SLOTS});
-        hipLaunchKernelGGL(kern, dim3(grid), dim3(TT * TT), 0, st, frame, order, queues, ranges, keys, ids, records, ra,
-                           pixstate, acc, evalcount);
-        used = grid;
-    }));
+    if (split) {
+        CS_DISPATCH_K(K, {
+            auto kern = render_bwd_split_kernel<KK>;
+            used = split_grid(persistent_grid(kern, 256), max_items, tile);
+            hipLaunchKernelGGL(kern, dim3(used), dim3(256), 0, st, frame, order, queues, ranges, keys, ids, records, ra,
+                               pixstate, acc, evalcount);
+        });
+    } else {
+        CS_DISPATCH_K(K, CS_DISPATCH_TILE(tile, {
+            auto kern = render_bwd_kernel<KK, TT, BBW>;
+            used = std::min({persistent_grid(kern, TT * TT), (int)max_items, EVAL_SLOTS});
+            hipLaunchKernelGGL(kern, dim3(used), dim3(TT * TT), 0, st, frame, order, queues, ranges, keys, ids, records, ra,
+                               pixstate, acc, evalcount);
+        }));
+    }
     return used;
 }
 

@@ -41,10 +41,10 @@ void launch_tile_length_keys(hipStream_t, uint32_t, const FrameHeader *, const u
 void launch_cell_ranges(hipStream_t, const uint32_t *, uint32_t, const uint32_t *, uint32_t, uint2 *, uint32_t, uint32_t);
 int launch_render_fwd(hipStream_t, int, int, const FrameHeader *, const uint32_t *, uint32_t, uint32_t *,
                        const uint2 *, const uint32_t *, const uint32_t *, const uint8_t *, const RenderArgs &, uint2 *,
-                       unsigned long long *, float *, size_t);
+                       unsigned long long *, float *, size_t, bool);
 int launch_render_bwd(hipStream_t, int, int, const FrameHeader *, const uint32_t *, uint32_t, uint32_t *,
                       const uint2 *, const uint32_t *, const uint32_t *, const uint8_t *, const RenderArgs &, const uint2 *, float *,
-                      unsigned long long *);
+                      unsigned long long *, bool);
 hipError_t launch_l1_grad(hipStream_t, const float *, const float *, size_t, float *, float *);
 } // namespace cs
 
@@ -345,6 +345,7 @@ int Frame::upload_views(const FrameHeader &hdr, const ViewDesc *views, int table
     if (table == 0) {
         cells = hdr.total_cells;
         key_bits = hdr.key_bits;
+        pixels = (size_t)hdr.total_pix;
     }
     std::vector<char> &sent = table_sent[table];
     if (table_stream[table] == st && sent.size() == bytes && std::memcmp(sent.data(), &hdr, sizeof(hdr)) == 0 &&
@@ -563,6 +564,15 @@ static int wait_pair_count(const HostRing &ring, uint32_t tag, hipStream_t st, u
     return CS_OK;
 }
 
+// Up to this many pixels in all views of a call the compositing is split by
+// record (see render.hip): its squares then do not fill the chip, or only a few
+// times over.  K = 6, forward (us, by tile / by record): 400x250 121 / 74, 480x330
+// 112 / 84, 560x360 95 / 89, 640x400 87 / 96; K = 4: 560x360 112 / 89, 720x450
+// 102 / 106.  The backward holds two records' values a wavefront, at K = 6 in
+// twice the registers of K = 4's tile kernel: 400x250 126 / 119, 450x300 129 /
+// 137; K = 4: 560x360 156 / 141, 640x427 139 / 155.
+constexpr size_t SPLIT_PIXELS = 200 * 1024, SPLIT_PIXELS_BWD = 100 * 1024;
+
 // Forward pass on frame F.  device_count: the pair count stays on the device
 // (fixed capacities, graph capture); otherwise it is read back to size the
 // pair buffers exactly (plus `margin`).
@@ -578,6 +588,7 @@ int enqueue_forward(cs_ctx *ctx, Frame &F, const cs_scene *sc, const RenderArgs 
     // cells that the buffers and the cell sort provide for: this call's, or (graph
     // capture, replayed with other resolutions) any that its tiles can form
     const size_t ncells = device_count ? F.cap_cells() : F.cells;
+    const bool split_fwd = F.pixels <= SPLIT_PIXELS;
     const int sort_bits = std::max(1, ilog2_ceil(ncells));
     // The clearing of the frame's counters, the sort temporaries and the tile
     // ranges rides on the kernels before their users (preprocess, pair scan,
@@ -657,7 +668,7 @@ int enqueue_forward(cs_ctx *ctx, Frame &F, const cs_scene *sc, const RenderArgs 
         tm.begin();
         F.eval_slots = launch_render_fwd(st, F.K, kn.tile, F.d_frame, F.order, (uint32_t)F.cap_tiles, F.counters + CNT_QUEUE, F.ranges,
                           F.sorted_keys, F.sorted_ids, F.records, ra, F.pixstate, F.evalcount, zero_acc ? F.acc : nullptr,
-                          zero_acc ? F.ninst * acc_stride(F.K) : 0);
+                          zero_acc ? F.ninst * acc_stride(F.K) : 0, split_fwd);
         tm.end(CS_STAGE_RENDER_FWD);
     };
 
@@ -705,8 +716,7 @@ int enqueue_forward(cs_ctx *ctx, Frame &F, const cs_scene *sc, const RenderArgs 
         if (M > F.cap_pairs) { // did not fit: grow, reset the tile queues and counts, run the tail again
             int r = F.ensure_pairs(F.pair_room(M, tile_pairs, margin));
             if (r) return r;
-            launch_zero_ranges(st, F.counters + CNT_QUEUE, QUEUE_WORDS, nullptr, 0,
-                               nullptr, 0);
+            launch_zero_ranges(st, F.counters + CNT_QUEUE, QUEUE_WORDS, nullptr, 0, nullptr, 0);
             tail(M, nullptr);
         }
     }
@@ -733,7 +743,7 @@ int enqueue_backward(Frame &F, const cs_scene *sc, const cs_grads *g, const Rend
     tm.begin();
     F.eval_slots_bwd = launch_render_bwd(st, F.K, F.tile, F.d_frame_b, F.order, (uint32_t)F.cap_tiles, F.counters + CNT_QUEUE_B,
                                          F.ranges, F.sorted_keys, F.sorted_ids, F.records, ra, F.pixstate, F.acc,
-                                         F.evalcount + (size_t)EVAL_SLOTS * EVAL_FIELDS);
+                                         F.evalcount + (size_t)EVAL_SLOTS * EVAL_FIELDS, F.pixels <= (F.K <= 4 ? SPLIT_PIXELS : SPLIT_PIXELS_BWD));
     tm.end(CS_STAGE_RENDER_BWD);
     tm.begin();
     launch_preprocess_bwd(st, sc->n, F.V, F.K, F.deg, sc->dtype, sc->points, sc->delta, sc->sigma, sc->sh, F.d_frame_b,

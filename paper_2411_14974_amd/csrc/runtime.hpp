@@ -40,6 +40,7 @@ struct Frame {
     // form in views of any shape (every cell holds a tile)
     size_t cells = 0;
     uint32_t key_bits = 16;
+    size_t pixels = 0; // of the current views
     size_t cap_cells() const { return key_bits == 16 && cap_tiles > MAX_CELLS_16 ? (size_t)MAX_CELLS_16 : cap_tiles; }
     uint32_t npairs = 0;
     bool by_tile_pairs = false; // pair buffers sized by the (tile, convex) pairs (pair_room)

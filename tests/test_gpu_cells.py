@@ -123,3 +123,40 @@ def test_batch_of_views_with_different_cells(R):
         alone, _ = R.forward(ds, c, make_params())
         assert torch.equal(alone, o)
     st.release()
+
+
+@pytest.mark.parametrize("k", [3, 4, 5, 6, 7, 8])
+def test_small_views_split_by_record(R, k):
+    """Small views are composited by squares with the records split over the
+    wavefronts, a call with many pixels by tiles: the same scene seen alone and
+    in a batch with a large view gives the same images bit for bit, the same
+    work counts, and gradients equal up to the order of their sums."""
+    from paper_2411_14974_amd.binding import DeviceScene, make_params
+    rng = np.random.default_rng(70 + k)
+    sc = scenes.convexes_around(rng, scenes.uniform_centres(rng, 4000), k, 1)
+    cams = [scenes.orbit_camera(rng, w, h) for w, h in ((1000, 700), (61, 83), (8, 8), (250, 130))]
+    ds = DeviceScene.from_scene(sc, "cuda:0")
+    p = make_params(background=(0.2, 0.4, 0.6))
+    dls = [torch.from_numpy(rng.normal(size=(c.height, c.width, 3)).astype(np.float32)).cuda() for c in cams]
+    outs, st = R.forward_batch(ds, cams, p, want_state=True)
+    g = R.backward_batch(st, dls)
+    both = st.counters()
+    st.release()
+    total, alone = {n: 0.0 for n in g}, {n: 0 for n in both}
+    for c, o, dl in zip(cams, outs, dls):
+        img, s1 = R.forward(ds, c, p, want_state=True)
+        g1 = R.backward(s1, dl)
+        cnt = s1.counters()
+        s1.release()
+        assert torch.equal(img, o), (k, c.width)
+        for n in total:
+            total[n] = total[n] + g1[n].double()
+        for n in alone:
+            alone[n] += cnt[n]
+    for n in g:
+        gap = float((total[n] - g[n].double()).norm() / total[n].norm().clamp_min(1e-30))
+        assert gap <= 1e-5, (k, n, gap)
+    # (a batch's pairs and tests depend on nothing but the views; the record's
+    # evaluations counted per wavefront alike)
+    for n in ("pairs", "tested", "full", "full_bwd", "sum_T_full", "wave_evals"):
+        assert alone[n] == both[n], (k, n, alone[n], both[n])

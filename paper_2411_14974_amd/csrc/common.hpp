@@ -85,8 +85,8 @@ struct ViewDesc {
 // depth-ordered list is its cell's list filtered by the tile's mask bit.  A
 // view has the smallest cells of which VIEW_CELLS cover it, at most 4 x 4: a
 // small view's convexes are smaller than a few tiles, and large cells would
-// only lengthen the lists that its tiles filter (200k convexes at 256 x 256:
-// 0.29 ms with the 256 tiles as cells, 0.46 ms with 16 cells).
+// only lengthen the lists that its tiles filter (200k convexes at 256 x 256, a
+// whole render: 0.42 ms with the 256 tiles as cells, 0.46 ms with 16 cells).
 // A pair's sort key holds the cell in its low key_bits bits, the mask above:
 // 16 + 16 bits, or 28 + 4 (cells of at most 2 x 2) when a call has more cells.
 struct FrameHeader {
@@ -218,23 +218,28 @@ __device__ inline uint32_t bin_cells(uint4 b)
     return ((tx1 >> s) - (tx0 >> s) + 1u) * ((ty1 >> s) - (ty0 >> s) + 1u);
 }
 
-// Up to two word ranges that a kernel clears on the side (each block its
+// Up to three word ranges that a kernel clears on the side (each block its
 // share), in place of clearing launches of their own: the ranges' next users
-// run after the kernel in the stream.
+// run after the kernel in the stream.  `claims` (nullable): also the first word
+// of nclaims blocks of QUEUE_STRIDE words (the compositing's claim counters).
+constexpr int QUEUE_STRIDE = 1024; // 4 KiB
 struct ZeroSpans {
-    uint32_t *p[2];
-    uint32_t n[2];
+    uint32_t *p[3] = {nullptr, nullptr, nullptr};
+    uint32_t n[3] = {0u, 0u, 0u};
+    uint32_t *claims = nullptr;
+    uint32_t nclaims = 0;
 };
 __device__ inline void zero_share(const ZeroSpans &z)
 {
     const uint32_t nb = gridDim.x * gridDim.y, b = blockIdx.y * gridDim.x + blockIdx.x;
 #pragma unroll
-    for (int k = 0; k < 2; ++k) {
+    for (int k = 0; k < 3; ++k) {
         if (!z.p[k]) continue;
         const uint32_t per = (z.n[k] + nb - 1) / nb;
         const uint32_t lo = min(b * per, z.n[k]), hi = min(lo + per, z.n[k]);
         for (uint32_t i = lo + threadIdx.x; i < hi; i += blockDim.x) z.p[k][i] = 0u;
     }
+    if (z.claims && b == 0 && threadIdx.x < z.nclaims) z.claims[threadIdx.x * QUEUE_STRIDE] = 0u;
 }
 
 // Layout of a frame's counter buffer (32-bit words):
@@ -251,7 +256,6 @@ __device__ inline void zero_share(const ZeroSpans &z)
 //                             when the forward starts)
 //   [CNT_STATUS, ...)         the pair-offset scan's look-back status (u64 per tile)
 enum : int { CNT_PAIRS = 0, CNT_PAIRS_EFF = 1, CNT_OVERFLOW = 2, CNT_SORT_ERR = 3, CNT_TILE_PAIRS = 4, CNT_SCAN_TILE = 20, CNT_WORDS = 32 };
-constexpr int QUEUE_STRIDE = 1024; // 4 KiB
 constexpr int CNT_QUEUE = CNT_WORDS;
 constexpr int QUEUE_WORDS = NUM_QUEUES * QUEUE_STRIDE;
 constexpr int CNT_QUEUE_B = CNT_QUEUE + QUEUE_WORDS;

@@ -459,7 +459,7 @@ int cs_init_from_points(cs_ctx *ctx, int32_t n, const float *xyz, const float *r
         float4 *nodes = reinterpret_cast<float4 *>(scr + o_node);
         hipLaunchKernelGGL(curve_cube_kernel, dim3(1), dim3(CURVE_SAMPLES), 0, st, n, xyz, cube);
         uint32_t *temp = reinterpret_cast<uint32_t *>(scr + o_temp);
-        const ZeroSpans z{{temp, nullptr}, {(uint32_t)radix_sort_words((uint32_t)n, false, (uint32_t)n, 31, 8), 0u}};
+        const ZeroSpans z{{temp}, {(uint32_t)radix_sort_words((uint32_t)n, false, (uint32_t)n, 31, 8)}};
         hipLaunchKernelGGL(morton_kernel, grid, block, 0, st, n, xyz, cube, keys, ids, z);
         radix_sort(st, &keys, &ids, &keys2, &ids2, (uint32_t)n, nullptr, (uint32_t)n, 31, temp, 8,
                    reinterpret_cast<uint32_t *>(cube) + 8, true, nullptr, 0);

@@ -559,7 +559,8 @@ constexpr uint32_t FWD_CHUNK = 2;
 // of the batch loop (one record prefetch register among them) in scratch,
 // outside the record loop, and the extra wavefront hides more of the LDS and
 // transcendental latency (0.183 -> 0.169 ms at 1M convexes, 1080p, against 4
-// wavefronts and 106 VGPRs without spills).
+// wavefronts and 106 VGPRs without spills).  K = 7 and 8 hold more and would
+// spill 75 to 79 values: 4 wavefronts.
 constexpr int fwd_waves(int K, int TILE) { return K <= (TILE == 8 ? 4 : 6) ? 5 : 4; }
 template <int K, int TILE, int BATCH>
 __global__ __launch_bounds__(TILE *TILE) __attribute__((amdgpu_waves_per_eu(fwd_waves(K, TILE)))) void render_fwd_kernel(
@@ -955,9 +956,10 @@ __global__ __launch_bounds__(TILE *TILE) __attribute__((amdgpu_waves_per_eu(K <=
 // the walk's decisions are the other kernels' bit for bit).  The backward does
 // the same: alphas by record, T_n and the colour behind in order by every
 // wavefront, then each forms and sums the gradient values of its two records.
-// This costs about half as much again in instructions, and a record is loaded
-// and tested for every square instead of every tile, so it is for views whose
-// squares do not fill the chip (split_squares below).
+// All four wavefronts composite every record, and a record is loaded and tested
+// for every square instead of every tile: where the chip is full it takes 2.3
+// times as long (1M convexes, 1920 x 1080: forward 175 -> 412 us, backward 313 ->
+// 782), so it is for views whose squares do not fill the chip (SPLIT_PIXELS).
 constexpr int SPLIT = 8;
 constexpr float NOT_FULL = -1.0f, NOT_TESTED = -2.0f; // in place of alpha
 

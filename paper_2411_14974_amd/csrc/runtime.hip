@@ -32,6 +32,8 @@ size_t sort_temp_words(uint32_t, int, int);
 size_t scan_status_words(uint32_t);
 void launch_gather_scan(hipStream_t, uint32_t, const uint32_t *, const uint4 *, uint4 *, uint32_t *, uint32_t *,
                         uint32_t *, unsigned long long *, uint32_t, uint32_t, uint32_t *, uint32_t);
+bool launch_small_order(hipStream_t, uint32_t, const uint32_t *, const uint4 *, uint32_t *, uint4 *, uint32_t *, uint32_t *,
+                        uint32_t *, unsigned long long *, uint32_t, uint32_t, uint32_t *, uint32_t);
 void launch_fill_u32(hipStream_t, uint32_t *, size_t, uint32_t);
 void launch_emit_pairs(hipStream_t, uint32_t, uint32_t, const uint32_t *, const uint32_t *, const uint32_t *,
                        const uint4 *, const FrameHeader *, uint32_t, uint32_t *, uint32_t *, uint32_t *, uint32_t);
@@ -604,10 +606,12 @@ int enqueue_forward(cs_ctx *ctx, Frame &F, const cs_scene *sc, const RenderArgs 
         int r = F.ensure_pairs(1);
         if (r) return r;
     }
-    ZeroSpans zpre{{nullptr, nullptr}, {0u, 0u}};
+    ZeroSpans zpre;
     if (fused)
-        zpre = ZeroSpans{{F.counters, F.hist},
-                         {(uint32_t)F.counter_words, (uint32_t)radix_sort_words(ninst, false, ninst, 32, 8)}};
+        zpre = ZeroSpans{{F.counters, F.counters + CNT_STATUS, F.hist},
+                         {(uint32_t)CNT_WORDS, (uint32_t)(F.counter_words - CNT_STATUS),
+                          (uint32_t)radix_sort_words(ninst, false, ninst, 32, 8)},
+                         F.counters + CNT_QUEUE, 2 * NUM_QUEUES};
     else
         launch_zero_ranges(st, F.counters, F.counter_words, nullptr, 0, nullptr, 0);
     tm.begin();
@@ -679,19 +683,25 @@ int enqueue_forward(cs_ctx *ctx, Frame &F, const cs_scene *sc, const RenderArgs 
             int r = F.ensure_pairs(1);
             if (r) return r;
         }
-        tm.begin();
-        radix_sort(st, &keys, &ids, &keys_alt, &ids_alt, ninst, nullptr, ninst, 32, F.hist, 8, F.counters + CNT_SORT_ERR,
-                   fused, nullptr, 0);
-        tm.end(CS_STAGE_DEPTH_SORT);
-        tm.begin();
         // the count also goes straight to pinned host memory (no copy in the
         // stream); with the pair buffers' size known (a reused frame, graph
         // capture) the scan also prepares the pair pass
         scan_prepared = device_count || speculative;
-        launch_gather_scan(st, ninst, ids, F.bins, F.bins_sorted, F.counts_sorted, F.offsets, F.counters,
-                           device_count ? nullptr : reinterpret_cast<unsigned long long *>(F.ring->d_word), tag,
-                           scan_prepared ? (uint32_t)F.cap_pairs : 0u, reinterpret_cast<uint32_t *>(F.ranges),
-                           (uint32_t)(2 * F.cap_tiles));
+        unsigned long long *word = device_count ? nullptr : reinterpret_cast<unsigned long long *>(F.ring->d_word);
+        const uint32_t room = scan_prepared ? (uint32_t)F.cap_pairs : 0u, range_words = (uint32_t)(2 * F.cap_tiles);
+        uint32_t *rg = reinterpret_cast<uint32_t *>(F.ranges);
+        tm.begin();
+        const bool ordered = launch_small_order(st, ninst, keys, F.bins, ids_alt, F.bins_sorted, F.counts_sorted, F.offsets,
+                                                F.counters, word, tag, room, rg, range_words);
+        if (ordered) std::swap(ids, ids_alt);
+        else
+            radix_sort(st, &keys, &ids, &keys_alt, &ids_alt, ninst, nullptr, ninst, 32, F.hist, 8, F.counters + CNT_SORT_ERR,
+                       fused, nullptr, 0);
+        tm.end(CS_STAGE_DEPTH_SORT);
+        tm.begin();
+        if (!ordered)
+            launch_gather_scan(st, ninst, ids, F.bins, F.bins_sorted, F.counts_sorted, F.offsets, F.counters, word, tag, room, rg,
+                               range_words);
         tm.end(CS_STAGE_BIN_SCAN);
         if (!device_count) {
             if (!speculative) { // a new frame waits for its count here
@@ -1399,7 +1409,7 @@ int cs_debug_preprocess(cs_ctx *ctx, const cs_scene *sc, const cs_camera *cam, c
     CS_TRY(F.alloc((void **)&dbg, sizeof(DebugConvex) * (size_t)sc->n));
     launch_preprocess_fwd(st, sc->n, 1, sc->k, sc->sh_degree, sc->dtype, sc->points, sc->delta, sc->sigma, sc->opacity, sc->sh,
                           F.d_frame, ra, F.records, F.keys, F.ids, F.bins, F.hullpk, dbg,
-                          ZeroSpans{{nullptr, nullptr}, {0u, 0u}});
+                          ZeroSpans{});
     CS_HIP(hipGetLastError());
     CS_HIP(hipMemcpyAsync(out, dbg, sizeof(DebugConvex) * (size_t)sc->n, hipMemcpyDeviceToHost, st));
     CS_HIP(hipStreamSynchronize(st));

@@ -85,6 +85,24 @@ __device__ __forceinline__ void ss_store(uint64_t *p, uint64_t v)
     __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
+// The counts of cell pairs m and of tile pairs, where the host and the pair pass
+// look for them.
+__device__ __forceinline__ void store_pair_counts(uint32_t *counters, uint32_t m, uint32_t tiles, unsigned long long *host_word,
+                                                  uint32_t tag, uint32_t capacity)
+{
+    counters[CNT_PAIRS] = m;
+    counters[CNT_TILE_PAIRS] = tiles;
+    if (capacity) { // the pair pass's count, clamped to the buffers, and the overflow flag
+        counters[CNT_PAIRS_EFF] = m < capacity ? m : capacity;
+        counters[CNT_OVERFLOW] = m > capacity ? 1u : 0u;
+    }
+    if (host_word) {
+        const unsigned long long tg = (unsigned long long)tag << 32;
+        __hip_atomic_store(host_word + 1, tg | tiles, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+        __hip_atomic_store(host_word, tg | m, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    }
+}
+
 // host_word (nullable): two words of coherent pinned host memory that also
 // receive the counts of cell and tile pairs, each as tag << 32 | count: the
 // host waits for its tag there, with no copy or event in the stream.
@@ -166,18 +184,8 @@ __global__ __launch_bounds__(SCAN_BLOCK) void gather_scan_kernel(
         if (tid == 0) {
             s_excl = excl;
             if (base + SCAN_TILE >= n) {
-                const uint32_t m = (uint32_t)min(excl + tile_total, (uint64_t)MAX_CELL_PAIRS);
-                counters[CNT_PAIRS] = m;
-                counters[CNT_TILE_PAIRS] = excl_tiles + block_tiles;
-                if (capacity) { // the pair pass's count, clamped to the buffers, and the overflow flag
-                    counters[CNT_PAIRS_EFF] = m < capacity ? m : capacity;
-                    counters[CNT_OVERFLOW] = m > capacity ? 1u : 0u;
-                }
-                if (host_word) {
-                    const unsigned long long tg = (unsigned long long)tag << 32;
-                    __hip_atomic_store(host_word + 1, tg | (excl_tiles + block_tiles), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
-                    __hip_atomic_store(host_word, tg | m, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
-                }
+                store_pair_counts(counters, (uint32_t)min(excl + tile_total, (uint64_t)MAX_CELL_PAIRS),
+                                  excl_tiles + block_tiles, host_word, tag, capacity);
             }
         }
     }
@@ -204,7 +212,7 @@ void launch_gather_scan(hipStream_t st, uint32_t n, const uint32_t *sorted_ids, 
 {
     if (n == 0) return;
     const uint32_t tiles = (n + SCAN_TILE - 1) / SCAN_TILE;
-    const ZeroSpans z{{capacity ? ranges : nullptr, nullptr}, {capacity ? range_words : 0u, 0u}};
+    const ZeroSpans z{{capacity ? ranges : nullptr}, {capacity ? range_words : 0u}};
     hipLaunchKernelGGL(gather_scan_kernel, dim3(tiles), dim3(SCAN_BLOCK), 0, st, n, sorted_ids, bins, bins_sorted,
                        counts_sorted, offsets, counters, reinterpret_cast<uint64_t *>(counters + CNT_STATUS),
                        host_word, tag, capacity, z);
@@ -416,9 +424,11 @@ __global__ __launch_bounds__(OS_BLOCK) void os_scatter_kernel(
         os_store(&status[(size_t)t * R + tid], (t == 0 ? OS_INC : OS_AGG) | total);
     }
     const uint32_t dstart = os_block_excl(tid < R ? total : 0u, s_wsum);
-    const uint32_t dbase = os_block_excl(tid < R ? hist[tid] : 0u, s_wsum);
+    // (a sort of one tile has its histogram here)
+    const uint32_t all = tid < R ? (hist ? hist[tid] : total) : 0u;
+    const uint32_t dbase = hist ? os_block_excl(all, s_wsum) : dstart;
     // a sort of one pass: the digits are the keys, their runs the histogram's scan
-    if (ranges && t == 0 && tid < R && tid < (int)nranges) ranges[tid] = make_uint2(dbase, dbase + hist[tid]);
+    if (ranges && t == 0 && tid < R && tid < (int)nranges) ranges[tid] = make_uint2(dbase, dbase + all);
     if (tid < R) {
         s_dstart[tid] = dstart;
         uint32_t excl = 0;
@@ -568,7 +578,9 @@ bool radix_sort(hipStream_t st, uint32_t **keys, uint32_t **vals, uint32_t **key
     }
     const int hb = std::max(1, std::min(tiles, 256)); // one workgroup per CU: fewer same-address global adds
     const int widest = os_width(end_bit, P, 0);
-    if (small) {
+    const bool one_tile = tiles == 1; // (of n_grid, so for any count on the device)
+    if (one_tile) {
+    } else if (small) {
         OS_DISPATCH(widest, (os_launch_hist<BB, OS_ITEMS_MIN>(st, *keys, n_host, n_dev, hb, end_bit, P, temp)));
     } else {
         OS_DISPATCH(widest, (os_launch_hist<BB, 2 * OS_ITEMS_MIN>(st, *keys, n_host, n_dev, hb, end_bit, P, temp)));
@@ -580,17 +592,160 @@ bool radix_sort(hipStream_t st, uint32_t **keys, uint32_t **vals, uint32_t **key
         uint2 *rg = P == 1 ? ranges : nullptr;
         if (small) {
             OS_DISPATCH(b, (os_launch_scatter<BB, OS_ITEMS_MIN>(st, *keys, *vals, *keys_alt, *vals_alt, n_host, n_dev,
-                                                                tiles, shift, temp + (size_t)p * OS_RADIX,
+                                                                tiles, shift, one_tile ? nullptr : temp + (size_t)p * OS_RADIX,
                                                                 temp + OS_CTR + p, status, err, rg, nranges)));
         } else {
             OS_DISPATCH(b, (os_launch_scatter<BB, 2 * OS_ITEMS_MIN>(st, *keys, *vals, *keys_alt, *vals_alt, n_host,
-                                                                    n_dev, tiles, shift, temp + (size_t)p * OS_RADIX,
+                                                                    n_dev, tiles, shift, one_tile ? nullptr : temp + (size_t)p * OS_RADIX,
                                                                     temp + OS_CTR + p, status, err, rg, nranges)));
         }
         std::swap(*keys, *keys_alt);
         std::swap(*vals, *vals_alt);
     }
     return P == 1 && ranges != nullptr;
+}
+
+// --------------------------------------------- small scenes in one kernel ----
+
+// The depth sort, the gather of the binning records and the pair-offset scan of
+// up to SMALL_ORDER_MAX instances by one workgroup: the radix sort's four passes
+// in LDS (ranks by wavefront ballots, as above), then one scan.  Latency-bound,
+// in place of six launches that take 4 to 8 us each however few their keys: a
+// render of 1000 convexes at 128 x 128 97 -> 66 us; 8000 instances 41 us against
+// the launches' 57.  A thread holds ITEMS instances; element order is (wavefront,
+// item, lane).
+constexpr int SM_BLOCK = 1024, SM_WAVES = SM_BLOCK / 64;
+template <int ITEMS>
+__global__ __launch_bounds__(SM_BLOCK) void small_order_kernel(
+    uint32_t n, const uint32_t *__restrict__ keys, const uint4 *__restrict__ bins, uint32_t *__restrict__ sorted_ids,
+    uint4 *__restrict__ bins_sorted, uint32_t *__restrict__ counts_sorted, uint32_t *__restrict__ offsets,
+    uint32_t *__restrict__ counters, unsigned long long *__restrict__ host_word, uint32_t tag, uint32_t capacity, ZeroSpans zero)
+{
+    zero_share(zero); // the cell ranges, when this also prepares the pair pass
+    constexpr int R = 256;
+    __shared__ uint32_t s_key[SM_BLOCK * ITEMS], s_val[SM_BLOCK * ITEMS];
+    __shared__ uint32_t s_cnt[SM_WAVES][R], s_start[R], s_wsum[2][SM_WAVES];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const uint64_t lt_mask = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
+    const uint32_t first = (uint32_t)(wave * 64 * ITEMS + lane);
+    uint32_t k[ITEMS], v[ITEMS], off[ITEMS];
+#pragma unroll
+    for (int i = 0; i < ITEMS; ++i) { // places past n: the largest key, behind every instance
+        v[i] = first + 64u * i;
+        k[i] = v[i] < n ? keys[v[i]] : 0xFFFFFFFFu;
+    }
+    for (int shift = 0; shift < 32; shift += 8) {
+        for (int d = tid; d < SM_WAVES * R; d += SM_BLOCK) (&s_cnt[0][0])[d] = 0u;
+        __syncthreads();
+#pragma unroll
+        for (int i = 0; i < ITEMS; ++i) {
+            const uint32_t dg = (k[i] >> shift) & (R - 1);
+            const uint64_t peers = digit_peers<8>(dg, true);
+            const uint32_t rank = __popcll(peers & lt_mask), before = s_cnt[wave][dg];
+            off[i] = before + rank;
+            if (rank == 0) s_cnt[wave][dg] = before + (uint32_t)__popcll(peers);
+        }
+        __syncthreads();
+        // per digit: exclusive over the wavefronts, then over the digits
+        uint32_t total = 0;
+        if (tid < R) {
+#pragma unroll
+            for (int w = 0; w < SM_WAVES; ++w) {
+                const uint32_t c = s_cnt[w][tid];
+                s_cnt[w][tid] = total;
+                total += c;
+            }
+        }
+        uint32_t incl = total;
+#pragma unroll
+        for (int o = 1; o < 64; o <<= 1) {
+            const uint32_t y = __shfl_up(incl, o, 64);
+            if (lane >= o) incl += y;
+        }
+        if (lane == 63) s_wsum[0][wave] = incl;
+        __syncthreads();
+        if (tid < R) {
+            for (int w = 0; w < wave; ++w) incl += s_wsum[0][w];
+            s_start[tid] = incl - total;
+        }
+        __syncthreads();
+#pragma unroll
+        for (int i = 0; i < ITEMS; ++i) {
+            const uint32_t dg = (k[i] >> shift) & (R - 1), at = s_start[dg] + s_cnt[wave][dg] + off[i];
+            s_key[at] = k[i];
+            s_val[at] = v[i];
+        }
+        __syncthreads();
+#pragma unroll
+        for (int i = 0; i < ITEMS; ++i) {
+            k[i] = s_key[first + 64u * i];
+            v[i] = s_val[first + 64u * i];
+        }
+    }
+    uint32_t c[ITEMS], run = 0, tile_pairs = 0;
+    uint4 b[ITEMS];
+#pragma unroll
+    for (int i = 0; i < ITEMS; ++i) b[i] = bins[min(v[i], n - 1u)];
+#pragma unroll
+    for (int i = 0; i < ITEMS; ++i) {
+        const uint32_t r = first + 64u * i;
+        const uint32_t cells = r < n ? bin_cells(b[i]) : 0u;
+        tile_pairs += r < n ? bin_count(b[i]) : 0u;
+        uint32_t incl = cells;
+#pragma unroll
+        for (int o = 1; o < 64; o <<= 1) {
+            const uint32_t y = __shfl_up(incl, o, 64);
+            if (lane >= o) incl += y;
+        }
+        c[i] = run + incl - cells; // before this one in the wavefront
+        run += __shfl(incl, 63, 64);
+        if (r < n) {
+            sorted_ids[r] = v[i];
+            bins_sorted[r] = b[i];
+            counts_sorted[r] = cells;
+        }
+    }
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) tile_pairs += __shfl_xor(tile_pairs, o, 64);
+    if (lane == 0) {
+        s_wsum[0][wave] = run;
+        s_wsum[1][wave] = tile_pairs;
+    }
+    __syncthreads();
+    uint32_t before = 0, m = 0, tiles = 0;
+    for (int w = 0; w < SM_WAVES; ++w) {
+        if (w < wave) before += s_wsum[0][w];
+        m += s_wsum[0][w];
+        tiles += s_wsum[1][w];
+    }
+#pragma unroll
+    for (int i = 0; i < ITEMS; ++i)
+        if (first + 64u * i < n) offsets[first + 64u * i] = before + c[i];
+    if (tid == 0) {
+        m = min(m, MAX_CELL_PAIRS);
+        store_pair_counts(counters, m, tiles, host_word, tag, capacity);
+    }
+}
+
+// Whether the order of n instances is made by small_order_kernel; then it is
+// (arguments as launch_gather_scan's, keys in instance order).  The line is where
+// the keys still fit LDS: one workgroup is faster up to there (above).
+constexpr uint32_t SMALL_ORDER_MAX = 8 * SM_BLOCK;
+bool launch_small_order(hipStream_t st, uint32_t n, const uint32_t *keys, const uint4 *bins, uint32_t *sorted_ids,
+                        uint4 *bins_sorted, uint32_t *counts_sorted, uint32_t *offsets, uint32_t *counters,
+                        unsigned long long *host_word, uint32_t tag, uint32_t capacity, uint32_t *ranges, uint32_t range_words)
+{
+    if (n == 0 || n > SMALL_ORDER_MAX) return false;
+    const ZeroSpans z{{capacity ? ranges : nullptr}, {capacity ? range_words : 0u}};
+    auto launch = [&](auto kern) {
+        hipLaunchKernelGGL(kern, dim3(1), dim3(SM_BLOCK), 0, st, n, keys, bins, sorted_ids, bins_sorted, counts_sorted, offsets,
+                           counters, host_word, tag, capacity, z);
+    };
+    if (n <= SM_BLOCK) launch(small_order_kernel<1>);
+    else if (n <= 2 * SM_BLOCK) launch(small_order_kernel<2>);
+    else if (n <= 4 * SM_BLOCK) launch(small_order_kernel<4>);
+    else launch(small_order_kernel<8>);
+    return true;
 }
 
 // ------------------------------------------------------------- binning ----
@@ -853,7 +1008,7 @@ void launch_emit_pairs(hipStream_t st, uint32_t n, uint32_t n_convex, const uint
                        uint32_t *zero, uint32_t zero_words)
 {
     if (n == 0) return;
-    const ZeroSpans z{{zero, nullptr}, {zero ? zero_words : 0u, 0u}};
+    const ZeroSpans z{{zero}, {zero ? zero_words : 0u}};
     hipLaunchKernelGGL(emit_pairs_kernel, dim3((n + EMIT_BLOCK - 1) / EMIT_BLOCK), dim3(EMIT_BLOCK), 0, st, n,
                        n_convex, sorted_ids, offsets, counts_sorted, bins_sorted, views, capacity, pair_tiles,
                        pair_ids, z);

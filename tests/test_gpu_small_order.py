@@ -1,0 +1,51 @@
+"""Up to 8192 instances of a call are depth-sorted, gathered and scanned by one
+workgroup, more by the radix sort's launches: at sizes on both sides of every
+step of that rule, with depths that repeat, every tile's list holds the same
+convexes in (depth, index) order and the counts agree with the lists."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+from paper_2411_14974_amd import scenes  # noqa: E402
+
+
+@pytest.fixture(scope="module")
+def R():
+    from paper_2411_14974_amd.binding import Renderer
+    r = Renderer(0)
+    yield r
+    r.close()
+
+
+@pytest.mark.parametrize("views", [1, 3])
+@pytest.mark.parametrize("n", [1, 2, 63, 65, 1023, 1024, 1025, 2049, 2731, 4097, 8192, 8193])
+def test_order_of_few_instances(R, n, views):
+    import oracle
+    from paper_2411_14974_amd.binding import DeviceScene, make_params
+    rng = np.random.default_rng(n)
+    centres = scenes.uniform_centres(rng, n)
+    centres[n // 2:] = centres[:n - n // 2]  # every other depth twice (or nearly)
+    sc = scenes.convexes_around(rng, centres, 4, 0)
+    cams = [scenes.orbit_camera(rng, w, h) for w, h in ((130, 70), (33, 48), (16, 16))[:views]]
+    ds = DeviceScene.from_scene(sc, "cuda:0")
+    outs, st = R.forward_batch(ds, cams, make_params(), want_state=True)
+    outs2, st2 = R.forward_batch(ds, cams, make_params(), want_state=True)  # a reused frame: sizes known
+    ranges, ids = st.tile_lists()
+    assert st.stats()["pairs"] == len(ids) == int((ranges[:, 1] - ranges[:, 0]).sum())
+    assert all(np.array_equal(a, b) for a, b in zip((ranges, ids), st2.tile_lists()))
+    assert all(torch.equal(a, b) for a, b in zip(outs, outs2))
+    t0 = 0
+    for cam, img in zip(cams, outs):
+        keys = np.array([c.key for c in oracle.preprocess(sc, cam)], np.uint64)
+        alone, _ = R.forward(ds, cam, make_params())
+        assert torch.equal(alone, img)
+        for t in range(t0, t0 + ((cam.width + 15) // 16) * ((cam.height + 15) // 16)):
+            lst = ids[ranges[t, 0]:ranges[t, 1]] % n
+            assert np.all(np.lexsort((lst, keys[lst])) == np.arange(len(lst))), (n, t)
+            assert len(set(lst.tolist())) == len(lst)
+        t0 += ((cam.width + 15) // 16) * ((cam.height + 15) // 16)
+    st.release()
+    st2.release()

@@ -440,19 +440,30 @@ template <int ACT> __device__ __forceinline__ float activate(float r)
     else return r;
 }
 
+// One parameter array of an Adam step.  Elements e with row > 0 and
+// e % row >= first take the second step size.
+struct AdamPart {
+    const float *g;
+    float *raw, *m, *v, *act; // act nullable
+    size_t n;
+    uint32_t first_block;  // of the grid: the part's chunks
+    int kind, row, first;
+    float step_size;       // lr / (1 - beta1^t) of the first rate
+    float step_size2;      // the same for the second rate (SH coefficients past the first)
+    bool vec;              // every array 16-byte aligned
+};
+constexpr int ADAM_PARTS = 5;
 struct AdamArgs {
-    float beta1, beta2, omb1, omb2, eps; // betas and 1 - betas (formed in double)
-    float step_size;  // lr / (1 - beta1^t) of the first rate
-    float step_size2; // the same for the second rate (SH coefficients past the first)
-    float bc2_sqrt;   // sqrt(1 - beta2^t)
+    float beta2, omb1, omb2, eps; // beta2, 1 - betas (formed in double)
+    float bc2_sqrt;               // sqrt(1 - beta2^t)
+    AdamPart part[ADAM_PARTS];
 };
 
-// Elements e with row > 0 and e % row >= first take the second rate.
 // One parameter element: the activation's derivative at the current raw
 // value, the moment updates and the step on the raw value.
 template <int ACT>
-__device__ __forceinline__ void adam_element(size_t e, size_t n, float r, float gact, float m0, float v0, int row,
-                                             int first, const AdamArgs &a, float &rn, float &mm, float &vv)
+__device__ __forceinline__ void adam_element(float r, float gact, float m0, float v0, float ss, const AdamArgs &a, float &rn,
+                                             float &mm, float &vv)
 {
     float da = 1.0f; // d activated / d raw at the current raw value
     if constexpr (ACT == ACT_EXP) da = expf(r);
@@ -464,68 +475,87 @@ __device__ __forceinline__ void adam_element(size_t e, size_t n, float r, float 
     mm = m0 + a.omb1 * (g - m0);
     vv = a.beta2 * v0 + a.omb2 * (g * g);
     const float denom = sqrtf(vv) / a.bc2_sqrt + a.eps;
-    // position in the row (32-bit arithmetic when the index fits: a 64-bit
-    // remainder is a long software sequence)
-    const uint32_t col = row <= 0 ? 0u : (n >> 32) == 0 ? (uint32_t)e % (uint32_t)row : (uint32_t)(e % (size_t)row);
-    const float ss = (row > 0 && (int)col >= first) ? a.step_size2 : a.step_size;
     rn = r - ss * (mm / denom);
 }
 
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+constexpr int ADAM_BLOCK = 256, ADAM_VECS = 1, ADAM_CHUNK = ADAM_BLOCK * ADAM_VECS * 4; // elements a workgroup
+
 template <int ACT>
-__global__ __launch_bounds__(256) void adam_kernel(size_t n, const float *__restrict__ g_act, float *__restrict__ raw,
-                                                   float *__restrict__ m, float *__restrict__ v,
-                                                   float *__restrict__ act_out, int row, int first, AdamArgs a)
+__device__ __forceinline__ void adam_chunk(const AdamArgs &a, const AdamPart &p, uint32_t chunk)
 {
-    for (size_t e = blockIdx.x * (size_t)blockDim.x + threadIdx.x; e < n; e += (size_t)gridDim.x * blockDim.x) {
+    const size_t e0 = (size_t)chunk * ADAM_CHUNK;
+    const uint32_t left = (uint32_t)min(p.n - e0, (size_t)ADAM_CHUNK), row = (uint32_t)p.row;
+    // the chunk's first element's place in its row
+    const uint32_t c0 = row ? (chunk % row) * (ADAM_CHUNK % row) % row : 0u;
+    auto rate = [&](uint32_t col) { return row && (int)col >= p.first ? p.step_size2 : p.step_size; };
+    auto one = [&](uint32_t i) {
+        const size_t e = e0 + i;
         float rn, mm, vv;
-        adam_element<ACT>(e, n, raw[e], g_act[e], m[e], v[e], row, first, a, rn, mm, vv);
-        raw[e] = rn;
-        m[e] = mm;
-        v[e] = vv;
-        if (act_out) act_out[e] = activate<ACT>(rn);
-    }
-}
-
-// The same update, four elements per thread in 16-byte accesses (every array
-// 16-byte aligned and n a multiple of 4); the arithmetic per element is the
-// scalar kernel's, so the results are identical.
-template <int ACT>
-__global__ __launch_bounds__(256) void adam4_kernel(size_t n, const float4 *__restrict__ g_act, float4 *__restrict__ raw,
-                                                    float4 *__restrict__ m, float4 *__restrict__ v,
-                                                    float4 *__restrict__ act_out, int row, int first, AdamArgs a)
-{
-    const size_t n4 = n / 4;
-    for (size_t q = blockIdx.x * (size_t)blockDim.x + threadIdx.x; q < n4; q += (size_t)gridDim.x * blockDim.x) {
-        const float4 r4 = raw[q], g4 = g_act[q], m4 = m[q], v4 = v[q];
-        const float rr[4] = {r4.x, r4.y, r4.z, r4.w}, gg[4] = {g4.x, g4.y, g4.z, g4.w};
-        const float mi[4] = {m4.x, m4.y, m4.z, m4.w}, vi[4] = {v4.x, v4.y, v4.z, v4.w};
-        float rn[4], mm[4], vv[4];
-#pragma unroll
-        for (int j = 0; j < 4; ++j) adam_element<ACT>(4 * q + j, n, rr[j], gg[j], mi[j], vi[j], row, first, a, rn[j], mm[j], vv[j]);
-        raw[q] = make_float4(rn[0], rn[1], rn[2], rn[3]);
-        m[q] = make_float4(mm[0], mm[1], mm[2], mm[3]);
-        v[q] = make_float4(vv[0], vv[1], vv[2], vv[3]);
-        if (act_out)
-            act_out[q] = make_float4(activate<ACT>(rn[0]), activate<ACT>(rn[1]), activate<ACT>(rn[2]),
-                                     activate<ACT>(rn[3]));
-    }
-}
-
-template <int ACT>
-void launch_adam(hipStream_t st, size_t n, const float *g, float *raw, float *m, float *v, float *act, int row,
-                 int first, const AdamArgs &a)
-{
-    if (n == 0) return;
-    auto al = [](const void *p) { return ((uintptr_t)p & 15u) == 0; };
-    if (n % 4 == 0 && al(g) && al(raw) && al(m) && al(v) && (!act || al(act))) {
-        const size_t blocks = std::min<size_t>((n / 4 + 255) / 256, 8192);
-        hipLaunchKernelGGL(adam4_kernel<ACT>, dim3((unsigned)blocks), dim3(256), 0, st, n, (const float4 *)g,
-                           (float4 *)raw, (float4 *)m, (float4 *)v, (float4 *)act, row, first, a);
+        adam_element<ACT>(p.raw[e], p.g[e], p.m[e], p.v[e], rate(row ? (c0 + i) % row : 0u), a, rn, mm, vv);
+        p.raw[e] = rn;
+        p.m[e] = mm;
+        p.v[e] = vv;
+        if (p.act) p.act[e] = activate<ACT>(rn);
+    };
+    if (!p.vec) {
+        for (uint32_t i = threadIdx.x; i < left; i += ADAM_BLOCK) one(i);
         return;
     }
-    const size_t blocks = std::min<size_t>((n + 255) / 256, 8192);
-    hipLaunchKernelGGL(adam_kernel<ACT>, dim3((unsigned)blocks), dim3(256), 0, st, n, g, raw, m, v, act, row, first,
-                       a);
+    const f32x4 *raw = reinterpret_cast<const f32x4 *>(p.raw + e0), *g = reinterpret_cast<const f32x4 *>(p.g + e0);
+    const f32x4 *m = reinterpret_cast<const f32x4 *>(p.m + e0), *v = reinterpret_cast<const f32x4 *>(p.v + e0);
+    f32x4 r4[ADAM_VECS], g4[ADAM_VECS], m4[ADAM_VECS], v4[ADAM_VECS];
+    const uint32_t full = left / 4;
+#pragma unroll
+    for (int k = 0; k < ADAM_VECS; ++k) {
+        const uint32_t q = min(threadIdx.x + (uint32_t)(k * ADAM_BLOCK), max(full, 1u) - 1u);
+        if (full == 0) break;
+        r4[k] = __builtin_nontemporal_load(raw + q);
+        g4[k] = __builtin_nontemporal_load(g + q);
+        m4[k] = __builtin_nontemporal_load(m + q);
+        v4[k] = __builtin_nontemporal_load(v + q);
+    }
+#pragma unroll
+    for (int k = 0; k < ADAM_VECS; ++k) {
+        const uint32_t q = threadIdx.x + (uint32_t)(k * ADAM_BLOCK);
+        if (q >= full) break;
+        uint32_t col = row ? (c0 + 4u * q) % row : 0u;
+        f32x4 rn, mm, vv, av;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            float x, y, z;
+            adam_element<ACT>(r4[k][j], g4[k][j], m4[k][j], v4[k][j], rate(col), a, x, y, z);
+            rn[j] = x;
+            mm[j] = y;
+            vv[j] = z;
+            av[j] = activate<ACT>(x);
+            col = col + 1 == row ? 0u : col + 1;
+        }
+        __builtin_nontemporal_store(rn, reinterpret_cast<f32x4 *>(p.raw + e0) + q);
+        __builtin_nontemporal_store(mm, reinterpret_cast<f32x4 *>(p.m + e0) + q);
+        __builtin_nontemporal_store(vv, reinterpret_cast<f32x4 *>(p.v + e0) + q);
+        if (p.act) reinterpret_cast<f32x4 *>(p.act + e0)[q] = av;
+    }
+    if (threadIdx.x < left % 4) one(4 * full + threadIdx.x); // the array's last ones
+}
+
+// One step on every parameter array: a workgroup updates one chunk of one array
+// in 16-byte accesses (element by element where an array is not so aligned).
+// HBM-bound: 4 reads and 4 writes an element.  What the step itself reads only
+// once does not go through the caches, the activated values that the next render
+// reads do: 1M convexes (K = 6, degree 3; 2.2 GB) 380 us, with every access cached
+// 428, with none 429, with only the loads cached 438; a launch per array 445.
+// 16 bytes a thread and array; 32 or 64 at once are no faster (394, 377).
+__global__ __launch_bounds__(ADAM_BLOCK) void adam_kernel(AdamArgs a)
+{
+    int k = 0;
+#pragma unroll
+    for (int j = 1; j < ADAM_PARTS; ++j) k = blockIdx.x >= a.part[j].first_block ? j : k;
+    const AdamPart &p = a.part[k];
+    const uint32_t chunk = blockIdx.x - p.first_block;
+    if (p.kind == ACT_ID) adam_chunk<ACT_ID>(a, p, chunk);
+    else if (p.kind == ACT_EXP) adam_chunk<ACT_EXP>(a, p, chunk);
+    else adam_chunk<ACT_SIGMOID>(a, p, chunk);
 }
 
 bool set_complete(const cs_param_set *p)
@@ -560,31 +590,29 @@ int cs_adam_step(cs_ctx *ctx, int32_t n, int32_t k, int32_t sh_degree, const cs_
     hipStream_t st = (hipStream_t)hip_stream;
     const double bc1 = 1.0 - std::pow(prm->beta1, (double)prm->step);
     const double bc2 = 1.0 - std::pow(prm->beta2, (double)prm->step);
-    auto args = [&](float lr, float lr2) {
-        AdamArgs a;
-        a.beta1 = (float)prm->beta1;
-        a.beta2 = (float)prm->beta2;
-        a.omb1 = (float)(1.0 - prm->beta1);
-        a.omb2 = (float)(1.0 - prm->beta2);
-        a.eps = prm->eps;
-        a.step_size = (float)(lr / bc1);
-        a.step_size2 = (float)(lr2 / bc1);
-        a.bc2_sqrt = (float)std::sqrt(bc2);
-        return a;
-    };
+    AdamArgs a{};
+    a.beta2 = (float)prm->beta2;
+    a.omb1 = (float)(1.0 - prm->beta1);
+    a.omb2 = (float)(1.0 - prm->beta2);
+    a.eps = prm->eps;
+    a.bc2_sqrt = (float)std::sqrt(bc2);
     const size_t N = (size_t)n;
     const int nsh = 3 * (sh_degree + 1) * (sh_degree + 1);
-    auto act = [&](float *cs_param_set::*f) { return activated ? activated->*f : nullptr; };
-    launch_adam<ACT_ID>(st, N * 3 * k, grad->points, raw->points, m->points, v->points, act(&cs_param_set::points), 0,
-                        0, args(prm->lr_points, prm->lr_points));
-    launch_adam<ACT_EXP>(st, N, grad->delta, raw->delta, m->delta, v->delta, act(&cs_param_set::delta), 0, 0,
-                         args(prm->lr_delta, prm->lr_delta));
-    launch_adam<ACT_EXP>(st, N, grad->sigma, raw->sigma, m->sigma, v->sigma, act(&cs_param_set::sigma), 0, 0,
-                         args(prm->lr_sigma, prm->lr_sigma));
-    launch_adam<ACT_SIGMOID>(st, N, grad->opacity, raw->opacity, m->opacity, v->opacity,
-                             act(&cs_param_set::opacity), 0, 0, args(prm->lr_opacity, prm->lr_opacity));
-    launch_adam<ACT_ID>(st, N * nsh, grad->sh, raw->sh, m->sh, v->sh, act(&cs_param_set::sh), nsh, 3,
-                        args(prm->lr_sh_dc, prm->lr_sh_rest));
+    uint32_t blocks = 0, parts = 0;
+    auto add = [&](int kind, size_t count, float *cs_grads::*gf, float *cs_param_set::*f, float lr, float lr2, int row, int first) {
+        AdamPart &p = a.part[parts++];
+        p = {grad->*gf, raw->*f, m->*f, v->*f, activated ? activated->*f : nullptr, count, blocks, kind, row, first,
+             (float)(lr / bc1), (float)(lr2 / bc1), true};
+        for (const float *q : {p.g, (const float *)p.raw, (const float *)p.m, (const float *)p.v, (const float *)p.act})
+            p.vec = p.vec && ((uintptr_t)q & 15u) == 0;
+        blocks += (uint32_t)((count + ADAM_CHUNK - 1) / ADAM_CHUNK); // (count < 2^31 * 48)
+    };
+    add(ACT_ID, N * 3 * k, &cs_grads::points, &cs_param_set::points, prm->lr_points, prm->lr_points, 0, 0);
+    add(ACT_EXP, N, &cs_grads::delta, &cs_param_set::delta, prm->lr_delta, prm->lr_delta, 0, 0);
+    add(ACT_EXP, N, &cs_grads::sigma, &cs_param_set::sigma, prm->lr_sigma, prm->lr_sigma, 0, 0);
+    add(ACT_SIGMOID, N, &cs_grads::opacity, &cs_param_set::opacity, prm->lr_opacity, prm->lr_opacity, 0, 0);
+    add(ACT_ID, N * nsh, &cs_grads::sh, &cs_param_set::sh, prm->lr_sh_dc, prm->lr_sh_rest, nsh, 3);
+    hipLaunchKernelGGL(adam_kernel, dim3(blocks), dim3(ADAM_BLOCK), 0, st, a);
     const hipError_t e = hipGetLastError();
     return e == hipSuccess ? CS_OK : fail(CS_EHIP, "adam launch: %s", hipGetErrorString(e));
 }

@@ -11,6 +11,7 @@
 // mask of the cell's tiles (see FrameHeader), so that the pairs are a quarter
 // of the (tile, convex) pairs.
 #include <algorithm>
+#include <type_traits>
 #include <utility>
 
 #include "common.hpp"
@@ -20,13 +21,18 @@ namespace cs {
 // ----------------------------------------------------------------- scan ----
 
 constexpr int SCAN_BLOCK = 256;
-constexpr int SCAN_ITEMS = 16;
-constexpr int SCAN_TILE = SCAN_BLOCK * SCAN_ITEMS;
+// Instances per thread: few enough that the chip has a few hundred workgroups
+// (a thread's gathers are one latency each), many enough that the tiles' claims
+// and look-back chain stay short.  us with 4 / 8 / 16: 20k 8 / 10 / 14, 100k 9.4 /
+// 10.7 / 14.6, 317k 16 / 14 / 16, 1M 40 / 32 / 29.
+inline int scan_items(uint32_t n) { return n <= 160u * 1024 ? 4 : n <= 640u * 1024 ? 8 : 16; }
+inline size_t scan_tiles(uint32_t n, int items) { return ((size_t)n + SCAN_BLOCK * items - 1) / (SCAN_BLOCK * items); }
 
 __device__ __forceinline__ int lds_pad(int i) { return i + (i >> 5); }
 
 // Exclusive scan of the block's SCAN_ITEMS values per thread held in LDS
 // (padded layout); returns the block total.
+template <int SCAN_ITEMS>
 __device__ uint32_t block_scan_lds(uint32_t *s, uint32_t *s_wave)
 {
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -62,7 +68,7 @@ __device__ uint32_t block_scan_lds(uint32_t *s, uint32_t *s_wave)
 }
 
 // (cell, convex) pair counts in depth order and their exclusive scan (the pair offsets), in
-// one pass: each workgroup claims the next tile of SCAN_TILE ranks, gathers
+// one pass: each workgroup claims the next tile of ranks, gathers
 // the binning records bins[sorted_ids[r]] (copied out in depth order for the
 // pair emission) and their pair counts, scans the counts in LDS, publishes the tile's sum and
 // finds its prefix by a decoupled look-back in which one wave reads 64
@@ -106,6 +112,7 @@ __device__ __forceinline__ void store_pair_counts(uint32_t *counters, uint32_t m
 // host_word (nullable): two words of coherent pinned host memory that also
 // receive the counts of cell and tile pairs, each as tag << 32 | count: the
 // host waits for its tag there, with no copy or event in the stream.
+template <int SCAN_ITEMS>
 __global__ __launch_bounds__(SCAN_BLOCK) void gather_scan_kernel(
     uint32_t n, const uint32_t *__restrict__ sorted_ids, const uint4 *__restrict__ bins,
     uint4 *__restrict__ bins_sorted, uint32_t *__restrict__ counts_sorted, uint32_t *__restrict__ offsets,
@@ -113,6 +120,7 @@ __global__ __launch_bounds__(SCAN_BLOCK) void gather_scan_kernel(
     uint32_t tag, uint32_t capacity, ZeroSpans zero)
 {
     zero_share(zero); // the cell ranges, when this scan also prepares the pair pass
+    constexpr int SCAN_TILE = SCAN_BLOCK * SCAN_ITEMS;
     __shared__ uint32_t s[SCAN_TILE + SCAN_TILE / 32];
     __shared__ uint32_t s_wave[SCAN_BLOCK / 64];
     __shared__ uint32_t s_tile;
@@ -123,22 +131,28 @@ __global__ __launch_bounds__(SCAN_BLOCK) void gather_scan_kernel(
     const uint32_t t = s_tile;
     const size_t base = (size_t)t * SCAN_TILE;
     if (base >= n) return;
-    uint32_t tile_pairs = 0;
+    uint32_t tile_pairs = 0, id[SCAN_ITEMS];
+    uint4 b[SCAN_ITEMS];
+    // (all the loads before the first use, at clamped places: one latency for
+    // each of the two chains instead of one per item)
+#pragma unroll
+    for (int k = 0; k < SCAN_ITEMS; ++k) id[k] = sorted_ids[min(base + (size_t)k * SCAN_BLOCK + tid, (size_t)n - 1)];
+#pragma unroll
+    for (int k = 0; k < SCAN_ITEMS; ++k) b[k] = bins[id[k]]; // the one random read per instance
 #pragma unroll
     for (int k = 0; k < SCAN_ITEMS; ++k) {
         const size_t i = base + (size_t)k * SCAN_BLOCK + tid;
         uint32_t c = 0;
         if (i < n) {
-            const uint4 b = bins[sorted_ids[i]]; // the one random read per instance
-            c = bin_cells(b);
-            tile_pairs += bin_count(b);
-            bins_sorted[i] = b;
+            c = bin_cells(b[k]);
+            tile_pairs += bin_count(b[k]);
+            bins_sorted[i] = b[k];
             counts_sorted[i] = c;
         }
         s[lds_pad(k * SCAN_BLOCK + tid)] = c;
     }
     __syncthreads();
-    const uint32_t tile_total = block_scan_lds(s, s_wave);
+    const uint32_t tile_total = block_scan_lds<SCAN_ITEMS>(s, s_wave);
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) tile_pairs += __shfl_xor(tile_pairs, o, 64);
     if (lane == 0) s_wave[tid >> 6] = tile_pairs; // (the scan above ended with a barrier)
@@ -198,8 +212,13 @@ __global__ __launch_bounds__(SCAN_BLOCK) void gather_scan_kernel(
     }
 }
 
-// 32-bit words of the scan's look-back status (u64 per tile of SCAN_TILE ranks).
-size_t scan_status_words(uint32_t n) { return 2 * (((size_t)n + SCAN_TILE - 1) / SCAN_TILE + 1); }
+// 32-bit words of the scan's look-back status (u64 per tile) for up to n
+// instances: the most tiles that any count up to n is split into.
+size_t scan_status_words(uint32_t n)
+{
+    const size_t few = scan_tiles(std::min(n, 160u * 1024), 4), more = scan_tiles(std::min(n, 640u * 1024), 8);
+    return 2 * (std::max({few, more, scan_tiles(n, 16)}) + 1);
+}
 
 // bins_sorted[r] = bins[sorted_ids[r]], counts_sorted[r] its pair count,
 // offsets = their exclusive scan, counters[CNT_PAIRS] = the total,
@@ -211,11 +230,16 @@ void launch_gather_scan(hipStream_t st, uint32_t n, const uint32_t *sorted_ids, 
                         uint32_t range_words)
 {
     if (n == 0) return;
-    const uint32_t tiles = (n + SCAN_TILE - 1) / SCAN_TILE;
+    const int items = scan_items(n);
     const ZeroSpans z{{capacity ? ranges : nullptr}, {capacity ? range_words : 0u}};
-    hipLaunchKernelGGL(gather_scan_kernel, dim3(tiles), dim3(SCAN_BLOCK), 0, st, n, sorted_ids, bins, bins_sorted,
-                       counts_sorted, offsets, counters, reinterpret_cast<uint64_t *>(counters + CNT_STATUS),
-                       host_word, tag, capacity, z);
+    auto launch = [&](auto kern) {
+        hipLaunchKernelGGL(kern, dim3((unsigned)scan_tiles(n, items)), dim3(SCAN_BLOCK), 0, st, n, sorted_ids, bins, bins_sorted,
+                           counts_sorted, offsets, counters, reinterpret_cast<uint64_t *>(counters + CNT_STATUS),
+                           host_word, tag, capacity, z);
+    };
+    if (items == 4) launch(gather_scan_kernel<4>);
+    else if (items == 8) launch(gather_scan_kernel<8>);
+    else launch(gather_scan_kernel<16>);
 }
 
 // ----------------------------------------------------------- radix sort ----
@@ -237,8 +261,12 @@ void launch_gather_scan(hipStream_t st, uint32_t n, const uint32_t *sorted_ids, 
 
 constexpr int OS_BLOCK = 512;
 constexpr int OS_WAVES = OS_BLOCK / 64;
-constexpr int OS_ITEMS_MIN = 8;                       // keys per thread of the smaller tiles
-constexpr int OS_TILE_MIN = OS_BLOCK * OS_ITEMS_MIN;  // 4096 keys
+// Keys per thread: small tiles for few keys (more workgroups in flight), large
+// ones for many (a shorter look-back chain).  us a pass of 8 bits with 4 / 8: 20k 7.7 /
+// 9.4, 100k 9.3 / 10.1, 317k 13.2 / 12.8, 1M 22.5 / 17.9.
+constexpr uint32_t OS_FEW = 128u * 1024, OS_MANY = 1u << 22;
+inline int os_items(size_t n) { return n <= OS_FEW ? 4 : n <= OS_MANY ? 8 : 16; }
+inline size_t os_tiles(size_t n, int items) { return (n + OS_BLOCK * items - 1) / (OS_BLOCK * items); }
 constexpr int OS_RADIX = 256; // digits of up to 8 bits (one pass of 9 bits: os_radix)
 constexpr int OS_MAX_PASSES = 8;
 constexpr uint32_t OS_AGG = 1u << 30, OS_INC = 2u << 30, OS_VAL = OS_AGG - 1u;
@@ -394,9 +422,8 @@ __global__ __launch_bounds__(OS_BLOCK) void os_scatter_kernel(
 #pragma unroll
     for (int i = 0; i < ITEMS; ++i) {
         const size_t idx = wbase + i * 64 + lane;
-        const bool valid = idx < n;
-        k[i] = valid ? keys_in[idx] : 0u;
-        v[i] = valid ? vals_in[idx] : 0u;
+        k[i] = keys_in[min(idx, (size_t)n - 1)]; // (clamped: no branch between the loads)
+        v[i] = vals_in[min(idx, (size_t)n - 1)];
     }
 #pragma unroll
     for (int i = 0; i < ITEMS; ++i) {
@@ -492,7 +519,8 @@ __global__ void fill_u32_kernel(uint32_t *__restrict__ p, size_t n, uint32_t v);
 size_t sort_temp_words(uint32_t n_capacity, int end_bit, int digit_bits)
 {
     digit_bits = std::min(8, std::max(4, digit_bits));
-    const size_t tiles = ((size_t)n_capacity + OS_TILE_MIN - 1) / OS_TILE_MIN; // the smaller tiles: more of them
+    // (the most tiles that any count up to the capacity is split into)
+    const size_t tiles = std::max(os_tiles(std::min(n_capacity, OS_FEW), 4), os_tiles(n_capacity, 8));
     return OS_STATUS + (size_t)os_passes(end_bit, digit_bits) * std::max<size_t>(tiles, 1) * OS_RADIX;
 }
 
@@ -526,6 +554,13 @@ static void os_launch_scatter(hipStream_t st, const uint32_t *keys, const uint32
     default: { constexpr int BB = 8; CALL; } break;                                                                \
     }
 
+#define OS_ITEMS_DISPATCH(ITEMS, CALL)                                                                             \
+    do {                                                                                                           \
+        if (ITEMS == 4) CALL(std::integral_constant<int, 4>{});                                                    \
+        else if (ITEMS == 8) CALL(std::integral_constant<int, 8>{});                                               \
+        else CALL(std::integral_constant<int, 16>{});                                                              \
+    } while (0)
+
 // Sorts bits [0, end_bit) of the keys in ceil(end_bit / digit_bits) passes
 // (digit_bits in 4..8; the bits are split evenly over the passes).  On
 // return *keys/*vals point at the sorted arrays (one of the two buffer pairs).
@@ -551,8 +586,7 @@ size_t radix_sort_words(uint32_t n_host, bool n_on_device, uint32_t n_capacity, 
     const uint32_t n_grid = n_on_device ? n_capacity : n_host;
     if (n_grid == 0 || end_bit <= 0) return 0;
     const int P = os_passes(end_bit, digit_bits);
-    const int tile = n_grid <= (1u << 22) ? OS_TILE_MIN : 2 * OS_TILE_MIN;
-    const size_t tiles = ((size_t)n_grid + tile - 1) / tile;
+    const size_t tiles = os_tiles(n_grid, os_items(n_grid));
     return OS_STATUS + (size_t)P * tiles * os_radix(os_width(end_bit, P, 0));
 }
 
@@ -566,11 +600,7 @@ bool radix_sort(hipStream_t st, uint32_t **keys, uint32_t **vals, uint32_t **key
     const uint32_t n_grid = n_dev ? n_capacity : n_host;
     if (n_grid == 0 || end_bit <= 0) return false;
     const int P = os_passes(end_bit, digit_bits);
-    // up to 4M elements: tiles of OS_TILE_MIN (more workgroups in flight);
-    // beyond: twice as large (half the look-back chain)
-    const bool small = n_grid <= (1u << 22);
-    const int tile = small ? OS_TILE_MIN : 2 * OS_TILE_MIN;
-    const int tiles = (int)((n_grid + tile - 1) / tile);
+    const int items = os_items(n_grid), tiles = (int)os_tiles(n_grid, items);
     const size_t words = radix_sort_words(n_host, n_dev != nullptr, n_capacity, end_bit, digit_bits);
     if (!temp_clear) {
         const size_t fb = std::min<size_t>((words + 255) / 256, 4096);
@@ -579,26 +609,21 @@ bool radix_sort(hipStream_t st, uint32_t **keys, uint32_t **vals, uint32_t **key
     const int hb = std::max(1, std::min(tiles, 256)); // one workgroup per CU: fewer same-address global adds
     const int widest = os_width(end_bit, P, 0);
     const bool one_tile = tiles == 1; // (of n_grid, so for any count on the device)
-    if (one_tile) {
-    } else if (small) {
-        OS_DISPATCH(widest, (os_launch_hist<BB, OS_ITEMS_MIN>(st, *keys, n_host, n_dev, hb, end_bit, P, temp)));
-    } else {
-        OS_DISPATCH(widest, (os_launch_hist<BB, 2 * OS_ITEMS_MIN>(st, *keys, n_host, n_dev, hb, end_bit, P, temp)));
-    }
+    auto hist = [&](auto I) {
+        OS_DISPATCH(widest, (os_launch_hist<BB, I.value>(st, *keys, n_host, n_dev, hb, end_bit, P, temp)));
+    };
+    if (!one_tile) OS_ITEMS_DISPATCH(items, hist);
     for (int p = 0; p < P; ++p) {
         const int shift = os_shift(end_bit, P, p);
         const int b = os_width(end_bit, P, p);
         uint32_t *status = temp + OS_STATUS + (size_t)p * tiles * os_radix(widest);
         uint2 *rg = P == 1 ? ranges : nullptr;
-        if (small) {
-            OS_DISPATCH(b, (os_launch_scatter<BB, OS_ITEMS_MIN>(st, *keys, *vals, *keys_alt, *vals_alt, n_host, n_dev,
-                                                                tiles, shift, one_tile ? nullptr : temp + (size_t)p * OS_RADIX,
-                                                                temp + OS_CTR + p, status, err, rg, nranges)));
-        } else {
-            OS_DISPATCH(b, (os_launch_scatter<BB, 2 * OS_ITEMS_MIN>(st, *keys, *vals, *keys_alt, *vals_alt, n_host,
-                                                                    n_dev, tiles, shift, one_tile ? nullptr : temp + (size_t)p * OS_RADIX,
-                                                                    temp + OS_CTR + p, status, err, rg, nranges)));
-        }
+        auto scatter = [&](auto I) {
+            OS_DISPATCH(b, (os_launch_scatter<BB, I.value>(st, *keys, *vals, *keys_alt, *vals_alt, n_host, n_dev, tiles, shift,
+                                                           one_tile ? nullptr : temp + (size_t)p * OS_RADIX,
+                                                           temp + OS_CTR + p, status, err, rg, nranges)));
+        };
+        OS_ITEMS_DISPATCH(items, scatter);
         std::swap(*keys, *keys_alt);
         std::swap(*vals, *vals_alt);
     }

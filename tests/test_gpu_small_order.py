@@ -49,3 +49,24 @@ def test_order_of_few_instances(R, n, views):
         t0 += ((cam.width + 15) // 16) * ((cam.height + 15) // 16)
     st.release()
     st2.release()
+
+
+# 64 views: instances on both sides of the sizes at which the sort's and the
+# scan's tiles grow (128k, 160k, 640k)
+@pytest.mark.parametrize("n", [2048, 2049, 2560, 2561, 10240, 10241])
+def test_order_of_many_views(R, n):
+    import oracle
+    from paper_2411_14974_amd.binding import DeviceScene, make_params
+    rng = np.random.default_rng(n)
+    sc = scenes.convexes_around(rng, scenes.uniform_centres(rng, n), 4, 0)
+    cams = [scenes.orbit_camera(rng, 16, 16) for _ in range(64)]
+    ds = DeviceScene.from_scene(sc, "cuda:0")
+    _, st = R.forward_batch(ds, cams, make_params(), want_state=True)
+    ranges, ids = st.tile_lists()
+    assert st.stats()["pairs"] == len(ids) == int((ranges[:, 1] - ranges[:, 0]).sum()) > n
+    for t in (0, 1, 31, 62, 63):
+        keys = np.array([c.key for c in oracle.preprocess(sc, cams[t])], np.uint64)
+        lst = ids[ranges[t, 0]:ranges[t, 1]] % n
+        assert np.all(np.lexsort((lst, keys[lst])) == np.arange(len(lst))), (n, t)
+        assert set(oracle.tile_candidates(sc, cams[t], 16, 0, 0).tolist()) <= set(lst.tolist())
+    st.release()

@@ -14,6 +14,7 @@
 // child_scale about p_k: points p_k + s (p_j - c), c the point mean; delta is
 // kept, sigma and opacity are scaled, the SH coefficients are copied.
 #include <algorithm>
+#include <type_traits>
 
 #include "common.hpp"
 #include "convexsplat.h"
@@ -29,11 +30,13 @@ enum : uint8_t { DN_PRUNE = 0, DN_KEEP = 1, DN_SPLIT = 2 };
 
 // Point mean and squared radius of a convex in float32: sums in point order,
 // one division by K, squared distances as (dx dx + dy dy) + dz dz.
-__device__ __forceinline__ void centre_radius(const float *p, int K, float &cx, float &cy, float &cz, float &r2)
+template <int K>
+__device__ __forceinline__ void centre_radius(const float *p, float &cx, float &cy, float &cz, float &r2)
 {
     cx = p[0];
     cy = p[1];
     cz = p[2];
+#pragma unroll
     for (int k = 1; k < K; ++k) {
         cx = cx + p[3 * k];
         cy = cy + p[3 * k + 1];
@@ -44,36 +47,55 @@ __device__ __forceinline__ void centre_radius(const float *p, int K, float &cx, 
     cy = cy / fk;
     cz = cz / fk;
     r2 = 0.0f;
+#pragma unroll
     for (int k = 0; k < K; ++k) {
         const float dx = p[3 * k] - cx, dy = p[3 * k + 1] - cy, dz = p[3 * k + 2] - cz;
         r2 = fmaxf(r2, (dx * dx + dy * dy) + dz * dz);
     }
 }
 
-__device__ __forceinline__ uint8_t decide(const float *p, int K, float opacity, float acc, float den,
+template <int K>
+__device__ __forceinline__ uint8_t decide(const float *p, float opacity, float acc, float den,
                                           const cs_densify_params &dp)
 {
     float cx, cy, cz, r2;
-    centre_radius(p, K, cx, cy, cz, r2);
+    centre_radius<K>(p, cx, cy, cz, r2);
     if (opacity < dp.opacity_min || r2 > dp.size_max * dp.size_max) return DN_PRUNE;
     if (den > 0.0f && acc / den > dp.split_threshold) return DN_SPLIT;
     return DN_KEEP;
 }
 
-__global__ __launch_bounds__(DN_BLOCK) void densify_classify_kernel(int n, int K, const float *__restrict__ points,
+// One convex per thread; the points arrive through LDS as a coalesced run (odd
+// row stride; read by each thread from its own row, 1M convexes take 46 us
+// instead of 16).
+template <int K>
+__global__ __launch_bounds__(DN_BLOCK) void densify_classify_kernel(int n, const float *__restrict__ points,
                                                                     const float *__restrict__ opacity,
                                                                     const float *__restrict__ accum,
                                                                     const float *__restrict__ denom,
                                                                     cs_densify_params dp, uint8_t *__restrict__ code,
                                                                     uint32_t *__restrict__ blk)
 {
+    constexpr int PK = 3 * K, PS = PK | 1;
+    __shared__ float s_p[DN_BLOCK * PS];
     __shared__ uint32_t s_cnt[2];
     if (threadIdx.x < 2) s_cnt[threadIdx.x] = 0;
+    const int base = blockIdx.x * DN_BLOCK, i = base + threadIdx.x, last = min(i, n - 1);
+    const float op = opacity[last], ac = accum[last], de = denom[last];
+    const int total = min(DN_BLOCK, n - base) * PK;
+    const float *src = points + (size_t)base * PK;
+    float v[PK];
+#pragma unroll
+    for (int u = 0; u < PK; ++u) v[u] = src[min((int)threadIdx.x + u * DN_BLOCK, total - 1)];
+#pragma unroll
+    for (int u = 0; u < PK; ++u) {
+        const int j = threadIdx.x + u * DN_BLOCK;
+        s_p[(j / PK) * PS + j % PK] = v[u];
+    }
     __syncthreads();
-    const int i = blockIdx.x * DN_BLOCK + threadIdx.x;
     uint8_t c = DN_PRUNE;
     if (i < n) {
-        c = decide(points + (size_t)i * 3 * K, K, opacity[i], accum[i], denom[i], dp);
+        c = decide<K>(s_p + threadIdx.x * PS, op, ac, de, dp);
         code[i] = c;
     }
     const uint32_t nk = (uint32_t)__popcll(__ballot(i < n && c == DN_KEEP));
@@ -125,13 +147,16 @@ __global__ __launch_bounds__(DN_SCAN_THREADS) void densify_scan_kernel(int nb, u
     }
 }
 
+template <int V> struct Vec { typedef float type __attribute__((ext_vector_type(V))); };
+template <> struct Vec<1> { typedef float type; };
+
 // for j in [threadIdx.x, total) in steps of DN_BLOCK: store(j, load(j)), with
 // U loads of a thread issued before their stores (a plain copy loop waits for
 // each load in turn: the stores might alias the next loads).
-template <int U, typename L, typename S> __device__ __forceinline__ void batched_for(int total, L load, S store)
+template <int U, typename T, typename L, typename S> __device__ __forceinline__ void batched_for(int total, L load, S store)
 {
     for (int j0 = threadIdx.x; j0 < total; j0 += U * DN_BLOCK) {
-        float v[U];
+        T v[U];
 #pragma unroll
         for (int u = 0; u < U; ++u) v[u] = load(min(j0 + u * DN_BLOCK, total - 1)); // unconditional loads
 #pragma unroll
@@ -142,12 +167,29 @@ template <int U, typename L, typename S> __device__ __forceinline__ void batched
     }
 }
 
+// Rows of W floats to the contiguous rows at dst: output row q is row from(q)
+// of src, in accesses of V floats that each go past the caches (the scene is
+// read once and written once).
+template <int W, int V, typename F>
+__device__ __forceinline__ void copy_rows(float *__restrict__ dst, const float *__restrict__ src, int rows, F from)
+{
+    typedef typename Vec<V>::type T;
+    constexpr int WV = W / V;
+    batched_for<V == 1 ? 8 : 4, T>(rows * WV, [&](int j) {
+        const int q = j / WV, e = j - q * WV;
+        return __builtin_nontemporal_load(reinterpret_cast<const T *>(src + (size_t)from(q) * W) + e);
+    }, [&](int j, T x) { __builtin_nontemporal_store(x, reinterpret_cast<T *>(dst) + j); });
+}
+
 // The block's kept convexes go to one contiguous run of output rows and its
 // children to another, so the rows are copied cooperatively (consecutive
-// threads, consecutive floats) from LDS lists of the block's kept and split
-// convexes.
+// threads, consecutive accesses) from LDS lists of the block's kept and split
+// convexes; VEC: every array is 16-byte aligned, so rows go in the widest
+// accesses that their length allows.  HBM-bound; 1M convexes, K = 6, degree 3,
+// 5 % split (0.65 GB): 118 us, in single floats through the caches 169.
+template <int K, bool VEC>
 __global__ __launch_bounds__(DN_BLOCK) void densify_scatter_kernel(
-    int n, int K, int nsh, const float *__restrict__ points, const float *__restrict__ delta,
+    int n, int nsh, const float *__restrict__ points, const float *__restrict__ delta,
     const float *__restrict__ sigma, const float *__restrict__ opacity, const float *__restrict__ sh,
     const uint8_t *__restrict__ code, const uint32_t *__restrict__ blk, const uint32_t *__restrict__ tot,
     cs_densify_params dp, cs_scene_out out)
@@ -175,33 +217,33 @@ __global__ __launch_bounds__(DN_BLOCK) void densify_scatter_kernel(
         nk += s_wk[v];
         ns += s_ws[v];
     }
-    const int PK = 3 * K;
+    constexpr int PK = 3 * K;
     if (c == DN_KEEP) s_keep[lk] = (uint32_t)i;
     if (c == DN_SPLIT) {
         s_split[ls] = (uint32_t)i;
         float cx, cy, cz, r2;
-        centre_radius(points + (size_t)i * PK, K, cx, cy, cz, r2);
+        centre_radius<K>(points + (size_t)i * PK, cx, cy, cz, r2);
         s_c[3 * ls] = cx;
         s_c[3 * ls + 1] = cy;
         s_c[3 * ls + 2] = cz;
     }
     __syncthreads();
     const size_t kbase = blk[2 * blockIdx.x], sbase = (size_t)tot[0] + (size_t)K * blk[2 * blockIdx.x + 1];
+    constexpr int PV = !VEC ? 1 : PK % 4 == 0 ? 4 : PK % 2 == 0 ? 2 : 1;
+    // SH rows of either kind (their length: by degree)
+    auto sh_rows = [&](size_t row, int rows, auto from) {
+        float *dst = out.sh + row * nsh;
+        switch (nsh) {
+        case 3: copy_rows<3, 1>(dst, sh, rows, from); break;
+        case 12: copy_rows<12, VEC ? 4 : 1>(dst, sh, rows, from); break;
+        case 27: copy_rows<27, 1>(dst, sh, rows, from); break;
+        default: copy_rows<48, VEC ? 4 : 1>(dst, sh, rows, from); break;
+        }
+    };
     // kept rows
-    batched_for<8>((int)nk * PK, [&](int j) {
-        const int r = j / PK, e = j - r * PK;
-        return points[(size_t)s_keep[r] * PK + e];
-    }, [&](int j, float x) {
-        const int r = j / PK, e = j - r * PK;
-        out.points[(kbase + r) * PK + e] = x;
-    });
-    batched_for<8>((int)nk * nsh, [&](int j) {
-        const int r = j / nsh, e = j - r * nsh;
-        return sh[(size_t)s_keep[r] * nsh + e];
-    }, [&](int j, float x) {
-        const int r = j / nsh, e = j - r * nsh;
-        out.sh[(kbase + r) * nsh + e] = x;
-    });
+    auto kept = [&](int q) { return s_keep[q]; };
+    copy_rows<PK, PV>(out.points + kbase * PK, points, (int)nk, kept);
+    sh_rows(kbase, (int)nk, kept);
     for (int r = threadIdx.x; r < (int)nk; r += DN_BLOCK) {
         const uint32_t src = s_keep[r];
         out.delta[kbase + r] = delta[src];
@@ -212,22 +254,32 @@ __global__ __launch_bounds__(DN_BLOCK) void densify_scatter_kernel(
     // children: row q = t K + k is child k of the block's t-th split convex,
     // the convex scaled by child_scale about its point k
     const float s = dp.child_scale;
-    batched_for<8>((int)ns * K * PK, [&](int j) {
+    batched_for<8, float>((int)ns * K * PK, [&](int j) {
         const int q = j / PK, e = j - q * PK;
         const int t = q / K, k = q - t * K, d = e % 3;
         const float *p = points + (size_t)s_split[t] * PK;
         return p[3 * k + d] + s * (p[e] - s_c[3 * t + d]);
     }, [&](int j, float x) { out.points[sbase * PK + j] = x; });
-    batched_for<8>((int)ns * K * nsh, [&](int j) {
-        const int q = j / nsh, e = j - q * nsh;
-        return sh[(size_t)s_split[q / K] * nsh + e];
-    }, [&](int j, float x) { out.sh[sbase * nsh + j] = x; });
+    sh_rows(sbase, (int)ns * K, [&](int q) { return s_split[q / K]; });
     for (int q = threadIdx.x; q < (int)ns * K; q += DN_BLOCK) {
         const uint32_t src = s_split[q / K];
         out.delta[sbase + q] = delta[src];
         out.sigma[sbase + q] = sigma[src] * dp.child_sigma_scale;
         out.opacity[sbase + q] = opacity[src] * dp.child_opacity_scale;
         out.src[sbase + q] = (int32_t)src;
+    }
+}
+
+// f(std::integral_constant<int, K>) for a checked K in 3..8.
+template <typename F> void with_k(int K, F f)
+{
+    switch (K) {
+    case 3: f(std::integral_constant<int, 3>{}); break;
+    case 4: f(std::integral_constant<int, 4>{}); break;
+    case 5: f(std::integral_constant<int, 5>{}); break;
+    case 6: f(std::integral_constant<int, 6>{}); break;
+    case 7: f(std::integral_constant<int, 7>{}); break;
+    default: f(std::integral_constant<int, 8>{}); break;
     }
 }
 
@@ -297,8 +349,10 @@ int cs_densify(cs_ctx *ctx, const cs_scene *sc, const float *accum, const float 
     uint8_t *code = reinterpret_cast<uint8_t *>(scratch);
     uint32_t *blk = reinterpret_cast<uint32_t *>(code + code_bytes), *tot = blk + 2 * (size_t)nb;
     const float *points = static_cast<const float *>(sc->points);
-    hipLaunchKernelGGL(densify_classify_kernel, dim3(nb), dim3(DN_BLOCK), 0, st, n, K, points,
-                       static_cast<const float *>(sc->opacity), accum, denom, *dp, code, blk);
+    with_k(K, [&](auto k) {
+        hipLaunchKernelGGL(densify_classify_kernel<k.value>, dim3(nb), dim3(DN_BLOCK), 0, st, n, points,
+                           static_cast<const float *>(sc->opacity), accum, denom, *dp, code, blk);
+    });
     hipLaunchKernelGGL(densify_scan_kernel, dim3(1), dim3(DN_SCAN_THREADS), 0, st, nb, blk, tot);
     uint32_t *hw = ctx->ring.h_word + 8;
     e = hipMemcpyAsync(hw, tot, 8, hipMemcpyDeviceToHost, st);
@@ -318,10 +372,18 @@ int cs_densify(cs_ctx *ctx, const cs_scene *sc, const float *accum, const float 
         (void)hipFreeAsync(scratch, st);
         return fail(CS_EINVAL, "output array pointer is NULL");
     }
-    hipLaunchKernelGGL(densify_scatter_kernel, dim3(nb), dim3(DN_BLOCK), 0, st, n, K, nsh, points,
-                       static_cast<const float *>(sc->delta), static_cast<const float *>(sc->sigma),
-                       static_cast<const float *>(sc->opacity), static_cast<const float *>(sc->sh), code, blk, tot,
-                       *dp, *out);
+    bool vec = true;
+    for (const void *q : {(const void *)points, (const void *)sc->sh, (const void *)out->points, (const void *)out->sh})
+        vec = vec && ((uintptr_t)q & 15u) == 0;
+    with_k(K, [&](auto k) {
+        auto launch = [&](auto kern) {
+            hipLaunchKernelGGL(kern, dim3(nb), dim3(DN_BLOCK), 0, st, n, nsh, points, static_cast<const float *>(sc->delta),
+                               static_cast<const float *>(sc->sigma), static_cast<const float *>(sc->opacity),
+                               static_cast<const float *>(sc->sh), code, blk, tot, *dp, *out);
+        };
+        if (vec) launch(densify_scatter_kernel<k.value, true>);
+        else launch(densify_scatter_kernel<k.value, false>);
+    });
     e = hipGetLastError();
     (void)hipFreeAsync(scratch, st);
     return e == hipSuccess ? CS_OK : fail(CS_EHIP, "densify launch: %s", hipGetErrorString(e));

@@ -378,8 +378,12 @@ __global__ __launch_bounds__(PF_BLOCK) void preprocess_fwd_kernel(
                 pixel_span(bx0 - mg, bx1 + mg, cam.W, u0, u1);
                 pixel_span(by0 - mg, by1 + mg, cam.H, v0, v1);
                 if (u0 <= u1 && v0 <= v1) {
-                    tx0 = u0 / ra.tile; tx1 = u1 / ra.tile;
-                    ty0 = v0 / ra.tile; ty1 = v1 / ra.tile;
+                    // (tiles are 8, 16 or 32 pixels: shifts, where a division by
+                    // a value that the compiler does not know is some 25 instructions,
+                    // twice in every row of tiles below)
+                    const int ts = __builtin_ctz((uint32_t)ra.tile);
+                    tx0 = u0 >> ts; tx1 = u1 >> ts;
+                    ty0 = v0 >> ts; ty1 = v1 >> ts;
                     h.box_u = (uint32_t)u0 | ((uint32_t)u1 << 16);
                     h.box_v = (uint32_t)v0 | ((uint32_t)v1 << 16);
                     // Drop the tiles where one line keeps x2 above the skip
@@ -418,8 +422,8 @@ __global__ __launch_bounds__(PF_BLOCK) void preprocess_fwd_kernel(
                         uint64_t m = big ? BIG_EMPTY : 0ull;
                         for (int ty = ty0, r = 0; ty <= ty1; ty += bh, ++r) {
                             const int tyb = min(ty + bh - 1, ty1);
-                            const double c0 = (double)max(ty * ra.tile, v0) + 0.5 - oy;
-                            const double c1 = (double)min(tyb * ra.tile + ra.tile - 1, v1) + 0.5 - oy;
+                            const double c0 = (double)max(ty << ts, v0) + 0.5 - oy;
+                            const double c1 = (double)min(((tyb + 1) << ts) - 1, v1) + 0.5 - oy;
                             double xlo = -INFINITY, xhi = INFINITY; // kept pixel centres, origin-relative
                             bool none = false;
 #pragma unroll
@@ -434,7 +438,7 @@ __global__ __launch_bounds__(PF_BLOCK) void preprocess_fwd_kernel(
                             const double ulo = fmax(ceil(xlo + ox - 0.5), (double)u0);
                             const double uhi = fmin(floor(xhi + ox - 0.5), (double)u1);
                             if (none || !(ulo <= uhi)) continue;
-                            const int kx0 = (int)ulo / ra.tile - tx0, kx1 = (int)uhi / ra.tile - tx0;
+                            const int kx0 = ((int)ulo >> ts) - tx0, kx1 = ((int)uhi >> ts) - tx0;
                             if (big) {
                                 m = (m & ~(BIG_FIELD << (2 * BIG_BITS * r))) | big_field(kx0 / bw, kx1 / bw, r);
                             } else {

@@ -369,22 +369,24 @@ __device__ __forceinline__ void pipe_store_records(const u32x4 (&pre)[NL], uint4
 // (workgroups are dealt to the 8 XCDs round-robin), so neighbouring tiles, which
 // share convex records, meet in one L2, and steals from the other bands when
 // its own runs dry.  Every workgroup exits once all bands are through.
-// CHUNK items are claimed at once (the workgroup keeps the rest of its run in
-// cnext..cend).  A claim's round trip is a microsecond or two: a workgroup's
+// Items are claimed one at a time: tiles differ by a factor of four and a
+// workgroup takes only a few (1.7 tiles each at 979 x 546), so runs of two cost
+// more in balance than they save in claims (forward, 317k convexes there 98 -> 78 us,
+// 1M at 1920 x 1080 176 -> 167).  A claim's round trip is a microsecond or two: a workgroup's
 // first items are its own by its index, without a claim, and a band whose items
 // are all given out that way is not claimed from (a 128 x 128 view of one convex:
 // 20 -> 11 us).  A claim made ahead, while the last item is worked on, is no gain: it ties an
 // item to a workgroup that may be long busy (100k convexes at 1297 x 840: 0.102
 // -> 0.139 ms).
-template <uint32_t CHUNK> struct Claims {
+struct Claims {
     uint32_t *queues;
     uint32_t total;
     int q, tried;         // the band that items are taken from, bands found dry
     bool first;
-    uint32_t cnext, cend;
+    uint32_t item;
 
     __device__ __forceinline__ Claims(uint32_t *queues_, uint32_t total_)
-        : queues(queues_), total(total_), q(blockIdx.x % NUM_QUEUES), tried(0), first(true), cnext(0), cend(0)
+        : queues(queues_), total(total_), q(blockIdx.x % NUM_QUEUES), tried(0), first(true), item(0)
     {
     }
     __device__ __forceinline__ uint32_t per() const { return (total + NUM_QUEUES - 1) / NUM_QUEUES; }
@@ -393,30 +395,27 @@ template <uint32_t CHUNK> struct Claims {
     // items of a band that belong to workgroups by their index
     __device__ __forceinline__ uint32_t given(int b) const
     {
-        return CHUNK * ((gridDim.x + (uint32_t)(NUM_QUEUES - 1 - b)) / NUM_QUEUES);
+        return (gridDim.x + (uint32_t)(NUM_QUEUES - 1 - b)) / NUM_QUEUES;
     }
     __device__ __forceinline__ bool take(uint32_t k) // item k of band q
     {
         if (k >= size(q)) return false;
-        cnext = lo(q) + k;
-        cend = lo(q) + min(size(q), k + CHUNK);
+        item = lo(q) + k;
         return true;
     }
     // thread 0 only
     __device__ __forceinline__ uint32_t one()
     {
-        if (cnext < cend) return cnext++;
-        bool got = first && take(CHUNK * (blockIdx.x / NUM_QUEUES));
+        bool got = first && take(blockIdx.x / NUM_QUEUES);
         first = false;
         while (!got && tried < NUM_QUEUES) {
-            if (given(q) < size(q)) got = take(given(q) + atomicAdd(&queues[QUEUE_STRIDE * q], CHUNK));
+            if (given(q) < size(q)) got = take(given(q) + atomicAdd(&queues[QUEUE_STRIDE * q], 1u));
             if (!got) {
                 q = (q + 1) % NUM_QUEUES;
                 ++tried;
             }
         }
-        if (!got) return 0xFFFFFFFFu;
-        return cnext++;
+        return got ? item : 0xFFFFFFFFu;
     }
     // The next item, for the whole workgroup (0xFFFFFFFF: none left).
     __device__ __forceinline__ uint32_t next(uint32_t *s_item)
@@ -425,9 +424,9 @@ template <uint32_t CHUNK> struct Claims {
         __syncthreads();
         // a scalar: what hangs on the item (view, cell, list, image size) then stays
         // in scalar registers
-        const uint32_t item = (uint32_t)__builtin_amdgcn_readfirstlane((int)*s_item);
+        const uint32_t i = (uint32_t)__builtin_amdgcn_readfirstlane((int)*s_item);
         __syncthreads();
-        return item;
+        return i;
     }
 };
 
@@ -551,10 +550,6 @@ __device__ __forceinline__ void store_work_counts(unsigned long long *evalcount,
 
 } // namespace
 
-// Tiles the forward claims per queue atomic: its per-tile cost is even enough
-// that runs of 2 balance; the backward's varies more and claims one at a time.
-constexpr uint32_t FWD_CHUNK = 2;
-
 // 5 wavefronts per SIMD (at most 96 VGPRs): the compiler keeps a few values
 // of the batch loop (one record prefetch register among them) in scratch,
 // outside the record loop, and the extra wavefront hides more of the LDS and
@@ -588,7 +583,7 @@ __global__ __launch_bounds__(TILE *TILE) __attribute__((amdgpu_waves_per_eu(fwd_
     const ViewDesc *views = reinterpret_cast<const ViewDesc *>(frame + 1);
     const int nviews = (int)frame->nviews;
     const uint32_t total_tiles = frame->total_tiles;
-    Claims<FWD_CHUNK> claims(queues, total_tiles);
+    Claims claims(queues, total_tiles);
     // work counters: pairs tested / pairs past the max-line test (the hull
     // sizes and wavefront evaluations of the same pairs are counted by the
     // backward walk, where they cost less)
@@ -835,7 +830,7 @@ __global__ __launch_bounds__(TILE *TILE) __attribute__((amdgpu_waves_per_eu(K <=
     const int nviews = (int)frame->nviews;
     const uint32_t total_tiles = frame->total_tiles;
     const int lane = threadIdx.x & 63, wbit = threadIdx.x >> 6;
-    Claims<1> claims(queues, total_tiles);
+    Claims claims(queues, total_tiles);
     uint32_t nfull = 0, nsumT = 0, nwave = 0;
     TileFeed<NT, RING, true> feed;
     for (;;) {
@@ -959,7 +954,7 @@ __global__ __launch_bounds__(TILE *TILE) __attribute__((amdgpu_waves_per_eu(K <=
 // All four wavefronts composite every record, and a record is loaded and tested
 // for every square instead of every tile: where the chip is full it takes 2.3
 // times as long (1M convexes, 1920 x 1080: forward 175 -> 412 us, backward 313 ->
-// 782), so it is for views whose squares do not fill the chip (SPLIT_PIXELS).
+// 782), so it is for views whose squares do not fill the chip (split_by_record).
 constexpr int SPLIT = 8;
 constexpr float NOT_FULL = -1.0f, NOT_TESTED = -2.0f; // in place of alpha
 
@@ -999,7 +994,7 @@ __global__ __launch_bounds__(256) void render_fwd_split_kernel(
     const ViewDesc *views = reinterpret_cast<const ViewDesc *>(frame + 1);
     const int nviews = (int)frame->nviews;
     const uint32_t side = (uint32_t)ra.tile / 8u, total = frame->total_tiles * side * side;
-    Claims<1> claims(queues, total);
+    Claims claims(queues, total);
     uint32_t nevals = 0, nfull = 0;
     const uint32_t zper = total ? (zero_n4 + total - 1) / total : 0u;
     int buf = 0;
@@ -1139,7 +1134,7 @@ __global__ __launch_bounds__(256) void render_bwd_split_kernel(
     const int nviews = (int)frame->nviews;
     const uint32_t side = (uint32_t)ra.tile / 8u, total = frame->total_tiles * side * side;
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-    Claims<1> claims(queues, total);
+    Claims claims(queues, total);
     uint32_t nfull = 0, nsumT = 0, nwave = 0;
     TileFeed<NT, RING, true> feed;
     int buf = 0;

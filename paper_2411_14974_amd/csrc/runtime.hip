@@ -568,12 +568,12 @@ static int wait_pair_count(const HostRing &ring, uint32_t tag, hipStream_t st, u
 
 // Up to this many pixels in all views of a call the compositing is split by
 // record (see render.hip): its squares then do not fill the chip, or only a few
-// times over.  K = 6, forward (us, by tile / by record): 400x250 121 / 74, 480x330
-// 112 / 84, 560x360 95 / 89, 640x400 87 / 96; K = 4: 560x360 112 / 89, 720x450
-// 102 / 106.  The backward holds two records' values a wavefront, at K = 6 in
-// twice the registers of K = 4's tile kernel: 400x250 126 / 119, 450x300 129 /
-// 137; K = 4: 560x360 156 / 141, 640x427 139 / 155.
-constexpr size_t SPLIT_PIXELS = 200 * 1024, SPLIT_PIXELS_BWD = 100 * 1024;
+// times over.  Forward / backward by tile against by record (us): K = 6, 100k convexes,
+// 320x210 93/152 - 74/101, 400x250 87/154 - 65/111, 480x330 70/127 - 76/125, 560x360
+// 68/122 - 81/139; K = 8, 480x330 70/124 - 72/122, 560x360 69/121 - 76/137.  Few
+// lines make a record's evaluation cheap and leave room for two: K = 4, 20k, 560x360
+// 64/127 - 58/81, 640x400 47/88 - 60/88.
+inline bool split_by_record(int K, size_t pixels) { return pixels <= (K <= 4 ? 208u : 128u) * 1024u; }
 
 // Forward pass on frame F.  device_count: the pair count stays on the device
 // (fixed capacities, graph capture); otherwise it is read back to size the
@@ -590,7 +590,7 @@ int enqueue_forward(cs_ctx *ctx, Frame &F, const cs_scene *sc, const RenderArgs 
     // cells that the buffers and the cell sort provide for: this call's, or (graph
     // capture, replayed with other resolutions) any that its tiles can form
     const size_t ncells = device_count ? F.cap_cells() : F.cells;
-    const bool split_fwd = F.pixels <= SPLIT_PIXELS;
+    const bool split = split_by_record(F.K, F.pixels);
     const int sort_bits = std::max(1, ilog2_ceil(ncells));
     // The clearing of the frame's counters, the sort temporaries and the tile
     // ranges rides on the kernels before their users (preprocess, pair scan,
@@ -672,7 +672,7 @@ int enqueue_forward(cs_ctx *ctx, Frame &F, const cs_scene *sc, const RenderArgs 
         tm.begin();
         F.eval_slots = launch_render_fwd(st, F.K, kn.tile, F.d_frame, F.order, (uint32_t)F.cap_tiles, F.counters + CNT_QUEUE, F.ranges,
                           F.sorted_keys, F.sorted_ids, F.records, ra, F.pixstate, F.evalcount, zero_acc ? F.acc : nullptr,
-                          zero_acc ? F.ninst * acc_stride(F.K) : 0, split_fwd);
+                          zero_acc ? F.ninst * acc_stride(F.K) : 0, split);
         tm.end(CS_STAGE_RENDER_FWD);
     };
 
@@ -753,7 +753,7 @@ int enqueue_backward(Frame &F, const cs_scene *sc, const cs_grads *g, const Rend
     tm.begin();
     F.eval_slots_bwd = launch_render_bwd(st, F.K, F.tile, F.d_frame_b, F.order, (uint32_t)F.cap_tiles, F.counters + CNT_QUEUE_B,
                                          F.ranges, F.sorted_keys, F.sorted_ids, F.records, ra, F.pixstate, F.acc,
-                                         F.evalcount + (size_t)EVAL_SLOTS * EVAL_FIELDS, F.pixels <= (F.K <= 4 ? SPLIT_PIXELS : SPLIT_PIXELS_BWD));
+                                         F.evalcount + (size_t)EVAL_SLOTS * EVAL_FIELDS, split_by_record(F.K, F.pixels));
     tm.end(CS_STAGE_RENDER_BWD);
     tm.begin();
     launch_preprocess_bwd(st, sc->n, F.V, F.K, F.deg, sc->dtype, sc->points, sc->delta, sc->sigma, sc->sh, F.d_frame_b,

@@ -1124,6 +1124,11 @@ int cs_render_forward_batch(cs_ctx *ctx, const cs_scene *sc, int32_t n_views, co
             StageTimer off(ctx, st, false);
             CS_TRY(capture_graph(ctx, *F, &F->gfwd, [&] { return enqueue_forward(ctx, *F, sc, ra, kn, true, 1.0, off); }));
             F->gfwd_zero = F->acc != nullptr;
+            // the captured sort provides for other resolutions and may leave its lists in
+            // the other pair of buffers than the eager first frame's did, which a
+            // backward captured since then reads
+            if (F->gbwd) { (void)hipGraphExecDestroy(F->gbwd); F->gbwd = nullptr; }
+            if (F->gbwd_nz) { (void)hipGraphExecDestroy(F->gbwd_nz); F->gbwd_nz = nullptr; }
         }
         tm.begin();
         CS_HIP(hipGraphLaunch(F->gfwd, st));

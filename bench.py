@@ -71,12 +71,14 @@ def stage_work(stage, n, m, K, deg, cnt):
         return "hbm", n * (4 + 4 * 16)
     if stage == "bin_scan":  # read id 4 + binning record 16; write it in depth order 16 + count 4 + offset 4
         return "hbm", n * 44
+    # the pairs that are emitted and sorted are (cell, convex) pairs, of which there
+    # is at least one for every 16 (tile, convex) pairs m, the count at hand
     if stage == "emit":  # per convex: id, offset, binning record 24 B; per pair: write 8 B
-        return "hbm", n * 24 + m * 8
-    if stage == "tile_sort":  # one histogram read (4 B) + 2 passes x (read 8 B + write 8 B) over the pairs
-        return "hbm", m * (4 + 2 * 16)
+        return "hbm", n * 24 + m // 16 * 8
+    if stage == "tile_sort":  # one histogram read (4 B) + one pass x (read 8 B + write 8 B) over the pairs
+        return "hbm", m // 16 * (4 + 16)
     if stage == "ranges":
-        return "hbm", m * 4
+        return "hbm", m // 16 * 4
     if stage == "render_fwd":  # full pairs x the forward per-pair cost at the measured mean hull size
         return "alu", cnt["full"] * pair_cost(stage, T_mean)
     if stage == "render_bwd":

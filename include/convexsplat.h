@@ -12,7 +12,8 @@
  *     frees them.  The library owns cs_ctx, cs_fwd_state and their workspace.
  *   - Work is enqueued on `hip_stream` (a hipStream_t; NULL = the null stream)
  *     in stream order.  cs_render_forward makes one host synchronisation: a
- *     4-byte read of the number of (convex, tile) pairs to size its buffers.
+ *     read of the numbers of (cell, convex) and (tile, convex) pairs to size its
+ *     buffers (a cell: a block of up to 4x4 tiles that share a list).
  *   - A context is used by one host thread and one stream at a time; separate
  *     contexts are independent.
  *   - Return value 0 = success, a negative CS_E* code otherwise; no exception
@@ -102,10 +103,11 @@ typedef struct {
 enum {
     CS_STAGE_PREPROCESS = 0, /* per-convex projection, hull, lines, colour, key, tile rectangle */
     CS_STAGE_DEPTH_SORT,     /* radix sort of the convexes by depth key */
-    CS_STAGE_BIN_SCAN,       /* tile counts in depth order and their exclusive scan */
-    CS_STAGE_EMIT,           /* (tile, convex) pair emission */
-    CS_STAGE_TILE_SORT,      /* stable radix sort of the pairs by tile */
-    CS_STAGE_RANGES,         /* per-tile list ranges */
+    CS_STAGE_BIN_SCAN,       /* cell counts in depth order and their exclusive scan (up to 8192
+                              * instances: done by the depth sort's kernel) */
+    CS_STAGE_EMIT,           /* (cell, convex) pair emission, with the kept tiles of each cell */
+    CS_STAGE_TILE_SORT,      /* stable radix sort of the pairs by cell */
+    CS_STAGE_RANGES,         /* per-cell list ranges, where the sort does not leave them */
     CS_STAGE_RENDER_FWD,     /* per-tile forward compositing */
     CS_STAGE_RENDER_BWD,     /* per-tile backward compositing */
     CS_STAGE_PREPROCESS_BWD, /* per-convex backward chain rule */
@@ -155,7 +157,7 @@ int cs_render_forward(cs_ctx *ctx, const cs_scene *scene, const cs_camera *cam, 
  * carved from one static device array of CS_NOALLOC_SCRATCH_BYTES that each
  * device holds from its first cs_create until the process ends.  The call
  * makes no device allocation or free; like cs_render_forward it waits for the
- * 4-byte pair count (read into pinned memory made by cs_create), so it cannot
+ * pair counts (read into pinned memory made by cs_create), so it cannot
  * be captured into a graph.
  *   out_rgb: [height][width][3] device, written.  Stream-ordered on hip_stream.
  *   Limits: the per-convex buffers (about 250 B per convex), the per-tile and
@@ -393,7 +395,9 @@ int cs_densify(cs_ctx *ctx, const cs_scene *scene, const float *accum, const flo
  * 3DGS convention the paper follows).  Writes dl_drgb = dL/drgb ([h][w][3],
  * DEVICE) and ADDS L to *loss (DEVICE, one float; the caller zeroes it).  The
  * mask term of the equation belongs to a learnable-mask extension that this
- * rasterizer does not have.  Uses 36 bytes per pixel of stream-ordered scratch. */
+ * rasterizer does not have.  Uses
+ * stream-ordered scratch: one float per workgroup, and 36 bytes per pixel for images
+ * of 96k to 512k pixels (12 where dl_drgb overlaps an input). */
 int cs_ssim_loss_grad(cs_ctx *ctx, const float *rgb, const float *target, int32_t width, int32_t height, float lambda,
                       float *dl_drgb, float *loss, void *hip_stream);
 
@@ -435,7 +439,8 @@ int cs_adam_step(cs_ctx *ctx, int32_t n, int32_t k, int32_t sh_degree, const cs_
  * are).  delta, sigma, opacity take the given initial (activated) values; SH
  * coefficient 0 reproduces rgb (nullable: grey 0.5), the others are 0.
  * xyz, rgb: DEVICE [n][3]; out: DEVICE arrays of the scene's shapes.  The
- * neighbour search is exact and brute force: O(n^2). */
+ * neighbour search is exact (a curve-ordered search with box bounds; ties and
+ * results as if every pair were compared). */
 typedef struct {
     float radius_scale; /* paper: 1.2 */
     float radius_min;   /* floor of the mean distance (coincident cloud points) */

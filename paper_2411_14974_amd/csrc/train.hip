@@ -404,9 +404,9 @@ int ssim_rows(int strips, int H, int cus)
 // Pixels of the images that go through the tiles.  A strip's step costs about a
 // microsecond however few workgroups run, which tiles undercut while the image
 // fills the chip but a few times over (us, strips / tiles: 200x120 29 / 33,
-// 400x300 34 / 32, 640x427 41 / 34, 979x546 51 / 52, 1297x840 72 / 83,
-// 1920x1080 109 / 147).
-constexpr size_t SS_TILES_FROM = 96 * 1024, SS_TILES_TO = 512 * 1024;
+// 400x300 34 / 32, 640x427 41 / 34, 900x600 56 / 54, 979x546 55 / 55, 1000x640 60 / 58,
+// 1100x700 64 / 68, 1297x840 72 / 83, 1920x1080 109 / 147).
+constexpr size_t SS_TILES_FROM = 96 * 1024, SS_TILES_TO = 656 * 1024;
 
 __global__ __launch_bounds__(256) void copy_floats_kernel(size_t n, const float *__restrict__ from, float *__restrict__ to)
 {

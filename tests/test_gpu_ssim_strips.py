@@ -25,7 +25,7 @@ def images(w, h):
     return x, np.clip(x + rng.normal(0, 0.1, x.shape), 0, 1).astype(np.float32)
 
 
-@pytest.mark.parametrize("w,h", [(1, 1), (1, 40), (5, 3), (75, 11), (76, 12), (151, 64), (226, 21), (640, 1), (333, 410), (1000, 530)])
+@pytest.mark.parametrize("w,h", [(1, 1), (1, 40), (5, 3), (75, 11), (76, 12), (151, 64), (226, 21), (640, 1), (333, 410), (1000, 530), (1031, 653)])
 def test_matches_oracle(R, w, h):
     from oracle import losses
     x, y = images(w, h)

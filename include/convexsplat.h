@@ -199,7 +199,8 @@ int cs_state_release(cs_ctx *ctx, cs_fwd_state *state);
  * replays, the scene arrays, n_views, K and the tuning may not (a change
  * re-captures).  A graph replay makes no host synchronisation; a frame whose
  * pairs exceed the capacity is reported by cs_batch_check or the backward call
- * as CS_EOVERFLOW (the buffers have then grown: render the frame again).  In
+ * as CS_EOVERFLOW, each time they are called on it (render the frame again: the
+ * next forward grows the buffers for it).  In
  * graph mode a context holds one batch state at a time: the next batched
  * forward invalidates the previous one. */
 int cs_render_forward_batch(cs_ctx *ctx, const cs_scene *scene, int32_t n_views, const cs_camera *cams,

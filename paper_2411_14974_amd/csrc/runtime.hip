@@ -242,6 +242,8 @@ int Frame::ensure_pairs(size_t m)
                     cap_pairs);
     for (void *p : {(void *)pt, (void *)pi, (void *)pt_alt, (void *)pi_alt, (void *)hist})
         if (p) release_buffer(p);
+    // (should an allocation below fail, the next call allocates again)
+    pt = pi = pt_alt = pi_alt = hist = nullptr;
     cap_pairs = std::max<size_t>(m, 1);
     // sort temporaries: the largest of the depth, tile and tile-order sorts
     // (tile keys sorted in digits of 4 to 8 bits: sized for the most passes)
@@ -250,11 +252,11 @@ int Frame::ensure_pairs(size_t m)
                                 sort_temp_words((uint32_t)cap_pairs, tile_bits, 4),
                                 sort_temp_words((uint32_t)cap_tiles, 16, 8)});
 #define CS_A(ptr, bytes) do { int r_ = alloc((void **)&(ptr), (bytes)); if (r_) return r_; } while (0)
-    CS_A(pt, cap_pairs * 4);
+    CS_A(hist, hw * 4);
     CS_A(pi, cap_pairs * 4);
     CS_A(pt_alt, cap_pairs * 4);
     CS_A(pi_alt, cap_pairs * 4);
-    CS_A(hist, hw * 4);
+    CS_A(pt, cap_pairs * 4); // the last: set where all of them are
 #undef CS_A
     return CS_OK;
 }
@@ -1116,6 +1118,12 @@ int cs_render_forward_batch(cs_ctx *ctx, const cs_scene *sc, int32_t n_views, co
         ctx->batch_key = key;
     } else {
         CS_TRY(F->upload_views(vp.hdr, vp.views.data()));
+        if (F->overflowed) { // the last frame did not fit: room for its pairs, and graphs captured anew on it
+            CS_HIP(hipStreamSynchronize(F->st));
+            F->drop_graphs();
+            CS_TRY(F->ensure_pairs(F->pair_room(F->h_counters[CNT_PAIRS], F->h_counters[CNT_TILE_PAIRS], 1.3)));
+            F->overflowed = false;
+        }
         if (F->gfwd && F->acc && !F->gfwd_zero) { // accumulators appeared: capture again with their clearing
             (void)hipGraphExecDestroy(F->gfwd);
             F->gfwd = nullptr;
@@ -1165,14 +1173,12 @@ int cs_batch_check(cs_ctx *ctx, const cs_fwd_state *s)
     }
     CS_HIP(hipEventSynchronize(F->counters_ev));
     if (F->h_counters[CNT_SORT_ERR]) return fail(CS_EHIP, "radix sort: a look-back wait exceeded its bound");
+    // Reported at every call until the next forward, which grows the buffers: this
+    // state's lists stay where they are, whatever is called on it.
     const uint32_t m = F->h_counters[CNT_TILE_PAIRS];
-    if (F->h_counters[CNT_OVERFLOW] || m > F->cap_tile_pairs) {
-        CS_HIP(hipStreamSynchronize(F->st));
-        F->drop_graphs();
-        int r = F->ensure_pairs(F->pair_room(F->h_counters[CNT_PAIRS], m, 1.3));
-        if (r) return r;
-        return fail(CS_EOVERFLOW, "frame needed %u (convex, tile) pairs; buffers grown, render it again", m);
-    }
+    if (F->h_counters[CNT_OVERFLOW] || m > F->cap_tile_pairs) F->overflowed = true;
+    if (F->overflowed)
+        return fail(CS_EOVERFLOW, "frame needed %u (convex, tile) pairs; render it again, with buffers grown for it", m);
     return CS_OK;
 }
 

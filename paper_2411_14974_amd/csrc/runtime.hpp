@@ -45,6 +45,7 @@ struct Frame {
     uint32_t npairs = 0;
     bool by_tile_pairs = false; // pair buffers sized by the (tile, convex) pairs (pair_room)
     size_t cap_tile_pairs = 0;  // then: the tile pairs of a frame that is not reported as overflowing
+    bool overflowed = false;    // the last frame was reported as overflowing: the next one grows the buffers
     hipStream_t st = nullptr;
     std::vector<void *> allocs;
     size_t bytes_held = 0;

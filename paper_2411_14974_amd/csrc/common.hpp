@@ -137,9 +137,10 @@ constexpr int EVAL_SLOTS = 16384;
 enum : int { EV_TESTED = 0, EV_FULL = 1, EV_SUM_T = 2, EV_WAVES = 3, EVAL_FIELDS = 4 };
 
 // Device counters of one frame (u32 words).
-// Per-instance binning record (16 bytes): the view's cell shift and the tile
-// rectangle, tx0 | shift << 12 | ty0 << 16 and tx1 | ty1 << 16 (empty when tx0 >
-// tx1; a view has at most 2048 tiles a side), and 64 bits of kept tiles:
+// Per-instance binning record (16 bytes): the tile rectangle, tx0 | ty0 << 16
+// and tx1 | ty1 << 16 (empty when tx0 > tx1; a view has at most 2048 tiles a
+// side), the view's cell shift and the number of (cell, convex) pairs in the bits
+// between (bin_cells), and 64 bits of kept tiles:
 //  - a rectangle of at most 64 tiles: the mask of kept tiles (bit
 //    (ty - ty0) * width + (tx - tx0));
 //  - a larger one: its rows are grouped into at most BIG_BANDS bands of
@@ -147,16 +148,36 @@ enum : int { EV_TESTED = 0, EV_FULL = 1, EV_SUM_T = 2, EV_WAVES = 3, EVAL_FIELDS
 //    blocks of ceil(tw / 2^BIG_BITS) tiles; field r (2 BIG_BITS bits) holds
 //    band r's kept blocks as the interval bx0 | bx1 << BIG_BITS (empty when
 //    bx0 > bx1), and the band keeps every tile of those blocks.
-__host__ __device__ inline uint4 make_bin(int tx0, int ty0, int tx1, int ty1, uint64_t mask, uint32_t shift)
+// The cells that hold a kept tile of a rectangle of at most 64 tiles, each by
+// one bit: that of the cell's first tile in the rectangle (kept or not).
+__host__ __device__ inline uint64_t cell_marks(uint64_t mask, uint32_t tx0, uint32_t ty0, uint32_t tw, uint32_t th, uint32_t s)
 {
-    return make_uint4((uint32_t)tx0 | (shift << 12) | ((uint32_t)ty0 << 16), (uint32_t)tx1 | ((uint32_t)ty1 << 16), (uint32_t)mask,
-                      (uint32_t)(mask >> 32));
+    if (s == 0) return mask;
+    const uint32_t side = 1u << s, first = side - (tx0 & (side - 1u)); // columns of the first cell
+    const uint64_t rowmask = tw < 64 ? (1ull << tw) - 1ull : ~0ull;
+    const uint64_t starts = ((s == 1 ? 0x5555555555555555ull : 0x1111111111111111ull) << first) & rowmask; // of the others
+    uint64_t marks = 0;
+    for (uint32_t r = 0, next; r < th; r = next) { // one row of cells: the tile rows r .. next - 1
+        next = ((ty0 + r) | (side - 1u)) + 1u - ty0;
+        next = next < th ? next : th;
+        const uint32_t bits = (next - r) * tw;
+        uint64_t row = (mask >> (r * tw)) & (bits < 64 ? (1ull << bits) - 1ull : ~0ull);
+        if (next - r > 1) { // (tw <= 32) the columns kept in one of them
+            row |= row >> tw;
+            row |= (row >> tw) >> tw;
+            row &= rowmask;
+        }
+        uint64_t any = row | (row >> 1);
+        if (s > 1) any |= any >> 2;
+        marks |= ((any & starts) | ((row & ((1ull << first) - 1ull)) != 0ull ? 1ull : 0ull)) << (r * tw);
+    }
+    return marks;
 }
-__host__ __device__ inline uint32_t bin_shift(uint4 b) { return (b.x >> 12) & 15u; }
-__host__ __device__ inline uint32_t bin_tx0(uint4 b) { return b.x & 0xFFFu; }
-__host__ __device__ inline uint32_t bin_ty0(uint4 b) { return b.x >> 16; }
-__host__ __device__ inline uint32_t bin_tx1(uint4 b) { return b.y & 0xFFFFu; }
-__host__ __device__ inline uint32_t bin_ty1(uint4 b) { return b.y >> 16; }
+__host__ __device__ inline uint32_t bin_shift(uint4 b) { return (b.x >> 11) & 3u; }
+__host__ __device__ inline uint32_t bin_tx0(uint4 b) { return b.x & 0x7FFu; }
+__host__ __device__ inline uint32_t bin_ty0(uint4 b) { return (b.x >> 16) & 0x7FFu; }
+__host__ __device__ inline uint32_t bin_tx1(uint4 b) { return b.y & 0x7FFu; }
+__host__ __device__ inline uint32_t bin_ty1(uint4 b) { return (b.y >> 16) & 0x7FFu; }
 #ifndef CS_BIG_BANDS
 #define CS_BIG_BANDS 4
 #endif
@@ -209,13 +230,52 @@ __device__ inline uint32_t bin_count(uint4 b)
     return c;
 }
 
-// The cells that a binning record's tile rectangle meets: each is one pair (a
-// cell whose kept tiles are all culled included: its mask is empty).
-__device__ inline uint32_t bin_cells(uint4 b)
+// The block of cells that band r of a larger rectangle meets: its first cell
+// and its cells across and down (0 when the band is empty).
+struct CellBlock { uint32_t x, y, nx, ny; };
+__host__ __device__ inline CellBlock band_cells(uint64_t mask, int tx0, int ty0, int tw, int th, int r, uint32_t s)
 {
-    const uint32_t tx0 = bin_tx0(b), ty0 = bin_ty0(b), tx1 = bin_tx1(b), ty1 = bin_ty1(b), s = bin_shift(b);
+    int row0, nrow, col0, ncol;
+    big_band(mask, tw, th, r, &row0, &nrow, &col0, &ncol);
+    const uint32_t x = (uint32_t)(tx0 + col0) >> s, y = (uint32_t)(ty0 + row0) >> s;
+    if (ncol == 0) return {x, y, 0u, 0u};
+    return {x, y, ((uint32_t)(tx0 + col0 + ncol - 1) >> s) - x + 1u, ((uint32_t)(ty0 + row0 + nrow - 1) >> s) - y + 1u};
+}
+// (cell, convex) pairs of a rectangle: one for every cell with a kept tile; of a
+// larger rectangle one for every band that has kept tiles in the cell (each with
+// the band's part of the tiles).  Every pair holds a tile that no other does, so
+// they are never more than the (tile, convex) pairs.
+__host__ __device__ inline uint32_t rect_cells(int tx0, int ty0, int tx1, int ty1, uint64_t mask, uint32_t s)
+{
     if (tx0 > tx1 || ty0 > ty1) return 0u;
-    return ((tx1 >> s) - (tx0 >> s) + 1u) * ((ty1 >> s) - (ty0 >> s) + 1u);
+    const int tw = tx1 - tx0 + 1, th = ty1 - ty0 + 1;
+    if (tw * th <= 64)
+        return (uint32_t)__builtin_popcountll(cell_marks(mask, (uint32_t)tx0, (uint32_t)ty0, (uint32_t)tw, (uint32_t)th, s));
+    uint32_t c = 0;
+#pragma unroll
+    for (int r = 0; r < BIG_BANDS; ++r) {
+        const CellBlock k = band_cells(mask, tx0, ty0, tw, th, r, s);
+        c += k.nx * k.ny;
+    }
+    return c;
+}
+// The record holds the count in 18 bits (all ones: not held), 3 and 5 in x, 5 and 5 in
+// y: counted again by the pair scan, it took that from 31 to 51 us (1M
+// convexes, 1920 x 1080).
+constexpr uint32_t BIN_CELLS_LATER = (1u << 18) - 1u;
+__host__ __device__ inline uint4 make_bin(int tx0, int ty0, int tx1, int ty1, uint64_t mask, uint32_t shift)
+{
+    const uint32_t n = rect_cells(tx0, ty0, tx1, ty1, mask, shift), c = n < BIN_CELLS_LATER ? n : BIN_CELLS_LATER;
+    return make_uint4((uint32_t)tx0 | (shift << 11) | ((c & 7u) << 13) | ((uint32_t)ty0 << 16) | (((c >> 3) & 31u) << 27),
+                      (uint32_t)tx1 | (((c >> 8) & 31u) << 11) | ((uint32_t)ty1 << 16) | ((c >> 13) << 27), (uint32_t)mask,
+                      (uint32_t)(mask >> 32));
+}
+__host__ __device__ inline uint32_t bin_cells(uint4 b)
+{
+    const uint32_t c = ((b.x >> 13) & 7u) | ((b.x >> 27) << 3) | (((b.y >> 11) & 31u) << 8) | ((b.y >> 27) << 13);
+    if (c != BIN_CELLS_LATER) return c;
+    return rect_cells((int)bin_tx0(b), (int)bin_ty0(b), (int)bin_tx1(b), (int)bin_ty1(b),
+                      (uint64_t)b.z | ((uint64_t)b.w << 32), bin_shift(b));
 }
 
 // Up to three word ranges that a kernel clears on the side (each block its

@@ -220,15 +220,15 @@ int Frame::init(int n_, int K_, int deg_, int V_, size_t tiles, size_t pix, hipS
 
 // Pairs to make room for, given the counts of (cell, convex) and (tile, convex)
 // pairs: the cell pairs with a margin.  A graph's frame (by_tile_pairs) is sized
-// by the tile pairs, of which a caller is promised the margin, and a frame past
-// it is reported: then any frame within the promise fits, whatever share of
-// its cells' tiles its convexes reach (surplus workgroups of the grids leave
-// at once).
+// by the tile pairs, of which a caller is promised the margin (never less than
+// before), and a frame past it is reported: a frame never has more cell pairs than tile pairs
+// (bin_cells), so any within the promise fits, whatever share of its cells'
+// tiles its convexes reach (surplus workgroups of the grids leave at once).
 size_t Frame::pair_room(uint32_t cell_pairs, uint32_t tile_pairs, double margin)
 {
     size_t room = (size_t)std::ceil(cell_pairs * margin);
     if (by_tile_pairs) {
-        cap_tile_pairs = (size_t)std::ceil(tile_pairs * margin);
+        cap_tile_pairs = std::max(cap_tile_pairs, (size_t)std::ceil(tile_pairs * margin));
         room = std::max(room, cap_tile_pairs);
     }
     return std::min<size_t>(room, MAX_CELL_PAIRS);

@@ -779,43 +779,66 @@ bool launch_small_order(hipStream_t st, uint32_t n, const uint32_t *keys, const 
 // cooperatively: their pair ranges are contiguous ([offsets[r], offsets[r] +
 // counts[r]) in rank order), so the workgroup strides over the whole run with
 // one pair per thread (coalesced stores).  Within an instance the pairs run
-// row-major over the cells that its tile rectangle meets; a pair's key is the
-// cell with the mask of its kept tiles above (see FrameHeader).  Instance id =
-// view * n_convex + convex.
+// row-major over the cells with kept tiles, band by band in a large rectangle
+// (see bin_cells); a pair's key is the cell with the mask of its kept tiles
+// above (see FrameHeader).  Instance id = view * n_convex + convex.  30 us for 1M
+// convexes at 1920 x 1080 (pairs of every cell that the rectangle meets: 27 us, and
+// 2 us more in their sort).
 constexpr int EMIT_BLOCK = 256;
 constexpr int EMIT_ITEMS = 8;
 constexpr int EMIT_CHUNK = EMIT_BLOCK * EMIT_ITEMS; // pairs whose owners are found per round
 
+// Position of the q-th set bit of m (q < popcount(m)).
+__device__ __forceinline__ uint32_t nth_set_bit(uint64_t m, uint32_t q)
+{
+    uint32_t pos = 0;
+    uint32_t w = (uint32_t)m;
+    const uint32_t c32 = __popc(w);
+    if (q >= c32) { q -= c32; w = (uint32_t)(m >> 32); pos = 32; }
+#pragma unroll
+    for (int half = 16; half >= 1; half >>= 1) {
+        const uint32_t c = __popc(w & ((1u << half) - 1u));
+        if (q >= c) { q -= c; w >>= half; pos += half; }
+    }
+    return pos;
+}
+// q / d for q < 2^24, through the reciprocal, corrected by one step.
+__device__ __forceinline__ uint32_t small_div(uint32_t q, uint32_t d)
+{
+    uint32_t r = (uint32_t)((float)q * __builtin_amdgcn_rcpf((float)d));
+    if (r * d > q) --r;
+    else if ((r + 1u) * d <= q) ++r;
+    return r;
+}
 // The kept tiles of the cell whose first tile is (ctx, cty), one bit per tile
-// row-major over the cell: the rectangle's mask (at most 64 tiles) or its
-// bands' column intervals (larger), cut to the cell.
+// row-major over the cell, of a rectangle of at most 64 tiles.
 __device__ __forceinline__ uint32_t cell_mask(uint64_t mask, int tx0, int ty0, int w, int th, int ctx, int cty,
                                               int shift)
 {
     const int side = 1 << shift;
     const uint32_t sidemask = (1u << side) - 1u;
     const int c0 = ctx - tx0; // the cell's first column, rectangle-relative (may be negative)
+    const uint64_t rowmask = w < 64 ? (1ull << w) - 1ull : ~0ull;
     uint32_t m = 0;
-    if (w * th <= 64) {
-        const uint64_t rowmask = w < 64 ? (1ull << w) - 1ull : ~0ull;
-        for (int sy = 0; sy < side; ++sy) {
-            const int r = cty + sy - ty0;
-            if (r < 0 || r >= th) continue;
-            const uint64_t row = (mask >> (r * w)) & rowmask;
-            const uint32_t nib = (uint32_t)(c0 >= 0 ? row >> c0 : row << -c0) & sidemask;
-            m |= nib << (sy * side);
-        }
-    } else {
-        const int bh = big_bh(th);
-        for (int sy = 0; sy < side; ++sy) {
-            const int r = cty + sy - ty0;
-            if (r < 0 || r >= th) continue;
-            int row0, nrow, col0, ncol;
-            big_band(mask, w, th, r / bh, &row0, &nrow, &col0, &ncol);
-            const int lo = max(col0 - c0, 0), hi = min(col0 + ncol - 1 - c0, side - 1);
-            if (ncol > 0 && lo <= hi) m |= (((2u << hi) - 1u) & ~((1u << lo) - 1u)) << (sy * side);
-        }
+    for (int sy = 0; sy < side; ++sy) {
+        const int r = cty + sy - ty0;
+        if (r < 0 || r >= th) continue;
+        const uint64_t row = (mask >> (r * w)) & rowmask;
+        const uint32_t nib = (uint32_t)(c0 >= 0 ? row >> c0 : row << -c0) & sidemask;
+        m |= nib << (sy * side);
     }
+    return m;
+}
+// The tiles of the cell whose first tile is (ctx, cty) in band r of a larger one.
+__device__ __forceinline__ uint32_t band_mask(uint64_t mask, int tx0, int ty0, int w, int th, int r, int ctx, int cty, int shift)
+{
+    int row0, nrow, col0, ncol;
+    big_band(mask, w, th, r, &row0, &nrow, &col0, &ncol);
+    const int last = (1 << shift) - 1;
+    const int x0 = max(tx0 + col0 - ctx, 0), x1 = min(tx0 + col0 + ncol - 1 - ctx, last);
+    const int y0 = max(ty0 + row0 - cty, 0), y1 = min(ty0 + row0 + nrow - 1 - cty, last);
+    uint32_t m = 0;
+    for (int y = y0; y <= y1; ++y) m |= (((2u << x1) - 1u) & ~((1u << x0) - 1u)) << (y << shift);
     return m;
 }
 
@@ -831,7 +854,10 @@ __global__ __launch_bounds__(EMIT_BLOCK) void emit_pairs_kernel(
     __shared__ uint4 s_bin[EMIT_BLOCK];
     __shared__ uint32_t s_base[EMIT_BLOCK]; // the view's cell_off
     __shared__ uint32_t s_cx[EMIT_BLOCK];   // the view's cells per row
-    __shared__ float s_rw[EMIT_BLOCK];      // 1 / cells per row of the rectangle
+    // a rectangle of at most 64 tiles: its cell marks (low, high word); a larger one:
+    // the pairs up to the end of its first bands
+    __shared__ uint32_t s_in[3][EMIT_BLOCK];
+    static_assert(BIG_BANDS == 4, "a word for every band but the last");
     __shared__ uint32_t s_own[EMIT_CHUNK];  // owner (block-local convex) of each pair of the chunk
     __shared__ uint32_t s_wmax[EMIT_BLOCK / 64];
     __shared__ uint32_t s_end;
@@ -853,7 +879,20 @@ __global__ __launch_bounds__(EMIT_BLOCK) void emit_pairs_kernel(
             s_base[tid] = (uint32_t)vd.cell_off;
             const uint32_t shift = bin_shift(b);
             s_cx[tid] = ((uint32_t)vd.tiles_x + (1u << shift) - 1u) >> shift;
-            s_rw[tid] = 1.0f / (float)((bin_tx1(b) >> shift) - (bin_tx0(b) >> shift) + 1u);
+            const uint32_t tx0 = bin_tx0(b), ty0 = bin_ty0(b), tw = bin_tx1(b) - tx0 + 1u, th = bin_ty1(b) - ty0 + 1u;
+            const uint64_t mask = (uint64_t)b.z | ((uint64_t)b.w << 32);
+            if (tw * th <= 64u) {
+                const uint64_t marks = cell_marks(mask, tx0, ty0, tw, th, shift);
+                s_in[0][tid] = (uint32_t)marks;
+                s_in[1][tid] = (uint32_t)(marks >> 32);
+            } else {
+                uint32_t end = 0;
+#pragma unroll
+                for (int k = 0; k < BIG_BANDS - 1; ++k) {
+                    const CellBlock c = band_cells(mask, (int)tx0, (int)ty0, (int)tw, (int)th, k, shift);
+                    s_in[k][tid] = end += c.nx * c.ny;
+                }
+            }
         }
         if (tid == cnt - 1) s_end = off + count;
     }
@@ -909,14 +948,25 @@ __global__ __launch_bounds__(EMIT_BLOCK) void emit_pairs_kernel(
             const uint32_t q = p - s_off[lo];
             const uint4 b = s_bin[lo];
             const uint32_t tx0 = bin_tx0(b), ty0 = bin_ty0(b), tx1 = bin_tx1(b), ty1 = bin_ty1(b), shift = bin_shift(b);
-            const uint32_t cx0 = tx0 >> shift, cw = (tx1 >> shift) - cx0 + 1u;
-            // q / cw through the reciprocal (q < 2^24), corrected by one step
-            uint32_t row = (uint32_t)((float)q * s_rw[lo]);
-            if (row * cw > q) --row;
-            else if ((row + 1) * cw <= q) ++row;
-            const uint32_t cx = cx0 + (q - row * cw), cy = (ty0 >> shift) + row;
-            const uint32_t mask = cell_mask((uint64_t)b.z | ((uint64_t)b.w << 32), (int)tx0, (int)ty0, (int)(tx1 - tx0 + 1u),
-                                            (int)(ty1 - ty0 + 1u), (int)(cx << shift), (int)(cy << shift), (int)shift);
+            const uint32_t tw = tx1 - tx0 + 1u, th = ty1 - ty0 + 1u;
+            const uint64_t kept = (uint64_t)b.z | ((uint64_t)b.w << 32);
+            const uint32_t in0 = s_in[0][lo], in1 = s_in[1][lo];
+            uint32_t cx, cy, mask;
+            if (tw * th <= 64u) { // the q-th marked cell
+                const uint32_t at = nth_set_bit((uint64_t)in0 | ((uint64_t)in1 << 32), q), row = small_div(at, tw);
+                cx = (tx0 + at - row * tw) >> shift;
+                cy = (ty0 + row) >> shift;
+                mask = cell_mask(kept, (int)tx0, (int)ty0, (int)tw, (int)th, (int)(cx << shift), (int)(cy << shift), (int)shift);
+            } else { // the q-th cell of the bands, band by band
+                const uint32_t in2 = s_in[2][lo];
+                const int r = (q >= in0) + (q >= in1) + (q >= in2);
+                const uint32_t before = r == 0 ? 0u : r == 1 ? in0 : r == 2 ? in1 : in2;
+                const CellBlock c = band_cells(kept, (int)tx0, (int)ty0, (int)tw, (int)th, r, shift);
+                const uint32_t qb = q - before, nx = max(c.nx, 1u), row = small_div(qb, nx);
+                cx = c.x + qb - row * nx;
+                cy = c.y + row;
+                mask = band_mask(kept, (int)tx0, (int)ty0, (int)tw, (int)th, r, (int)(cx << shift), (int)(cy << shift), (int)shift);
+            }
             pair_keys[p] = (s_base[lo] + cy * s_cx[lo] + cx) | (mask << kbits);
             pair_ids[p] = s_id[lo];
         }

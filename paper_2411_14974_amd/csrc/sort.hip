@@ -30,8 +30,14 @@ inline size_t scan_tiles(uint32_t n, int items) { return ((size_t)n + SCAN_BLOCK
 
 __device__ __forceinline__ int lds_pad(int i) { return i + (i >> 5); }
 
+// Sum of two counts of cell pairs that are at most MAX_CELL_PAIRS, saturating
+// there.  A call that goes beyond is refused, but its count must arrive: one
+// convex can make 2^20 pairs (16384 x 16384 in tiles of 8), 4096 of them 2^32.
+__device__ __forceinline__ uint32_t add_cells(uint32_t a, uint32_t b) { return min(a + b, MAX_CELL_PAIRS); }
+
 // Exclusive scan of the block's SCAN_ITEMS values per thread held in LDS
-// (padded layout); returns the block total.
+// (padded layout); returns the block total.  The sum of a wavefront's values is
+// at most 2^30 and a little; sums over wavefronts saturate at MAX_CELL_PAIRS.
 template <int SCAN_ITEMS>
 __device__ uint32_t block_scan_lds(uint32_t *s, uint32_t *s_wave)
 {
@@ -53,11 +59,11 @@ __device__ uint32_t block_scan_lds(uint32_t *s, uint32_t *s_wave)
     __syncthreads();
     uint32_t wbase = 0, total = 0;
     for (int w = 0; w < SCAN_BLOCK / 64; ++w) {
-        const uint32_t c = s_wave[w];
-        if (w < wave) wbase += c;
-        total += c;
+        const uint32_t c = min(s_wave[w], MAX_CELL_PAIRS);
+        if (w < wave) wbase = add_cells(wbase, c);
+        total = add_cells(total, c);
     }
-    uint32_t run = wbase + incl - sum;
+    uint32_t run = wbase + incl - sum; // (below 2^32)
 #pragma unroll
     for (int k = 0; k < SCAN_ITEMS; ++k) {
         s[lds_pad(tid * SCAN_ITEMS + k)] = run;
@@ -76,10 +82,7 @@ __device__ uint32_t block_scan_lds(uint32_t *s, uint32_t *s_wave)
 // A status word: state in bits 62-63, cell pairs in bits 32-61 (saturating), tile
 // pairs (modulo 2^32) below.
 constexpr uint64_t SS_AGG = 1ull << 62, SS_INC = 2ull << 62, SS_VAL = SS_AGG - 1ull;
-__device__ __forceinline__ uint64_t ss_pack(uint64_t cells, uint32_t tiles)
-{
-    return (min(cells, (uint64_t)MAX_CELL_PAIRS) << 32) | tiles;
-}
+__device__ __forceinline__ uint64_t ss_pack(uint32_t cells, uint32_t tiles) { return ((uint64_t)cells << 32) | tiles; }
 constexpr uint32_t SS_SPIN_LIMIT = 1u << 22;
 
 __device__ __forceinline__ uint64_t ss_load(const uint64_t *p)
@@ -124,7 +127,7 @@ __global__ __launch_bounds__(SCAN_BLOCK) void gather_scan_kernel(
     __shared__ uint32_t s[SCAN_TILE + SCAN_TILE / 32];
     __shared__ uint32_t s_wave[SCAN_BLOCK / 64];
     __shared__ uint32_t s_tile;
-    __shared__ uint64_t s_excl;
+    __shared__ uint32_t s_excl;
     const int tid = threadIdx.x, lane = tid & 63;
     if (tid == 0) s_tile = atomicAdd(&counters[CNT_SCAN_TILE], 1u);
     __syncthreads();
@@ -161,8 +164,7 @@ __global__ __launch_bounds__(SCAN_BLOCK) void gather_scan_kernel(
         uint32_t block_tiles = 0;
         for (int w = 0; w < SCAN_BLOCK / 64; ++w) block_tiles += s_wave[w];
         if (tid == 0) ss_store(&status[t], (t == 0 ? SS_INC : SS_AGG) | ss_pack(tile_total, block_tiles));
-        uint64_t excl = 0;
-        uint32_t excl_tiles = 0;
+        uint32_t excl = 0, excl_tiles = 0;
         if (t > 0) {
             int64_t j = (int64_t)t - 1; // the window's newest tile
             uint32_t spins = 0;
@@ -181,34 +183,33 @@ __global__ __launch_bounds__(SCAN_BLOCK) void gather_scan_kernel(
                     __builtin_amdgcn_s_sleep(1);
                     continue;
                 }
-                uint64_t v = (lane <= fi) ? (sv & SS_VAL) >> 32 : 0ull;
+                uint32_t v = (lane <= fi) ? (uint32_t)((sv & SS_VAL) >> 32) : 0u;
                 uint32_t vt = (lane <= fi) ? (uint32_t)sv : 0u;
 #pragma unroll
                 for (int o = 32; o > 0; o >>= 1) {
-                    v += __shfl_xor(v, o, 64);
+                    v = add_cells(v, __shfl_xor(v, o, 64));
                     vt += __shfl_xor(vt, o, 64);
                 }
-                excl += v;
+                excl = add_cells(excl, v);
                 excl_tiles += vt;
                 if (fi < 64) break;
                 j -= 64;
             }
-            if (tid == 0) ss_store(&status[t], SS_INC | ss_pack(excl + tile_total, excl_tiles + block_tiles));
+            if (tid == 0) ss_store(&status[t], SS_INC | ss_pack(add_cells(excl, tile_total), excl_tiles + block_tiles));
         }
         if (tid == 0) {
             s_excl = excl;
             if (base + SCAN_TILE >= n) {
-                store_pair_counts(counters, (uint32_t)min(excl + tile_total, (uint64_t)MAX_CELL_PAIRS),
-                                  excl_tiles + block_tiles, host_word, tag, capacity);
+                store_pair_counts(counters, add_cells(excl, tile_total), excl_tiles + block_tiles, host_word, tag, capacity);
             }
         }
     }
     __syncthreads();
-    const uint32_t ex = (uint32_t)s_excl;
+    const uint32_t ex = s_excl;
 #pragma unroll
     for (int k = 0; k < SCAN_ITEMS; ++k) {
         const size_t i = base + (size_t)k * SCAN_BLOCK + tid;
-        if (i < n) offsets[i] = s[lds_pad(k * SCAN_BLOCK + tid)] + ex;
+        if (i < n) offsets[i] = min(s[lds_pad(k * SCAN_BLOCK + tid)] + ex, MAX_CELL_PAIRS); // (the sum below 2^32)
     }
 }
 
@@ -737,19 +738,16 @@ __global__ __launch_bounds__(SM_BLOCK) void small_order_kernel(
         s_wsum[1][wave] = tile_pairs;
     }
     __syncthreads();
-    uint32_t before = 0, m = 0, tiles = 0;
+    uint32_t before = 0, m = 0, tiles = 0; // (a wavefront's 512 instances at most: some 2^29 pairs)
     for (int w = 0; w < SM_WAVES; ++w) {
-        if (w < wave) before += s_wsum[0][w];
-        m += s_wsum[0][w];
+        if (w < wave) before = add_cells(before, s_wsum[0][w]);
+        m = add_cells(m, s_wsum[0][w]);
         tiles += s_wsum[1][w];
     }
 #pragma unroll
     for (int i = 0; i < ITEMS; ++i)
-        if (first + 64u * i < n) offsets[first + 64u * i] = before + c[i];
-    if (tid == 0) {
-        m = min(m, MAX_CELL_PAIRS);
-        store_pair_counts(counters, m, tiles, host_word, tag, capacity);
-    }
+        if (first + 64u * i < n) offsets[first + 64u * i] = min(before + c[i], MAX_CELL_PAIRS);
+    if (tid == 0) store_pair_counts(counters, m, tiles, host_word, tag, capacity);
 }
 
 // Whether the order of n instances is made by small_order_kernel; then it is

@@ -239,7 +239,7 @@ int cs_state_stats(cs_ctx *ctx, const cs_fwd_state *state, int64_t *n_pairs, int
  * state, summed over the compositing workgroups (synchronises the stream).
  * They price the compositing kernels against their roofline (the per-pair
  * work of Sec. 3.1 Eqs. smoothness/sharpness, T lines per pair):
- *   pairs       (tile, convex) pairs binned
+ *   pairs       (tile, convex) pairs binned (2^32 - 1 where there are more)
  *   tested      (pixel, convex) pairs of the forward walk inside the record's pixel box
  *   full        of those, the pairs past the max-line test (LogSumExp and sigmoid evaluated)
  *   full_bwd    the same count in the backward walk, which visits the same pairs

@@ -306,7 +306,7 @@ __device__ inline void zero_share(const ZeroSpans &z)
 //   [0, CNT_WORDS)            counters read back by the host:
 //     CNT_SORT_ERR: a radix-sort look-back wait ran out of its bound (never expected)
 //     CNT_PAIRS: (cell, convex) pairs; CNT_PAIRS_EFF: those that fit the buffers
-//     CNT_TILE_PAIRS: (tile, convex) pairs that they stand for
+//     CNT_TILE_PAIRS: (tile, convex) pairs that they stand for (at most 2^32 - 1)
 //     CNT_SCAN_TILE: tile claims of the pair-offset scan
 //   [CNT_QUEUE, CNT_QUEUE_B)  the forward compositing's work queues' claim
 //                             counters, one per QUEUE_STRIDE words: device-scope

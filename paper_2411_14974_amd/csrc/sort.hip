@@ -34,6 +34,9 @@ __device__ __forceinline__ int lds_pad(int i) { return i + (i >> 5); }
 // there.  A call that goes beyond is refused, but its count must arrive: one
 // convex can make 2^20 pairs (16384 x 16384 in tiles of 8), 4096 of them 2^32.
 __device__ __forceinline__ uint32_t add_cells(uint32_t a, uint32_t b) { return min(a + b, MAX_CELL_PAIRS); }
+// Sum of two counts of tile pairs, saturating at 2^32 - 1 (a call's cell pairs
+// can stand for 2^34).
+__device__ __forceinline__ uint32_t add_tiles(uint32_t a, uint32_t b) { return a + b < a ? 0xFFFFFFFFu : a + b; }
 
 // Exclusive scan of the block's SCAN_ITEMS values per thread held in LDS
 // (padded layout); returns the block total.  The sum of a wavefront's values is
@@ -79,8 +82,8 @@ __device__ uint32_t block_scan_lds(uint32_t *s, uint32_t *s_wave)
 // pair emission) and their pair counts, scans the counts in LDS, publishes the tile's sum and
 // finds its prefix by a decoupled look-back in which one wave reads 64
 // predecessors' 64-bit status words at a time.  The last tile stores the total.
-// A status word: state in bits 62-63, cell pairs in bits 32-61 (saturating), tile
-// pairs (modulo 2^32) below.
+// A status word: state in bits 62-63, cell pairs in bits 32-61, tile pairs below
+// (both saturating).
 constexpr uint64_t SS_AGG = 1ull << 62, SS_INC = 2ull << 62, SS_VAL = SS_AGG - 1ull;
 __device__ __forceinline__ uint64_t ss_pack(uint32_t cells, uint32_t tiles) { return ((uint64_t)cells << 32) | tiles; }
 constexpr uint32_t SS_SPIN_LIMIT = 1u << 22;
@@ -157,12 +160,12 @@ __global__ __launch_bounds__(SCAN_BLOCK) void gather_scan_kernel(
     __syncthreads();
     const uint32_t tile_total = block_scan_lds<SCAN_ITEMS>(s, s_wave);
 #pragma unroll
-    for (int o = 32; o > 0; o >>= 1) tile_pairs += __shfl_xor(tile_pairs, o, 64);
+    for (int o = 32; o > 0; o >>= 1) tile_pairs = add_tiles(tile_pairs, __shfl_xor(tile_pairs, o, 64));
     if (lane == 0) s_wave[tid >> 6] = tile_pairs; // (the scan above ended with a barrier)
     __syncthreads();
     if (tid < 64) {
         uint32_t block_tiles = 0;
-        for (int w = 0; w < SCAN_BLOCK / 64; ++w) block_tiles += s_wave[w];
+        for (int w = 0; w < SCAN_BLOCK / 64; ++w) block_tiles = add_tiles(block_tiles, s_wave[w]);
         if (tid == 0) ss_store(&status[t], (t == 0 ? SS_INC : SS_AGG) | ss_pack(tile_total, block_tiles));
         uint32_t excl = 0, excl_tiles = 0;
         if (t > 0) {
@@ -188,19 +191,19 @@ __global__ __launch_bounds__(SCAN_BLOCK) void gather_scan_kernel(
 #pragma unroll
                 for (int o = 32; o > 0; o >>= 1) {
                     v = add_cells(v, __shfl_xor(v, o, 64));
-                    vt += __shfl_xor(vt, o, 64);
+                    vt = add_tiles(vt, __shfl_xor(vt, o, 64));
                 }
                 excl = add_cells(excl, v);
-                excl_tiles += vt;
+                excl_tiles = add_tiles(excl_tiles, vt);
                 if (fi < 64) break;
                 j -= 64;
             }
-            if (tid == 0) ss_store(&status[t], SS_INC | ss_pack(add_cells(excl, tile_total), excl_tiles + block_tiles));
+            if (tid == 0) ss_store(&status[t], SS_INC | ss_pack(add_cells(excl, tile_total), add_tiles(excl_tiles, block_tiles)));
         }
         if (tid == 0) {
             s_excl = excl;
             if (base + SCAN_TILE >= n) {
-                store_pair_counts(counters, add_cells(excl, tile_total), excl_tiles + block_tiles, host_word, tag, capacity);
+                store_pair_counts(counters, add_cells(excl, tile_total), add_tiles(excl_tiles, block_tiles), host_word, tag, capacity);
             }
         }
     }
@@ -732,7 +735,7 @@ __global__ __launch_bounds__(SM_BLOCK) void small_order_kernel(
         }
     }
 #pragma unroll
-    for (int o = 32; o > 0; o >>= 1) tile_pairs += __shfl_xor(tile_pairs, o, 64);
+    for (int o = 32; o > 0; o >>= 1) tile_pairs = add_tiles(tile_pairs, __shfl_xor(tile_pairs, o, 64));
     if (lane == 0) {
         s_wsum[0][wave] = run;
         s_wsum[1][wave] = tile_pairs;
@@ -742,7 +745,7 @@ __global__ __launch_bounds__(SM_BLOCK) void small_order_kernel(
     for (int w = 0; w < SM_WAVES; ++w) {
         if (w < wave) before = add_cells(before, s_wsum[0][w]);
         m = add_cells(m, s_wsum[0][w]);
-        tiles += s_wsum[1][w];
+        tiles = add_tiles(tiles, s_wsum[1][w]);
     }
 #pragma unroll
     for (int i = 0; i < ITEMS; ++i)

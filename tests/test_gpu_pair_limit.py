@@ -14,6 +14,10 @@ from paper_2411_14974_amd import scenes  # noqa: E402
 SIDE = 16384
 
 
+def square(side):
+    return scenes.Camera(side, side, float(side), float(side), side / 2.0, side / 2.0)
+
+
 def triangles(n, size):
     """n triangles round the optical axis at depths 2 to 3, `size` times their depth wide."""
     z = np.linspace(2.0, 3.0, n)
@@ -29,7 +33,7 @@ def test_wrapped_sums_are_refused(n):
     from paper_2411_14974_amd.binding import CS_ENOMEM, CSError, DeviceScene, Renderer, make_params
     R = Renderer(0)
     try:
-        cam = scenes.Camera(SIDE, SIDE, float(SIDE), float(SIDE), SIDE / 2.0, SIDE / 2.0)
+        cam = square(SIDE)
         out = torch.empty((SIDE, SIDE, 3), device="cuda:0")
         p = make_params(tile=8)
         filled = DeviceScene.from_scene(triangles(n, 100.0), "cuda:0")
@@ -42,5 +46,22 @@ def test_wrapped_sums_are_refused(n):
                 R.forward(filled, cam, p, out=out)
             assert e.value.code == CS_ENOMEM
             say(f"[pair limit] {n} convexes over {SIDE}^2, {'reused' if reused else 'new'} frame: {e.value}")
+    finally:
+        R.close()
+
+
+def test_tile_pairs_saturate():
+    """4096 convexes over 8192 x 8192 pixels in tiles of 8: 2^28 cell pairs, which a
+    call can hold, that stand for 2^32 tile pairs."""
+    from paper_2411_14974_amd.binding import DeviceScene, Renderer, make_params
+    R = Renderer(0)
+    try:
+        cam, p = square(8192), make_params(tile=8)
+        ds = DeviceScene.from_scene(triangles(4096, 100.0), "cuda:0")
+        out, st = R.forward(ds, cam, p, want_state=True)
+        assert st.counters()["pairs"] == (1 << 32) - 1
+        st.release()
+        few, _ = R.forward(DeviceScene.from_scene(triangles(4096, 100.0).subset(np.arange(64)), "cuda:0"), cam, p)
+        assert torch.equal(few, out)  # (what lies behind the first 64 is never seen)
     finally:
         R.close()

@@ -110,13 +110,16 @@ void Frame::release_buffer(void *p)
         }
 }
 
+void Frame::drop_backward_graphs()
+{
+    for (Captured *g : {gbwd, gbwd_nz})
+        for (int k = 0; k < 2; ++k) g[k].drop();
+}
+
 void Frame::drop_graphs()
 {
-    if (gfwd) (void)hipGraphExecDestroy(gfwd);
-    if (gbwd) (void)hipGraphExecDestroy(gbwd);
-    if (gbwd_nz) (void)hipGraphExecDestroy(gbwd_nz);
-    gfwd = gbwd = gbwd_nz = nullptr;
-    gfwd_zero = false;
+    for (Captured &g : gfwd) g.drop();
+    drop_backward_graphs();
 }
 
 Frame::~Frame()
@@ -1124,23 +1127,22 @@ int cs_render_forward_batch(cs_ctx *ctx, const cs_scene *sc, int32_t n_views, co
             CS_TRY(F->ensure_pairs(F->pair_room(F->h_counters[CNT_PAIRS], F->h_counters[CNT_TILE_PAIRS], 1.3)));
             F->overflowed = false;
         }
-        if (F->gfwd && F->acc && !F->gfwd_zero) { // accumulators appeared: capture again with their clearing
-            (void)hipGraphExecDestroy(F->gfwd);
-            F->gfwd = nullptr;
-        }
-        if (!F->gfwd) {
+        Frame::Captured &gx = F->gfwd[split_by_record(F->K, F->pixels)];
+        if (gx.exec && F->acc && !gx.zero) gx.drop(); // accumulators appeared: capture again with their clearing
+        if (!gx.exec) {
             StageTimer off(ctx, st, false);
-            CS_TRY(capture_graph(ctx, *F, &F->gfwd, [&] { return enqueue_forward(ctx, *F, sc, ra, kn, true, 1.0, off); }));
-            F->gfwd_zero = F->acc != nullptr;
+            CS_TRY(capture_graph(ctx, *F, &gx.exec, [&] { return enqueue_forward(ctx, *F, sc, ra, kn, true, 1.0, off); }));
+            gx.zero = F->acc != nullptr;
+            gx.slots = F->eval_slots;
             // the captured sort provides for other resolutions and may leave its lists in
             // the other pair of buffers than the eager first frame's did, which a
             // backward captured since then reads
-            if (F->gbwd) { (void)hipGraphExecDestroy(F->gbwd); F->gbwd = nullptr; }
-            if (F->gbwd_nz) { (void)hipGraphExecDestroy(F->gbwd_nz); F->gbwd_nz = nullptr; }
+            F->drop_backward_graphs();
         }
         tm.begin();
-        CS_HIP(hipGraphLaunch(F->gfwd, st));
-        F->acc_zeroed = F->gfwd_zero;
+        CS_HIP(hipGraphLaunch(gx.exec, st));
+        F->acc_zeroed = gx.zero;
+        F->eval_slots = gx.slots;
         tm.end(CS_STAGE_GRAPH_FWD);
     }
     F->epoch++;
@@ -1218,23 +1220,24 @@ int cs_render_backward_batch(cs_ctx *ctx, const cs_scene *sc, int32_t n_views, c
     for (uint64_t v : {(uint64_t)(uintptr_t)g->points, (uint64_t)(uintptr_t)g->delta, (uint64_t)(uintptr_t)g->sigma,
                        (uint64_t)(uintptr_t)g->opacity, (uint64_t)(uintptr_t)g->sh})
         key = mix(key, v);
-    if (F->kbwd != key) { // other gradient buffers: both backward graphs are stale
-        if (F->gbwd) { (void)hipGraphExecDestroy(F->gbwd); F->gbwd = nullptr; }
-        if (F->gbwd_nz) { (void)hipGraphExecDestroy(F->gbwd_nz); F->gbwd_nz = nullptr; }
+    if (F->kbwd != key) { // other gradient buffers: the backward graphs are stale
+        F->drop_backward_graphs();
         F->kbwd = key;
     }
     // the graph without the clearing pass when the forward has cleared the accumulators
     const bool cleared = F->acc_zeroed;
-    hipGraphExec_t &gx = cleared ? F->gbwd_nz : F->gbwd;
-    if (!gx) {
+    Frame::Captured &gx = (cleared ? F->gbwd_nz : F->gbwd)[split_by_record(F->K, F->pixels)];
+    if (!gx.exec) {
         CS_TRY(F->ensure_acc());
         StageTimer off(ctx, st, false);
-        CS_TRY(capture_graph(ctx, *F, &gx, [&] { return enqueue_backward(*F, sc, g, ra, off, !cleared); }));
+        CS_TRY(capture_graph(ctx, *F, &gx.exec, [&] { return enqueue_backward(*F, sc, g, ra, off, !cleared); }));
+        gx.slots = F->eval_slots_bwd;
     }
     StageTimer tm(ctx, st, timing);
     tm.begin();
-    CS_HIP(hipGraphLaunch(gx, st));
+    CS_HIP(hipGraphLaunch(gx.exec, st));
     F->acc_zeroed = false; // the graph's backward has used them
+    F->eval_slots_bwd = gx.slots;
     tm.end(CS_STAGE_GRAPH_BWD);
     return CS_OK;
 }

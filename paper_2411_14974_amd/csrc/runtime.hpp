@@ -80,11 +80,23 @@ struct Frame {
     uint32_t *sorted_keys = nullptr, *sorted_ids = nullptr; // (cell, convex) pairs by cell, then depth
     uint32_t *order = nullptr;
 
-    // captured graphs (batched path): the forward (gfwd_zero: it clears the
-    // backward's accumulators), the backward with and without its clearing pass
-    hipGraphExec_t gfwd = nullptr, gbwd = nullptr, gbwd_nz = nullptr;
-    bool gfwd_zero = false;
+    // captured graphs (batched path), for views composited by tile and by record
+    // (split_by_record) in turn, since resolutions may change between replays: the
+    // forward (zero: it clears the backward's accumulators), the backward with and
+    // without its clearing pass; slots: the work-counter slots that a graph writes
+    struct Captured {
+        hipGraphExec_t exec = nullptr;
+        int slots = 0;
+        bool zero = false;
+        void drop()
+        {
+            if (exec) (void)hipGraphExecDestroy(exec);
+            exec = nullptr;
+        }
+    };
+    Captured gfwd[2], gbwd[2], gbwd_nz[2];
     uint64_t kbwd = 0;
+    void drop_backward_graphs();
     void drop_graphs();
     uint64_t epoch = 0;
 

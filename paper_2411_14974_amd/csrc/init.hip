@@ -14,6 +14,8 @@
 // operations of a point's (subtract, square, add, each rounded monotonically),
 // so it never exceeds the computed distance of a point inside: pruning drops no
 // neighbour, and the three distances are the brute-force search's bit for bit.
+// Should the sort report that one of its bounded waits ran out, its order is not
+// used and the search's kernel compares every pair instead.
 #include <algorithm>
 #include <cmath>
 #include <vector>
@@ -97,12 +99,14 @@ __device__ __forceinline__ bool finite3(float x, float y, float z)
 // samples within 3 sigma of the last estimate, so that a few far points (usual
 // in structure-from-motion clouds) do not stretch it; points outside fall into
 // its border cells.  cube[0..2] low corner, cube[3..5] cells per length.  One
-// workgroup.
+// workgroup; it also sets the sort's error word to err0.
 __global__ __launch_bounds__(CURVE_SAMPLES) void curve_cube_kernel(int n, const float *__restrict__ xyz,
-                                                                   float *__restrict__ cube)
+                                                                   float *__restrict__ cube, uint32_t *__restrict__ err,
+                                                                   uint32_t err0)
 {
     __shared__ float s_sum[CURVE_SAMPLES / 64][7], s_tot[7];
     const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+    if (t == 0) *err = err0;
     const size_t i = (size_t)t * (size_t)n / CURVE_SAMPLES;
     const float x = xyz[3 * i], y = xyz[3 * i + 1], z = xyz[3 * i + 2];
     const bool ok = finite3(x, y, z);
@@ -250,15 +254,23 @@ __device__ __forceinline__ float box_gap2(float3 alo, float3 ahi, float4 blo, fl
 // instructions per query and candidate) and by how few leaves are visited: 100k
 // points take 7.83 ms by brute force, 0.31 ms with 64 queries and 64-point
 // leaves, 1.71 ms with leaves chosen by the 16 points' box alone, 0.11 ms here.
+// *err nonzero (the sort failed): the queries are 16 points of the cloud as it
+// stands, each compared with all of it.
 __global__ __launch_bounds__(KN_BLOCK) void knn3_curve_kernel(int nleaves, int nnodes, const float4 *__restrict__ pts,
                                                               const float4 *__restrict__ boxes,
                                                               const float4 *__restrict__ nodes, int n,
+                                                              const float *__restrict__ xyz, const uint32_t *__restrict__ err,
                                                               float *__restrict__ mean_dist)
 {
     const int leaf = __builtin_amdgcn_readfirstlane((int)((blockIdx.x * KN_BLOCK + threadIdx.x) >> 6));
     if (leaf >= nleaves) return;
     const int lane = threadIdx.x & 63, ql = lane & (LEAF - 1), group = lane / LEAF;
-    const float4 q = pts[(size_t)leaf * LEAF + ql];
+    const bool sorted = *err == 0u;
+    float4 q = pts[(size_t)leaf * LEAF + ql];
+    if (!sorted) {
+        const size_t i = min((size_t)leaf * LEAF + ql, (size_t)n - 1);
+        q = make_float4(xyz[3 * i], xyz[3 * i + 1], xyz[3 * i + 2], __uint_as_float((uint32_t)i));
+    }
     const bool active = finite3(q.x, q.y, q.z);
     const float4 l4 = boxes[2 * (size_t)leaf], h4 = boxes[2 * (size_t)leaf + 1];
     const float3 glo = make_float3(l4.x, l4.y, l4.z), ghi = make_float3(h4.x, h4.y, h4.z);
@@ -289,9 +301,17 @@ __global__ __launch_bounds__(KN_BLOCK) void knn3_curve_kernel(int nleaves, int n
         for (int o = 8; o > 0; o >>= 1) m = fmaxf(m, __shfl_xor(m, o, 64));
         gmax = __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(m)));
     };
-    {
+    if (sorted) {
         const int l = leaf - 1 + group;
         scan(l < nleaves ? l : -1); // (l = -1 before the first leaf)
+    } else {
+        const uint32_t self = __float_as_uint(q.w);
+        for (uint32_t j = group; j < (uint32_t)n; j += 64 / LEAF) {
+            const float dx = xyz[3 * (size_t)j] - q.x, dy = xyz[3 * (size_t)j + 1] - q.y, dz = xyz[3 * (size_t)j + 2] - q.z;
+            const float e = (dx * dx + dy * dy) + dz * dz;
+            insert(e < INFINITY && j != self ? e : INFINITY);
+        }
+        nnodes = 0; // no leaf to visit
     }
     // whether the lane's box holds a point that some query may need: the 16
     // points' leaf may span a jump of the curve, so its box alone says little
@@ -388,7 +408,64 @@ __global__ __launch_bounds__(KN_BLOCK) void init_convex_kernel(const float *__re
     rows(a.nsh, [&](int r, int e) { return e < 3 ? s_f[r][e] : 0.0f; }, out.sh + (size_t)base * a.nsh);
 }
 
+// The scratch of a neighbour search: the mean distances, and for the search
+// along the curve its cube and the sort's error word, keys and indices (with the
+// sort's second pair and temporaries), the sorted points and the boxes.
+struct NeighbourScratch {
+    size_t bytes = 0, md = 0, cube = 0, pair[4] = {}, temp = 0, pts = 0, box = 0, node = 0;
+    explicit NeighbourScratch(int n)
+    {
+        const size_t N = (size_t)n, nleaves = (N + LEAF - 1) / LEAF, nnodes = (nleaves + NODE - 1) / NODE;
+        auto carve = [&](size_t b) {
+            const size_t at = bytes;
+            bytes = (bytes + b + 255) & ~(size_t)255;
+            return at;
+        };
+        md = carve(4 * N);
+        if (n <= BRUTE_MAX) return;
+        cube = carve(64);
+        for (size_t &o : pair) o = carve(4 * N);
+        temp = carve(4 * sort_temp_words((uint32_t)n, 31, 8));
+        pts = carve(16 * LEAF * nleaves);
+        box = carve(32 * nleaves);
+        node = carve(32 * nnodes);
+    }
+};
+
 } // namespace
+
+size_t neighbour_scratch_bytes(int n) { return NeighbourScratch(n).bytes; }
+
+// Mean distance of every point to its three nearest others, at the start of the
+// scratch (neighbour_scratch_bytes).  err0: what the sort's error word starts
+// from; 0 but where a test has the search go without the sort.
+void launch_neighbour_means(hipStream_t st, int n, const float *xyz, uint8_t *scr, uint32_t err0)
+{
+    const NeighbourScratch o(n);
+    const dim3 grid((n + KN_BLOCK - 1) / KN_BLOCK), block(KN_BLOCK);
+    float *md = reinterpret_cast<float *>(scr + o.md);
+    if (n <= BRUTE_MAX) {
+        hipLaunchKernelGGL(knn3_mean_kernel, grid, block, 0, st, n, xyz, md);
+        return;
+    }
+    const size_t nleaves = ((size_t)n + LEAF - 1) / LEAF, nnodes = (nleaves + NODE - 1) / NODE;
+    float *cube = reinterpret_cast<float *>(scr + o.cube);
+    uint32_t *err = reinterpret_cast<uint32_t *>(cube) + 8;
+    uint32_t *keys = reinterpret_cast<uint32_t *>(scr + o.pair[0]), *ids = reinterpret_cast<uint32_t *>(scr + o.pair[1]);
+    uint32_t *keys2 = reinterpret_cast<uint32_t *>(scr + o.pair[2]), *ids2 = reinterpret_cast<uint32_t *>(scr + o.pair[3]);
+    float4 *pts = reinterpret_cast<float4 *>(scr + o.pts), *boxes = reinterpret_cast<float4 *>(scr + o.box);
+    float4 *nodes = reinterpret_cast<float4 *>(scr + o.node);
+    hipLaunchKernelGGL(curve_cube_kernel, dim3(1), dim3(CURVE_SAMPLES), 0, st, n, xyz, cube, err, err0);
+    uint32_t *temp = reinterpret_cast<uint32_t *>(scr + o.temp);
+    const ZeroSpans z{{temp}, {(uint32_t)radix_sort_words((uint32_t)n, false, (uint32_t)n, 31, 8)}};
+    hipLaunchKernelGGL(morton_kernel, grid, block, 0, st, n, xyz, cube, keys, ids, z);
+    radix_sort(st, &keys, &ids, &keys2, &ids2, (uint32_t)n, nullptr, (uint32_t)n, 31, temp, 8, err, true, nullptr, 0);
+    const dim3 lgrid((unsigned)((nleaves * LEAF + KN_BLOCK - 1) / KN_BLOCK));
+    hipLaunchKernelGGL(leaf_kernel, lgrid, block, 0, st, n, (int)nleaves, xyz, ids, pts, boxes);
+    hipLaunchKernelGGL(node_kernel, dim3((unsigned)nnodes), dim3(NODE), 0, st, (int)nleaves, boxes, nodes);
+    hipLaunchKernelGGL(knn3_curve_kernel, dim3((unsigned)((nleaves * 64 + KN_BLOCK - 1) / KN_BLOCK)), block, 0, st, (int)nleaves,
+                       (int)nnodes, pts, boxes, nodes, n, xyz, err, md);
+}
 
 } // namespace cs
 
@@ -425,51 +502,12 @@ int cs_init_from_points(cs_ctx *ctx, int32_t n, const float *xyz, const float *r
         a.dir[3 * j + 1] = (float)yv;
         a.dir[3 * j + 2] = (float)(std::sin(phi) * rxy);
     }
-    const dim3 grid((n + KN_BLOCK - 1) / KN_BLOCK), block(KN_BLOCK);
-    const size_t N = (size_t)n, nleaves = (N + LEAF - 1) / LEAF, nnodes = (nleaves + NODE - 1) / NODE;
-    const bool curve = n > BRUTE_MAX;
-    // scratch: the mean distances; for the search along the curve its cube and
-    // the sort's error word, keys and indices (with the sort's second pair and
-    // temporaries), the sorted points and the boxes
-    size_t bytes = 0;
-    auto carve = [&](size_t b) {
-        const size_t at = bytes;
-        bytes = (bytes + b + 255) & ~(size_t)255;
-        return at;
-    };
-    const size_t o_md = carve(4 * N);
-    size_t o_cube = 0, o_pair[4] = {}, o_temp = 0, o_pts = 0, o_box = 0, o_node = 0;
-    if (curve) {
-        o_cube = carve(64);
-        for (size_t &o : o_pair) o = carve(4 * N);
-        o_temp = carve(4 * sort_temp_words((uint32_t)n, 31, 8));
-        o_pts = carve(16 * LEAF * nleaves);
-        o_box = carve(32 * nleaves);
-        o_node = carve(32 * nnodes);
-    }
     uint8_t *scr = nullptr;
-    hipError_t e = hipMallocAsync((void **)&scr, bytes, st);
+    hipError_t e = hipMallocAsync((void **)&scr, neighbour_scratch_bytes(n), st);
     if (e != hipSuccess) return fail(CS_ENOMEM, "init scratch: %s", hipGetErrorString(e));
-    float *md = reinterpret_cast<float *>(scr + o_md);
-    if (curve) {
-        float *cube = reinterpret_cast<float *>(scr + o_cube);
-        uint32_t *keys = reinterpret_cast<uint32_t *>(scr + o_pair[0]), *ids = reinterpret_cast<uint32_t *>(scr + o_pair[1]);
-        uint32_t *keys2 = reinterpret_cast<uint32_t *>(scr + o_pair[2]), *ids2 = reinterpret_cast<uint32_t *>(scr + o_pair[3]);
-        float4 *pts = reinterpret_cast<float4 *>(scr + o_pts), *boxes = reinterpret_cast<float4 *>(scr + o_box);
-        float4 *nodes = reinterpret_cast<float4 *>(scr + o_node);
-        hipLaunchKernelGGL(curve_cube_kernel, dim3(1), dim3(CURVE_SAMPLES), 0, st, n, xyz, cube);
-        uint32_t *temp = reinterpret_cast<uint32_t *>(scr + o_temp);
-        const ZeroSpans z{{temp}, {(uint32_t)radix_sort_words((uint32_t)n, false, (uint32_t)n, 31, 8)}};
-        hipLaunchKernelGGL(morton_kernel, grid, block, 0, st, n, xyz, cube, keys, ids, z);
-        radix_sort(st, &keys, &ids, &keys2, &ids2, (uint32_t)n, nullptr, (uint32_t)n, 31, temp, 8,
-                   reinterpret_cast<uint32_t *>(cube) + 8, true, nullptr, 0);
-        const dim3 lgrid((unsigned)((nleaves * LEAF + KN_BLOCK - 1) / KN_BLOCK));
-        hipLaunchKernelGGL(leaf_kernel, lgrid, block, 0, st, n, (int)nleaves, xyz, ids, pts, boxes);
-        hipLaunchKernelGGL(node_kernel, dim3((unsigned)nnodes), dim3(NODE), 0, st, (int)nleaves, boxes, nodes);
-        hipLaunchKernelGGL(knn3_curve_kernel, dim3((unsigned)((nleaves * 64 + KN_BLOCK - 1) / KN_BLOCK)), block, 0, st, (int)nleaves, (int)nnodes, pts, boxes, nodes, n, md);
-    } else {
-        hipLaunchKernelGGL(knn3_mean_kernel, grid, block, 0, st, n, xyz, md);
-    }
+    launch_neighbour_means(st, n, xyz, scr, 0);
+    const float *md = reinterpret_cast<const float *>(scr);
+    const dim3 grid((n + KN_BLOCK - 1) / KN_BLOCK), block(KN_BLOCK);
     hipLaunchKernelGGL(init_convex_kernel, grid, block, 0, st, xyz, rgb, md, a, *out);
     e = hipGetLastError();
     (void)hipFreeAsync(scr, st);

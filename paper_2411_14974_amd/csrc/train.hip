@@ -3,7 +3,7 @@
 //
 // * the photometric loss L = (1 - lambda) L1 + lambda (1 - SSIM) and its
 //   gradient with respect to the rendered image, in one pass down strips of
-//   columns: the rows' moments x, y, x^2 + y^2 and xy are blurred with the
+//   columns: the rows' moments x, y, (x - y)^2 and xy are blurred with the
 //   11x11 Gaussian window (separably, zero padding), each row of blurred
 //   moments gives the SSIM map and its partial derivatives with respect to
 //   them, and the partials' rows are blurred in turn (the window is symmetric:
@@ -248,7 +248,7 @@ constexpr int SS_OUT = SS_BLOCK - 2 * SS_HALO;
 __global__ __launch_bounds__(SS_BLOCK) void ssim_kernel(const float *__restrict__ x, const float *__restrict__ y, SsimArgs a,
                                                         float *__restrict__ grad, float *__restrict__ block_loss)
 {
-    __shared__ float4 s_in[2][SS_BLOCK + 2 * SS_HALO]; // x, y, x^2 + y^2, xy
+    __shared__ float4 s_in[2][SS_BLOCK + 2 * SS_HALO]; // x, y, (x - y)^2, xy
     __shared__ float4 s_p[2][SS_BLOCK + 2 * SS_HALO];  // dS/dmu_x, dS/dE[x^2], dS/dE[xy]
     const int t = threadIdx.x;
     const int c = blockIdx.x * SS_OUT - SS_HALO + t; // the thread's column
@@ -269,8 +269,9 @@ __global__ __launch_bounds__(SS_BLOCK) void ssim_kernel(const float *__restrict_
         if (!(ok && in_b)) xb = yb = 0.0f;
     };
     auto store = [&](int buf) {
-        s_in[buf][t] = make_float4(xa, ya, fmaf(xa, xa, ya * ya), xa * ya);
-        if (t < 2 * SS_HALO) s_in[buf][SS_BLOCK + t] = make_float4(xb, yb, fmaf(xb, xb, yb * yb), xb * yb);
+        const float da = xa - ya, db = xb - yb;
+        s_in[buf][t] = make_float4(xa, ya, da * da, xa * ya);
+        if (t < 2 * SS_HALO) s_in[buf][SS_BLOCK + t] = make_float4(xb, yb, db * db, xb * yb);
     };
     // the halves of s_p's halo that no thread writes are read only for columns
     // without an output
@@ -316,18 +317,21 @@ __global__ __launch_bounds__(SS_BLOCK) void ssim_kernel(const float *__restrict_
             q[2] = j == 0 ? a.g[0] * h.z : fmaf(a.g[j], h.z, q[2]);
             q[3] = j == 0 ? a.g[0] * h.w : fmaf(a.g[j], h.w, q[3]);
         }
-        {   // row r - 5 is complete: S = A1 A2 / (B1 B2) and its partials
+        {   // row r - 5 is complete: S = A1 A2 / (B1 B2) and its partials, with A1 = B1 - md^2
+            // and A2 = B2 - v, v the variance of x - y: small differences taken as such
+            // (equal images have a gradient of exactly 0), and B2's variances as v and twice the
+            // covariance, whose terms are no larger than the sum
             const float *q = m[(p + SS_R + 1) % SS_N];
             const int s = r - SS_R;
-            const float mx = q[0], my = q[1], mm = mx * mx + my * my, mxy = mx * my;
-            const float A1 = 2.0f * mxy + SS_C1, A2 = 2.0f * (q[3] - mxy) + SS_C2;
-            const float B1 = mm + SS_C1, B2 = (q[2] - mm) + SS_C2;
-            const float i1 = 1.0f / B1, i2 = 1.0f / B2, ii = i1 * i2;
-            const float S = A1 * A2 * ii;
+            const float mx = q[0], my = q[1], md = mx - my, v = fmaf(-md, md, q[2]);
+            const float i1 = 1.0f / (fmaf(mx, mx, my * my) + SS_C1);
+            const float i2 = 1.0f / ((2.0f * fmaf(-mx, my, q[3]) + SS_C2) + v);
+            const float l = md * md * i1, w = v * i2, q1 = 1.0f - l, q2 = 1.0f - w; // q1 = A1 / B1, q2 = A2 / B2
+            const float S = q1 * q2;
             const bool ok = col_in && s >= 0 && s < a.H;
-            const float d0 = 2.0f * (my * (A2 - A1) * ii + mx * S * (i2 - i1));
+            const float d0 = 2.0f * (i1 * q2 * fmaf(mx, l, -md) + i2 * q1 * fmaf(-mx, w, md));
             s_p[i & 1][SS_HALO + t] =
-                make_float4(ok ? d0 : 0.0f, ok ? -S * i2 : 0.0f, ok ? 2.0f * A1 * ii : 0.0f, 0.0f);
+                make_float4(ok ? d0 : 0.0f, ok ? -S * i2 : 0.0f, ok ? 2.0f * q1 * i2 : 0.0f, 0.0f);
             if (owner && s >= r0 && s < r1) sum -= a.lambda * S;
         }
         // partials of row r - 6 (last step's), into the rows r - 11 .. r - 1

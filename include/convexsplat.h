@@ -397,8 +397,9 @@ int cs_densify(cs_ctx *ctx, const cs_scene *scene, const float *accum, const flo
  * DEVICE) and ADDS L to *loss (DEVICE, one float; the caller zeroes it).  The
  * mask term of the equation belongs to a learnable-mask extension that this
  * rasterizer does not have.  Uses
- * stream-ordered scratch: one float per workgroup, and 36 bytes per pixel for images
- * of 96k to 656k pixels (12 where dl_drgb overlaps an input). */
+ * stream-ordered scratch: one float per workgroup, and 36 bytes per pixel for small
+ * images (up to some 0.7 Mpixel, narrow ones beyond; 12 for larger ones where
+ * dl_drgb overlaps an input). */
 int cs_ssim_loss_grad(cs_ctx *ctx, const float *rgb, const float *target, int32_t width, int32_t height, float lambda,
                       float *dl_drgb, float *loss, void *hip_stream);
 

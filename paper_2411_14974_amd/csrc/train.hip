@@ -7,9 +7,9 @@
 //   11x11 Gaussian window (separably, zero padding), each row of blurred
 //   moments gives the SSIM map and its partial derivatives with respect to
 //   them, and the partials' rows are blurred in turn (the window is symmetric:
-//   the same blur is its adjoint) and combined with x and y into dL/dx; images
-//   that fill the chip only a few times over take the two blurs as two passes
-//   over tiles, with the partials in memory between them;
+//   the same blur is its adjoint) and combined with x and y into dL/dx; small
+//   and narrow images take the two blurs as two passes over tiles, with the
+//   partials in memory between them;
 // * the fused Adam step on the raw parameters with their activations
 //   (sigmoid opacity, exponential delta and sigma): one launch per parameter
 //   array, one element per thread and iteration, read raw, m, v and
@@ -41,7 +41,7 @@ struct SsimArgs {
 };
 
 // ---- two passes over tiles, with the partials of every pixel in memory between
-//      them: images of SS_TILES_FROM to SS_TILES_TO pixels (see there)
+//      them: small and narrow images (ssim_by_tiles)
 
 constexpr int SS_TILE = 16;                 // output pixels per side of a workgroup
 constexpr int SS_IN = SS_TILE + 2 * SS_R;   // input rows / columns with the halo
@@ -239,8 +239,8 @@ __global__ __launch_bounds__(SS_TILE * SS_TILE) void ssim_grad_kernel(const floa
 // Bound by VALU issue: 154 fused multiply-adds of the blurs and about 80 other
 // instructions per column and step, 20 warm-up rows per workgroup and 30 of 256
 // columns of halo.  Two passes over tiles with the nine partials of a pixel in
-// memory between them, which read 26 x 26 pixels for 16 x 16, took 157 us at
-// 1920x1080; this takes 106 us.
+// memory between them, which read 26 x 26 pixels for 16 x 16, take 144 us at
+// 1920x1080; this takes 103 us.
 template <int P> struct Phase { static constexpr int value = P; };
 constexpr int SS_BLOCK = 256;
 constexpr int SS_HALO = 3 * SS_R;
@@ -387,30 +387,39 @@ __global__ __launch_bounds__(SS_BLOCK) void ssim_kernel(const float *__restrict_
 // hide each other's latencies, and more warm-up steps.  A step of k workgroups
 // on one CU (at most 4 fit) was measured at 1.08, 1.40, 1.74 and 2.1 us for k = 1
 // to 4 (120, 60, 40 and 30 rows at 1920x1080: 152, 113, 106, 108 us): 0.74 + 0.34
-// k; the rows with the least steps x price are taken.
-int ssim_rows(int strips, int H, int cus)
+// k; the rows with the least steps x price are taken.  *us: that product.
+int ssim_rows(int strips, int H, int cus, double *us)
 {
     int best = H;
-    double least = 1e300;
-    for (int segs = 1; segs <= H; ++segs) {
-        const int rows = (H + segs - 1) / segs, wgs = strips * ((H + rows - 1) / rows);
-        const int k = (wgs + cus - 1) / cus;
+    *us = 1e300;
+    for (int rows = H;;) {
+        const int segs = (H + rows - 1) / rows, k = (strips * segs + cus - 1) / cus;
         if (k > 8 && segs > 1) break;
         const double cost = (rows + 4 * SS_R + 1) * (k / 4 * 2.1 + (k % 4 ? 0.74 + 0.34 * (k % 4) : 0.0));
-        if (cost < least) {
-            least = cost;
+        if (cost < *us) {
+            *us = cost;
             best = rows;
         }
+        if (rows == 1) break;
+        const int more = (H + rows - 2) / (rows - 1); // segments of a row less
+        rows = (H + more - 1) / more;
     }
     return best;
 }
 
-// Pixels of the images that go through the tiles.  A strip's step costs about a
-// microsecond however few workgroups run, which tiles undercut while the image
-// fills the chip but a few times over (us, strips / tiles: 200x120 29 / 33,
-// 400x300 34 / 32, 640x427 41 / 34, 900x600 56 / 54, 979x546 55 / 55, 1000x640 60 / 58,
-// 1100x700 64 / 68, 1297x840 72 / 83, 1920x1080 109 / 147).
-constexpr size_t SS_TILES_FROM = 96 * 1024, SS_TILES_TO = 656 * 1024;
+// Whether an image goes through the tiles: a strip's step costs about a
+// microsecond however few workgroups run, and strips of a narrow image are
+// partly empty, where tiles undercut them.  Tiles take 15.6 us + 15.8 ns each and
+// no less than 24 us, strips 2 us over their steps (above).  us, strips / tiles:
+// 16x16 27 / 25, 300x300 32 / 26, 16x4096 44 / 27, 640x427 41 / 35, 900x600 56 / 50,
+// 979x546 55 / 51, 1000x640 60 / 54, 76x16384 110 / 96; 500x1500 60 / 65, 160x8192
+// 90 / 97, 1100x700 59 / 65, 100x16384 110 / 126, 1297x840 72 / 85, 1920x1080
+// 103 / 144.
+bool ssim_by_tiles(int width, int height, double strips_us)
+{
+    const double tiles = (double)((width + SS_TILE - 1) / SS_TILE) * ((height + SS_TILE - 1) / SS_TILE);
+    return std::max(24.0, 15.6 + 0.0158 * tiles) <= strips_us + 2.0;
+}
 
 __global__ __launch_bounds__(256) void copy_floats_kernel(size_t n, const float *__restrict__ from, float *__restrict__ to)
 {
@@ -641,9 +650,10 @@ int cs_ssim_loss_grad(cs_ctx *ctx, const float *rgb, const float *target, int32_
     int cus = 256;
     (void)hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, ctx->device);
     const int strips = (a.W3 + SS_OUT - 1) / SS_OUT;
-    a.rows = ssim_rows(strips, height, std::max(1, cus));
-    const size_t pixels = (size_t)width * height, n = 3 * pixels;
-    const bool tiles = pixels >= SS_TILES_FROM && pixels < SS_TILES_TO;
+    double strips_us = 0.0;
+    a.rows = ssim_rows(strips, height, std::max(1, cus), &strips_us);
+    const size_t n = 3 * (size_t)width * height;
+    const bool tiles = ssim_by_tiles(width, height, strips_us);
     const dim3 grid = tiles ? dim3((width + SS_TILE - 1) / SS_TILE, (height + SS_TILE - 1) / SS_TILE)
                             : dim3(strips, (height + a.rows - 1) / a.rows);
     const int nb = (int)(grid.x * grid.y);

@@ -59,9 +59,25 @@ def pair_cost(stage, T):
     return TRANS_SLOTS * (T + 4) + 2 * T + (12 * T + 30)
 
 
+PAIR_STAGES = ("emit", "tile_sort", "ranges")
+
+
+def cell_pairs(state, n, width, height, tile=16):
+    """(cell, convex) pairs of a one-view forward, from its tile lists: a view's
+    cells are the smallest blocks of 1, 2 x 2 or 4 x 4 tiles of which 512 cover it
+    (else 4 x 4)."""
+    ranges, ids = state.tile_lists()
+    tx, ty = -(-width // tile), -(-height // tile)
+    shift = next((s for s in (0, 1) if -(-tx >> s) * -(-ty >> s) <= 512), 2)
+    t = np.repeat(np.arange(tx * ty, dtype=np.int64), ranges[:, 1] - ranges[:, 0])
+    cell = ((t // tx) >> shift) * tx + ((t % tx) >> shift)
+    return int(np.unique(cell * n + ids).size)
+
+
 def stage_work(stage, n, m, K, deg, cnt):
-    """Algorithmic bytes (or VALU lane-operations) of one launch of a stage;
-    cnt: the device work counters of the step (cs_state_counters)."""
+    """Algorithmic bytes (or VALU lane-operations) of one launch of a stage; m:
+    (cell, convex) pairs (cell_pairs, for PAIR_STAGES); cnt: the device work
+    counters of the step (cs_state_counters)."""
     nc = (deg + 1) ** 2
     T_mean = cnt["sum_T_full"] / max(cnt["full_bwd"], 1)
     rec = 48 + 24 * T_mean  # header + the T hull lines written
@@ -71,14 +87,12 @@ def stage_work(stage, n, m, K, deg, cnt):
         return "hbm", n * (4 + 4 * 16)
     if stage == "bin_scan":  # read id 4 + binning record 16; write it in depth order 16 + count 4 + offset 4
         return "hbm", n * 44
-    # the pairs that are emitted and sorted are (cell, convex) pairs, of which there
-    # is at least one for every 16 (tile, convex) pairs m, the count at hand
     if stage == "emit":  # per convex: id, offset, binning record 24 B; per pair: write 8 B
-        return "hbm", n * 24 + m // 16 * 8
+        return "hbm", n * 24 + m * 8
     if stage == "tile_sort":  # one histogram read (4 B) + one pass x (read 8 B + write 8 B) over the pairs
-        return "hbm", m // 16 * (4 + 16)
-    if stage == "ranges":
-        return "hbm", m // 16 * 4
+        return "hbm", m * (4 + 16)
+    if stage == "ranges":  # a sort of more than one pass: its keys read (one pass leaves the ranges itself)
+        return "hbm", m * 4
     if stage == "render_fwd":  # full pairs x the forward per-pair cost at the measured mean hull size
         return "alu", cnt["full"] * pair_cost(stage, T_mean)
     if stage == "render_bwd":
@@ -592,7 +606,12 @@ def main():
     n, K, deg = scene.n, scene.k, scene.deg
     avg = {s: (t / c if c else 0.0) for s, (t, c) in timing.items()}
     dom = max(avg, key=avg.get)
-    bound, work = stage_work(dom, n, cnt["pairs"], K, deg, cnt)
+    m = 0
+    if dom in PAIR_STAGES:
+        st = step(plain_params)
+        m = cell_pairs(st, n, W, H)
+        st.release()
+    bound, work = stage_work(dom, n, m, K, deg, cnt)
     sec = avg[dom] / 1e3
     if bound == "hbm":
         achieved, peak, unit = work / sec / 1e9, HBM_PEAK_GBS, "GB/s"

@@ -11,9 +11,9 @@
 //   and narrow images take the two blurs as two passes over tiles, with the
 //   partials in memory between them;
 // * the fused Adam step on the raw parameters with their activations
-//   (sigmoid opacity, exponential delta and sigma): one launch per parameter
-//   array, one element per thread and iteration, read raw, m, v and
-//   dL/d(activated) (16 B), write raw, m, v and the new activated value (16 B).
+//   (sigmoid opacity, exponential delta and sigma): one launch for all arrays,
+//   four elements per thread; an element reads raw, m, v and dL/d(activated)
+//   (16 B) and writes raw, m, v and the new activated value (16 B).
 #include <algorithm>
 #include <cmath>
 
@@ -492,7 +492,7 @@ __device__ __forceinline__ void adam_element(float r, float gact, float m0, floa
 }
 
 typedef float f32x4 __attribute__((ext_vector_type(4)));
-constexpr int ADAM_BLOCK = 256, ADAM_VECS = 1, ADAM_CHUNK = ADAM_BLOCK * ADAM_VECS * 4; // elements a workgroup
+constexpr int ADAM_BLOCK = 256, ADAM_CHUNK = ADAM_BLOCK * 4; // elements a workgroup
 
 template <int ACT>
 __device__ __forceinline__ void adam_chunk(const AdamArgs &a, const AdamPart &p, uint32_t chunk)
@@ -517,27 +517,16 @@ __device__ __forceinline__ void adam_chunk(const AdamArgs &a, const AdamPart &p,
     }
     const f32x4 *raw = reinterpret_cast<const f32x4 *>(p.raw + e0), *g = reinterpret_cast<const f32x4 *>(p.g + e0);
     const f32x4 *m = reinterpret_cast<const f32x4 *>(p.m + e0), *v = reinterpret_cast<const f32x4 *>(p.v + e0);
-    f32x4 r4[ADAM_VECS], g4[ADAM_VECS], m4[ADAM_VECS], v4[ADAM_VECS];
-    const uint32_t full = left / 4;
-#pragma unroll
-    for (int k = 0; k < ADAM_VECS; ++k) {
-        const uint32_t q = min(threadIdx.x + (uint32_t)(k * ADAM_BLOCK), max(full, 1u) - 1u);
-        if (full == 0) break;
-        r4[k] = __builtin_nontemporal_load(raw + q);
-        g4[k] = __builtin_nontemporal_load(g + q);
-        m4[k] = __builtin_nontemporal_load(m + q);
-        v4[k] = __builtin_nontemporal_load(v + q);
-    }
-#pragma unroll
-    for (int k = 0; k < ADAM_VECS; ++k) {
-        const uint32_t q = threadIdx.x + (uint32_t)(k * ADAM_BLOCK);
-        if (q >= full) break;
+    const uint32_t full = left / 4, q = threadIdx.x;
+    if (q < full) {
+        const f32x4 r4 = __builtin_nontemporal_load(raw + q), g4 = __builtin_nontemporal_load(g + q);
+        const f32x4 m4 = __builtin_nontemporal_load(m + q), v4 = __builtin_nontemporal_load(v + q);
         uint32_t col = row ? (c0 + 4u * q) % row : 0u;
         f32x4 rn, mm, vv, av;
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
             float x, y, z;
-            adam_element<ACT>(r4[k][j], g4[k][j], m4[k][j], v4[k][j], rate(col), a, x, y, z);
+            adam_element<ACT>(r4[j], g4[j], m4[j], v4[j], rate(col), a, x, y, z);
             rn[j] = x;
             mm[j] = y;
             vv[j] = z;

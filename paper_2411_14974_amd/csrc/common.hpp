@@ -136,7 +136,6 @@ constexpr int EVAL_SLOTS = 16384;
 // follow the forward's EVAL_SLOTS
 enum : int { EV_TESTED = 0, EV_FULL = 1, EV_SUM_T = 2, EV_WAVES = 3, EVAL_FIELDS = 4 };
 
-// Device counters of one frame (u32 words).
 // Per-instance binning record (16 bytes): the tile rectangle, tx0 | ty0 << 16
 // and tx1 | ty1 << 16 (empty when tx0 > tx1; a view has at most 2048 tiles a
 // side), the view's cell shift and the number of (cell, convex) pairs in the bits

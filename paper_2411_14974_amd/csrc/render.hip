@@ -436,14 +436,14 @@ struct Claims {
 // to front, and counts those with the tile's mask bit per wavefront; after a
 // barrier whole sub-rounds of NT entries are appended in order, as (id,
 // position in the cell's list), until enough are queued (the rest is read
-// again by the next round).  Only the entries that are appended have their
+// again by the next round).  Only the entries that a round appends have their
 // ids read.  About a quarter of a cell's entries are a given tile's at 1M
 // convexes and 1080p, but a twelfth where convexes are smaller than a tile
 // (200k convexes, 256 x 256), hence rounds of 4 NT: with rounds of NT that
 // view's compositing took twice as long.
-// While a batch is composited one sub-round is in flight
-// (request), which the kernels count before and appends after the barrier of the next
-// batch (publish, append): where the hits are dense enough, the list is then
+// While a batch is composited one sub-round is in flight, every entry's key and id
+// (request), which the kernels count before and append after the barrier of the
+// next batch (publish, append): where the hits are dense enough, the list is then
 // read on without a wait.
 constexpr int FEED_SUB = 4;
 template <int NT, int RING, bool REVERSE> struct TileFeed {
@@ -710,10 +710,6 @@ template <int K> __device__ __forceinline__ int acc_slot(int qv, int T)
     return qv < T ? qv : qv < 2 * T ? K + (qv - T) : qv < 3 * T ? 2 * K + (qv - 2 * T) : 3 * K + (qv - 3 * T);
 }
 
-// Backward of one record for the wavefront's pixels: recompute the pair (the
-// forward's decisions, bit for bit), recover T_n, form the pixel's gradient
-// values, sum them over the wavefront and add the four row sums into the
-// record's LDS slot (compact layout, bwd_padded<K>() floats).
 // A pixel's state in the back-to-front walk: dL/dC, the transmittance after
 // its last contributor, the transmittance before the pair being walked (T_n,
 // recovered by division), and the colour composited behind it.
@@ -784,6 +780,10 @@ template <int NP> __device__ __forceinline__ void add_wave_sums(float *val, floa
     }
 }
 
+// Backward of one record for the wavefront's pixels: recompute the pair (the
+// forward's decisions, bit for bit), recover T_n, form the pixel's gradient
+// values, sum them over the wavefront and add the four row sums into the
+// record's LDS slot (compact layout, bwd_padded<K>() floats).
 template <int K, int NL>
 __device__ __forceinline__ void bwd_record(const uint8_t *rec, bool live, int u, int y, float pxf, float pyf,
                                            float eps, BwdPixel &P, float *slot, bool &full)

@@ -229,6 +229,8 @@ __device__ inline uint32_t bin_count(uint4 b)
     return c;
 }
 
+// Cells from tile t0 to tile t1 of a row or column.
+__host__ __device__ inline uint32_t cells_met(int t0, int t1, uint32_t s) { return ((uint32_t)t1 >> s) - ((uint32_t)t0 >> s) + 1u; }
 // The block of cells that band r of a larger rectangle meets: its first cell
 // and its cells across and down (0 when the band is empty).
 struct CellBlock { uint32_t x, y, nx, ny; };
@@ -240,16 +242,24 @@ __host__ __device__ inline CellBlock band_cells(uint64_t mask, int tx0, int ty0,
     if (ncol == 0) return {x, y, 0u, 0u};
     return {x, y, ((uint32_t)(tx0 + col0 + ncol - 1) >> s) - x + 1u, ((uint32_t)(ty0 + row0 + nrow - 1) >> s) - y + 1u};
 }
-// (cell, convex) pairs of a rectangle: one for every cell with a kept tile; of a
-// larger rectangle one for every band that has kept tiles in the cell (each with
-// the band's part of the tiles).  Every pair holds a tile that no other does, so
-// they are never more than the (tile, convex) pairs.
+// (cell, convex) pairs of a rectangle, never more than its (tile, convex) pairs:
+//  - of at most 64 tiles: one for every cell that it meets where these are no more
+//    than its kept tiles (a cell without any then makes a pair with an empty mask),
+//    else one for every cell with a kept tile.  (Only cells with a kept tile
+//    for every convex: 3 % fewer pairs, but a step of 1M convexes at 1920 x 1080 takes 916
+//    instead of 912 us, of 317k at 979 x 546 419 instead of 416: preprocess and emission
+//    tell the cells apart for longer than their pairs would take.)
+//  - of more: one for every band that has kept tiles in a cell, with the band's part
+//    of the tiles.
 __host__ __device__ inline uint32_t rect_cells(int tx0, int ty0, int tx1, int ty1, uint64_t mask, uint32_t s)
 {
     if (tx0 > tx1 || ty0 > ty1) return 0u;
     const int tw = tx1 - tx0 + 1, th = ty1 - ty0 + 1;
-    if (tw * th <= 64)
+    if (tw * th <= 64) {
+        const uint32_t kept = (uint32_t)__builtin_popcountll(mask), all = cells_met(tx0, tx1, s) * cells_met(ty0, ty1, s);
+        if (s == 0 || all <= kept) return s == 0 ? kept : all;
         return (uint32_t)__builtin_popcountll(cell_marks(mask, (uint32_t)tx0, (uint32_t)ty0, (uint32_t)tw, (uint32_t)th, s));
+    }
     uint32_t c = 0;
 #pragma unroll
     for (int r = 0; r < BIG_BANDS; ++r) {

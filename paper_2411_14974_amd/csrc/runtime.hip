@@ -225,7 +225,7 @@ int Frame::init(int n_, int K_, int deg_, int V_, size_t tiles, size_t pix, hipS
 // pairs: the cell pairs with a margin.  A graph's frame (by_tile_pairs) is sized
 // by the tile pairs, of which a caller is promised the margin (never less than
 // before), and a frame past it is reported: a frame never has more cell pairs than tile pairs
-// (bin_cells), so any within the promise fits, whatever share of its cells'
+// (rect_cells), so any within the promise fits, whatever share of its cells'
 // tiles its convexes reach (surplus workgroups of the grids leave at once).
 size_t Frame::pair_room(uint32_t cell_pairs, uint32_t tile_pairs, double margin)
 {

@@ -780,11 +780,9 @@ bool launch_small_order(hipStream_t st, uint32_t n, const uint32_t *keys, const 
 // cooperatively: their pair ranges are contiguous ([offsets[r], offsets[r] +
 // counts[r]) in rank order), so the workgroup strides over the whole run with
 // one pair per thread (coalesced stores).  Within an instance the pairs run
-// row-major over the cells with kept tiles, band by band in a large rectangle
-// (see bin_cells); a pair's key is the cell with the mask of its kept tiles
-// above (see FrameHeader).  Instance id = view * n_convex + convex.  30 us for 1M
-// convexes at 1920 x 1080 (pairs of every cell that the rectangle meets: 27 us, and
-// 2 us more in their sort).
+// row-major over its cells, band by band in a large rectangle (see rect_cells); a
+// pair's key is the cell with the mask of its kept tiles above (see FrameHeader).
+// Instance id = view * n_convex + convex.
 constexpr int EMIT_BLOCK = 256;
 constexpr int EMIT_ITEMS = 8;
 constexpr int EMIT_CHUNK = EMIT_BLOCK * EMIT_ITEMS; // pairs whose owners are found per round
@@ -855,8 +853,9 @@ __global__ __launch_bounds__(EMIT_BLOCK) void emit_pairs_kernel(
     __shared__ uint4 s_bin[EMIT_BLOCK];
     __shared__ uint32_t s_base[EMIT_BLOCK]; // the view's cell_off
     __shared__ uint32_t s_cx[EMIT_BLOCK];   // the view's cells per row
-    // a rectangle of at most 64 tiles: its cell marks (low, high word); a larger one:
-    // the pairs up to the end of its first bands
+    // a rectangle of at most 64 tiles: its cell marks (low, high word) and whether every
+    // cell that it meets makes a pair (then there are no marks); a larger one: the pairs up to the
+    // end of its first bands
     __shared__ uint32_t s_in[3][EMIT_BLOCK];
     static_assert(BIG_BANDS == 4, "a word for every band but the last");
     __shared__ uint32_t s_own[EMIT_CHUNK];  // owner (block-local convex) of each pair of the chunk
@@ -880,12 +879,17 @@ __global__ __launch_bounds__(EMIT_BLOCK) void emit_pairs_kernel(
             s_base[tid] = (uint32_t)vd.cell_off;
             const uint32_t shift = bin_shift(b);
             s_cx[tid] = ((uint32_t)vd.tiles_x + (1u << shift) - 1u) >> shift;
-            const uint32_t tx0 = bin_tx0(b), ty0 = bin_ty0(b), tw = bin_tx1(b) - tx0 + 1u, th = bin_ty1(b) - ty0 + 1u;
+            const uint32_t tx0 = bin_tx0(b), ty0 = bin_ty0(b), tx1 = bin_tx1(b), ty1 = bin_ty1(b);
+            const uint32_t tw = tx1 - tx0 + 1u, th = ty1 - ty0 + 1u;
             const uint64_t mask = (uint64_t)b.z | ((uint64_t)b.w << 32);
             if (tw * th <= 64u) {
-                const uint64_t marks = cell_marks(mask, tx0, ty0, tw, th, shift);
-                s_in[0][tid] = (uint32_t)marks;
-                s_in[1][tid] = (uint32_t)(marks >> 32);
+                const bool all = count == cells_met((int)tx0, (int)tx1, shift) * cells_met((int)ty0, (int)ty1, shift);
+                s_in[2][tid] = all ? 1u : 0u;
+                if (!all) {
+                    const uint64_t marks = cell_marks(mask, tx0, ty0, tw, th, shift);
+                    s_in[0][tid] = (uint32_t)marks;
+                    s_in[1][tid] = (uint32_t)(marks >> 32);
+                }
             } else {
                 uint32_t end = 0;
 #pragma unroll
@@ -951,15 +955,20 @@ __global__ __launch_bounds__(EMIT_BLOCK) void emit_pairs_kernel(
             const uint32_t tx0 = bin_tx0(b), ty0 = bin_ty0(b), tx1 = bin_tx1(b), ty1 = bin_ty1(b), shift = bin_shift(b);
             const uint32_t tw = tx1 - tx0 + 1u, th = ty1 - ty0 + 1u;
             const uint64_t kept = (uint64_t)b.z | ((uint64_t)b.w << 32);
-            const uint32_t in0 = s_in[0][lo], in1 = s_in[1][lo];
+            const uint32_t in0 = s_in[0][lo], in1 = s_in[1][lo], in2 = s_in[2][lo];
             uint32_t cx, cy, mask;
-            if (tw * th <= 64u) { // the q-th marked cell
-                const uint32_t at = nth_set_bit((uint64_t)in0 | ((uint64_t)in1 << 32), q), row = small_div(at, tw);
-                cx = (tx0 + at - row * tw) >> shift;
-                cy = (ty0 + row) >> shift;
+            if (tw * th <= 64u) {
+                if (in2) { // the q-th cell, row-major
+                    const uint32_t cw = cells_met((int)tx0, (int)tx1, shift), row = small_div(q, cw);
+                    cx = (tx0 >> shift) + q - row * cw;
+                    cy = (ty0 >> shift) + row;
+                } else { // the q-th marked one
+                    const uint32_t at = nth_set_bit((uint64_t)in0 | ((uint64_t)in1 << 32), q), row = small_div(at, tw);
+                    cx = (tx0 + at - row * tw) >> shift;
+                    cy = (ty0 + row) >> shift;
+                }
                 mask = cell_mask(kept, (int)tx0, (int)ty0, (int)tw, (int)th, (int)(cx << shift), (int)(cy << shift), (int)shift);
             } else { // the q-th cell of the bands, band by band
-                const uint32_t in2 = s_in[2][lo];
                 const int r = (q >= in0) + (q >= in1) + (q >= in2);
                 const uint32_t before = r == 0 ? 0u : r == 1 ? in0 : r == 2 ? in1 : in2;
                 const CellBlock c = band_cells(kept, (int)tx0, (int)ty0, (int)tw, (int)th, r, shift);

@@ -14,8 +14,8 @@
 // operations of a point's (subtract, square, add, each rounded monotonically),
 // so it never exceeds the computed distance of a point inside: pruning drops no
 // neighbour, and the three distances are the brute-force search's bit for bit.
-// Should the sort report that one of its bounded waits ran out, its order is not
-// used and the search's kernel compares every pair instead.
+// Should the sort report that one of its bounded waits ran out, the points keep the
+// cloud's order: the search is exact in any order, only slower.
 #include <algorithm>
 #include <cmath>
 #include <vector>
@@ -204,17 +204,18 @@ template <int G> __device__ __forceinline__ void store_box(float4 *box, float3 l
 }
 
 // The points in curve order (w: the cloud index; places past n are not a
-// number) and the leaves' boxes: 16 lanes per leaf.
+// number) and the leaves' boxes: 16 lanes per leaf.  *err nonzero (the sort
+// failed: ids may name a point twice and another not at all): in the cloud's order.
 __global__ __launch_bounds__(KN_BLOCK) void leaf_kernel(int n, int nleaves, const float *__restrict__ xyz,
-                                                        const uint32_t *__restrict__ ids, float4 *__restrict__ pts,
-                                                        float4 *__restrict__ boxes)
+                                                        const uint32_t *__restrict__ ids, const uint32_t *__restrict__ err,
+                                                        float4 *__restrict__ pts, float4 *__restrict__ boxes)
 {
     const size_t r = (size_t)blockIdx.x * KN_BLOCK + threadIdx.x;
     const size_t leaf = r / LEAF;
     if (leaf >= (size_t)nleaves) return; // whole groups of LEAF lanes
     float4 p = make_float4(NAN, NAN, NAN, 0.0f);
     if (r < (size_t)n) {
-        const uint32_t i = min(ids[r], (uint32_t)n - 1u);
+        const uint32_t i = *err ? (uint32_t)r : min(ids[r], (uint32_t)n - 1u);
         p = make_float4(xyz[3 * (size_t)i], xyz[3 * (size_t)i + 1], xyz[3 * (size_t)i + 2], __uint_as_float(i));
     }
     pts[r] = p;
@@ -254,23 +255,15 @@ __device__ __forceinline__ float box_gap2(float3 alo, float3 ahi, float4 blo, fl
 // instructions per query and candidate) and by how few leaves are visited: 100k
 // points take 7.83 ms by brute force, 0.31 ms with 64 queries and 64-point
 // leaves, 1.71 ms with leaves chosen by the 16 points' box alone, 0.11 ms here.
-// *err nonzero (the sort failed): the queries are 16 points of the cloud as it
-// stands, each compared with all of it.
 __global__ __launch_bounds__(KN_BLOCK) void knn3_curve_kernel(int nleaves, int nnodes, const float4 *__restrict__ pts,
                                                               const float4 *__restrict__ boxes,
                                                               const float4 *__restrict__ nodes, int n,
-                                                              const float *__restrict__ xyz, const uint32_t *__restrict__ err,
                                                               float *__restrict__ mean_dist)
 {
     const int leaf = __builtin_amdgcn_readfirstlane((int)((blockIdx.x * KN_BLOCK + threadIdx.x) >> 6));
     if (leaf >= nleaves) return;
     const int lane = threadIdx.x & 63, ql = lane & (LEAF - 1), group = lane / LEAF;
-    const bool sorted = *err == 0u;
-    float4 q = pts[(size_t)leaf * LEAF + ql];
-    if (!sorted) {
-        const size_t i = min((size_t)leaf * LEAF + ql, (size_t)n - 1);
-        q = make_float4(xyz[3 * i], xyz[3 * i + 1], xyz[3 * i + 2], __uint_as_float((uint32_t)i));
-    }
+    const float4 q = pts[(size_t)leaf * LEAF + ql];
     const bool active = finite3(q.x, q.y, q.z);
     const float4 l4 = boxes[2 * (size_t)leaf], h4 = boxes[2 * (size_t)leaf + 1];
     const float3 glo = make_float3(l4.x, l4.y, l4.z), ghi = make_float3(h4.x, h4.y, h4.z);
@@ -301,17 +294,9 @@ __global__ __launch_bounds__(KN_BLOCK) void knn3_curve_kernel(int nleaves, int n
         for (int o = 8; o > 0; o >>= 1) m = fmaxf(m, __shfl_xor(m, o, 64));
         gmax = __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(m)));
     };
-    if (sorted) {
+    {
         const int l = leaf - 1 + group;
         scan(l < nleaves ? l : -1); // (l = -1 before the first leaf)
-    } else {
-        const uint32_t self = __float_as_uint(q.w);
-        for (uint32_t j = group; j < (uint32_t)n; j += 64 / LEAF) {
-            const float dx = xyz[3 * (size_t)j] - q.x, dy = xyz[3 * (size_t)j + 1] - q.y, dz = xyz[3 * (size_t)j + 2] - q.z;
-            const float e = (dx * dx + dy * dy) + dz * dz;
-            insert(e < INFINITY && j != self ? e : INFINITY);
-        }
-        nnodes = 0; // no leaf to visit
     }
     // whether the lane's box holds a point that some query may need: the 16
     // points' leaf may span a jump of the curve, so its box alone says little
@@ -461,10 +446,10 @@ void launch_neighbour_means(hipStream_t st, int n, const float *xyz, uint8_t *sc
     hipLaunchKernelGGL(morton_kernel, grid, block, 0, st, n, xyz, cube, keys, ids, z);
     radix_sort(st, &keys, &ids, &keys2, &ids2, (uint32_t)n, nullptr, (uint32_t)n, 31, temp, 8, err, true, nullptr, 0);
     const dim3 lgrid((unsigned)((nleaves * LEAF + KN_BLOCK - 1) / KN_BLOCK));
-    hipLaunchKernelGGL(leaf_kernel, lgrid, block, 0, st, n, (int)nleaves, xyz, ids, pts, boxes);
+    hipLaunchKernelGGL(leaf_kernel, lgrid, block, 0, st, n, (int)nleaves, xyz, ids, err, pts, boxes);
     hipLaunchKernelGGL(node_kernel, dim3((unsigned)nnodes), dim3(NODE), 0, st, (int)nleaves, boxes, nodes);
     hipLaunchKernelGGL(knn3_curve_kernel, dim3((unsigned)((nleaves * 64 + KN_BLOCK - 1) / KN_BLOCK)), block, 0, st, (int)nleaves,
-                       (int)nnodes, pts, boxes, nodes, n, xyz, err, md);
+                       (int)nnodes, pts, boxes, nodes, n, md);
 }
 
 } // namespace cs

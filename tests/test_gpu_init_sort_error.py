@@ -1,6 +1,6 @@
 """The neighbour search along the curve does without the sort where that
-reports that a wait ran out: every pair is compared, with the same distances
-bit for bit."""
+reports that a wait ran out: the points keep the cloud's order, with the same
+distances bit for bit."""
 import ctypes as C
 
 import pytest

@@ -1145,7 +1145,7 @@ int cs_render_forward_batch(cs_ctx *ctx, const cs_scene *sc, int32_t n_views, co
         F->eval_slots = gx.slots;
         tm.end(CS_STAGE_GRAPH_FWD);
     }
-    F->epoch++;
+    F->epoch = ++ctx->batch_epoch;
     CS_HIP(hipMemcpyAsync(F->h_counters, F->counters, CNT_WORDS * 4, hipMemcpyDeviceToHost, st));
     CS_HIP(hipEventRecord(F->counters_ev, st));
     if (state_out) {

@@ -98,7 +98,7 @@ struct Frame {
     uint64_t kbwd = 0;
     void drop_backward_graphs();
     void drop_graphs();
-    uint64_t epoch = 0;
+    uint64_t epoch = 0; // of the frame's last batched forward, counted over the context's
 
     HostRing *ring = nullptr;
     hipEvent_t ready = nullptr; // recorded when the frame is handed back to the context's cache
@@ -145,6 +145,7 @@ struct cs_ctx {
     hipStream_t capture_stream = nullptr; // graphs are captured here (the null stream cannot be) and launched on the caller's
     cs::Frame *batch = nullptr;
     uint64_t batch_key = 0;
+    uint64_t batch_epoch = 0; // batched forwards in graph mode so far (a new frame may have an old one's address)
     std::map<std::tuple<int, int, int, int, int>, cs_tuning> tune;
     // request loop (serve.hip)
     cs::Server *server = nullptr;

@@ -61,3 +61,26 @@ def test_overflow_is_reported_until_the_next_forward(R, w, h):
             assert float((g[k].double() - gref[k].double()).norm() / gref[k].double().norm()) <= 1e-5, k
         st.release()
     say(f"[overflow {w}x{h}] reported until the next forward, which makes room for {pairs} pairs")
+
+
+def test_state_of_a_replaced_frame_is_refused(R):
+    """A state whose frame was given up for another scene's is refused, also where
+    the new frame lies at the old one's address."""
+    from paper_2411_14974_amd.binding import CS_EINVAL, FLAG_GRAPH, CSError, DeviceScene, make_params
+    rng = np.random.default_rng(3)
+    cams = [scenes.orbit_camera(rng, 200, 150)]
+    dls = [torch.from_numpy(rng.normal(size=(150, 200, 3)).astype(np.float32)).cuda()]
+    p = make_params(flags=FLAG_GRAPH)
+    held = []
+    for _ in range(4):
+        ds = DeviceScene.from_scene(scenes.convexes_around(rng, scenes.uniform_centres(rng, 3000), 6, 1), "cuda:0")
+        _, st = R.forward_batch(ds, cams, p, want_state=True)
+        for old in held:
+            assert R.batch_check(old) == CS_EINVAL
+            with pytest.raises(CSError) as e:
+                R.backward_batch(old, dls)
+            assert e.value.code == CS_EINVAL
+        assert R.batch_check(st) == 0
+        held.append(st)
+    for st in held:
+        st.release()

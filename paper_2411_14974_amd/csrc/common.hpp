@@ -147,6 +147,7 @@ enum : int { EV_TESTED = 0, EV_FULL = 1, EV_SUM_T = 2, EV_WAVES = 3, EVAL_FIELDS
 //    blocks of ceil(tw / 2^BIG_BITS) tiles; field r (2 BIG_BITS bits) holds
 //    band r's kept blocks as the interval bx0 | bx1 << BIG_BITS (empty when
 //    bx0 > bx1), and the band keeps every tile of those blocks.
+
 // The cells that hold a kept tile of a rectangle of at most 64 tiles, each by
 // one bit: that of the cell's first tile in the rectangle (kept or not).
 __host__ __device__ inline uint64_t cell_marks(uint64_t mask, uint32_t tx0, uint32_t ty0, uint32_t tw, uint32_t th, uint32_t s)
